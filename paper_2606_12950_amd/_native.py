@@ -96,6 +96,10 @@ def load():
     lib.maestro_route_ex.argtypes = [i64, P, P, P, P, i32, i32, P, P, P, P, f64, i32, i32, P, P, P, sz, P]
     lib.maestro_route_fitness.argtypes = [i64, P, P, P, P, i32, i32, i32, i32, P, P, P, P, P, P, P, P, P, P, P,
                                           f64, i32, P, P, P]
+    lib.maestro_route_fitness_pruned.argtypes = [i64, P, P, P, P, i32, i32, i32, i32, P, P, P, P, P, P, P, P, P, P, P,
+                                                 f64, i32, P, P, P, sz, P]
+    lib.maestro_route_fitness_workspace.argtypes = [i64, i32, i32, i32, i32, i32, i32]
+    lib.maestro_route_fitness_workspace.restype = sz
     lib.maestro_activation_latency.argtypes = [i32, i32, P, P, P, P, f64, P, P]
     lib.maestro_route_tiered.argtypes = [i64, P, P, P, P, i32, i32, P, P, P, f64, i32, i32, P, P, P, sz, P]
     lib.maestro_adaptive_rho.argtypes = [P, P, i64, f64, f64, P, P, P, sz, P]
@@ -156,6 +160,17 @@ def _workspace(t: Optional[torch.Tensor], name: str = "workspace") -> Optional[t
     if t is not None:
         _dev(t, name, torch.uint8)
     return t
+
+
+def _scratch(n_bytes: int, device, stream) -> Optional[torch.Tensor]:
+    """Scratch for one call on ``stream`` (None: the current one), from that stream's own allocator
+    pool, so that freeing it on return orders its reuse behind the call; None under graph capture."""
+    if stream is None:
+        if torch.cuda.is_current_stream_capturing():
+            return None
+        return torch.empty(n_bytes, dtype=torch.uint8, device=device)
+    with torch.cuda.stream(stream):
+        return _scratch(n_bytes, device, None)
 
 
 def _check(fn: str, status: int):
@@ -462,16 +477,21 @@ def route_fitness(model_id: torch.Tensor, src_id: torch.Tensor, class_id: torch.
     idx, fit = out
     _shape(_dev(idx, "node_idx", torch.int32), "node_idx", (n, k))
     _shape(_dev(fit, "fitness", torch.float32), "fitness", (n, k))
-    st = lib.maestro_route_fitness(n, _ptr(model_id), _ptr(src_id), _ptr(class_id), _ptr(kv_bytes),
-                                   int(n_models), M, rtt_ms.shape[0], class_weights.shape[0],
-                                   _ptr(free_bytes), _ptr(queue_ms), _ptr(act_ms), _ptr(resident_mask),
-                                   _ptr(act_matrix),
-                                   _ptr(deg_ms) if deg_ms is not None else None,
-                                   _ptr(plans.records) if plans is not None else None,
-                                   _ptr(plans.steps) if plans is not None else None,
-                                   _ptr(rtt_ms), _ptr(class_weights), _ptr(bounds),
-                                   float(rho), int(k), _ptr(idx), _ptr(fit), _stream(stream))
-    _check("maestro_route_fitness", st)
+    args = (n, _ptr(model_id), _ptr(src_id), _ptr(class_id), _ptr(kv_bytes), int(n_models), M, rtt_ms.shape[0],
+            class_weights.shape[0], _ptr(free_bytes), _ptr(queue_ms), _ptr(act_ms), _ptr(resident_mask),
+            _ptr(act_matrix), _ptr(deg_ms), _ptr(plans.records) if plans is not None else None,
+            _ptr(plans.steps) if plans is not None else None, _ptr(rtt_ms), _ptr(class_weights), _ptr(bounds),
+            float(rho), int(k), _ptr(idx), _ptr(fit))
+    # code under graph capture gets the kernel without scratch, so that nothing is allocated there
+    ws_bytes = lib.maestro_route_fitness_workspace(n, int(n_models), M, rtt_ms.shape[0], class_weights.shape[0], int(k),
+                                                   plans is not None)
+    if ws_bytes:
+        ws = _scratch(ws_bytes, model_id.device, stream)
+        if ws is not None:
+            _check("maestro_route_fitness_pruned",
+                   lib.maestro_route_fitness_pruned(*args, _ptr(ws), ws_bytes, _stream(stream)))
+            return idx, fit
+    _check("maestro_route_fitness", lib.maestro_route_fitness(*args, _stream(stream)))
     return idx, fit
 
 

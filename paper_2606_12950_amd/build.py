@@ -17,7 +17,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libmaestro.so")
-SOURCES = ("api.hip", "predict.hip", "roles.hip", "route.hip", "fitness.hip", "prioritize.hip")
+SOURCES = ("api.hip", "predict.hip", "roles.hip", "route.hip", "fitness.hip", "fitness_pruned.hip", "prioritize.hip")
 CALIBRATE_LIB = os.path.join(PKG, "libmaestro_calibrate.so")
 CALIBRATE_SOURCE = "calibrate.hip"
 

@@ -3,6 +3,7 @@
 #include <math.h>
 
 #include "internal.h"
+#include "maestro_fitness.h"
 
 namespace {
 
@@ -13,6 +14,44 @@ static_assert(sizeof(maestro_plan_step) == 16, "plan step layout");
 hipStream_t as_stream(void* s) { return static_cast<hipStream_t>(s); }
 
 }  // namespace
+
+// the argument checks shared by the two fitness routers
+static maestro_status check_fitness(int64_t n, const int32_t* model_id, const int32_t* src_id,
+                                     const int32_t* class_id, const double* kv_bytes,
+                                     int32_t n_models, int32_t n_nodes, int32_t n_src,
+                                     int32_t n_classes, const double* free_bytes,
+                                     const float* queue_ms, const float* act_ms,
+                                     const uint64_t* resident_mask, const float* act_matrix,
+                                     const float* deg_ms, const maestro_deg_plan* plans,
+                                     const maestro_plan_step* plan_steps, const float* rtt_ms,
+                                     const float* class_weights,
+                                     const float* bounds, double rho, int32_t k, int32_t* node_idx,
+                                     float* fitness) {
+  if (n < 0 || n_models < 1 || n_models > 64 || n_nodes < 1 || k < 1 || k > 16)
+    return MAESTRO_ERR_INVALID_ARG;
+  if (n_src < 1 || n_src > maestro::kMaxFitnessSources || n_classes < 1 ||
+      n_classes > maestro::kMaxFitnessClasses)
+    return MAESTRO_ERR_INVALID_ARG;
+  if (!(rho >= 0.0) || rho == INFINITY) return MAESTRO_ERR_INVALID_ARG;
+  if (!free_bytes || !queue_ms || !rtt_ms || !class_weights || !bounds) return MAESTRO_ERR_INVALID_ARG;
+  if (!aligned(free_bytes, 8) || !aligned(queue_ms, 4) || !aligned(rtt_ms, 4) || !aligned(class_weights, 4) ||
+      !aligned(bounds, 4))
+    return MAESTRO_ERR_INVALID_ARG;
+  if (act_matrix ? !aligned(act_matrix, 4)
+                 : (!act_ms || !resident_mask || !aligned(act_ms, 4) || !aligned(resident_mask, 8)))
+    return MAESTRO_ERR_INVALID_ARG;
+  if (plans ? (!aligned(plans, 16) || !plan_steps || !aligned(plan_steps, 16)) : (!deg_ms || !aligned(deg_ms, 4)))
+    return MAESTRO_ERR_INVALID_ARG;
+  if (n > 0) {
+    if (!model_id || !src_id || !class_id || !kv_bytes || !node_idx || !fitness)
+      return MAESTRO_ERR_INVALID_ARG;
+    if (!aligned(model_id, 4) || !aligned(src_id, 4) || !aligned(class_id, 4) ||
+        !aligned(kv_bytes, 8) || !aligned(node_idx, 4) || !aligned(fitness, 4))
+      return MAESTRO_ERR_INVALID_ARG;
+  }
+  if (n > (int64_t)1 << 37) return MAESTRO_ERR_UNSUPPORTED;
+  return MAESTRO_OK;
+}
 
 extern "C" {
 
@@ -267,33 +306,48 @@ maestro_status maestro_route_fitness(int64_t n, const int32_t* model_id, const i
                                      const float* class_weights,
                                      const float* bounds, double rho, int32_t k, int32_t* node_idx,
                                      float* fitness, void* stream) {
-  if (n < 0 || n_models < 1 || n_models > 64 || n_nodes < 1 || k < 1 || k > 16)
-    return MAESTRO_ERR_INVALID_ARG;
-  if (n_src < 1 || n_src > maestro::kMaxFitnessSources || n_classes < 1 ||
-      n_classes > maestro::kMaxFitnessClasses)
-    return MAESTRO_ERR_INVALID_ARG;
-  if (!(rho >= 0.0) || rho == INFINITY) return MAESTRO_ERR_INVALID_ARG;
-  if (!free_bytes || !queue_ms || !rtt_ms || !class_weights || !bounds) return MAESTRO_ERR_INVALID_ARG;
-  if (!aligned(free_bytes, 8) || !aligned(queue_ms, 4) || !aligned(rtt_ms, 4) || !aligned(class_weights, 4) ||
-      !aligned(bounds, 4))
-    return MAESTRO_ERR_INVALID_ARG;
-  if (act_matrix ? !aligned(act_matrix, 4)
-                 : (!act_ms || !resident_mask || !aligned(act_ms, 4) || !aligned(resident_mask, 8)))
-    return MAESTRO_ERR_INVALID_ARG;
-  if (plans ? (!aligned(plans, 16) || !plan_steps || !aligned(plan_steps, 16)) : (!deg_ms || !aligned(deg_ms, 4)))
-    return MAESTRO_ERR_INVALID_ARG;
-  if (n > 0) {
-    if (!model_id || !src_id || !class_id || !kv_bytes || !node_idx || !fitness)
-      return MAESTRO_ERR_INVALID_ARG;
-    if (!aligned(model_id, 4) || !aligned(src_id, 4) || !aligned(class_id, 4) ||
-        !aligned(kv_bytes, 8) || !aligned(node_idx, 4) || !aligned(fitness, 4))
-      return MAESTRO_ERR_INVALID_ARG;
-  }
-  if (n > (int64_t)1 << 37) return MAESTRO_ERR_UNSUPPORTED;
+  const maestro_status st = check_fitness(n, model_id, src_id, class_id, kv_bytes, n_models, n_nodes, n_src, n_classes,
+                                          free_bytes, queue_ms, act_ms, resident_mask, act_matrix, deg_ms, plans,
+                                          plan_steps, rtt_ms, class_weights, bounds, rho, k, node_idx, fitness);
+  if (st != MAESTRO_OK) return st;
   return maestro::launch_route_fitness(n, model_id, src_id, class_id, kv_bytes, n_models, n_nodes, n_src, n_classes,
                                        free_bytes, queue_ms, act_ms, resident_mask, act_matrix, deg_ms,
                                        plans, plan_steps, rtt_ms, class_weights, bounds, rho, k, node_idx, fitness,
                                        as_stream(stream));
+}
+
+size_t maestro_route_fitness_workspace(int64_t n, int32_t n_models, int32_t n_nodes, int32_t n_src,
+                                       int32_t n_classes, int32_t k, int32_t with_plans) {
+  if (n < 0 || n > (int64_t)1 << 37 || n_models < 1 || n_models > 64 || n_nodes < 1 || k < 1 || k > 16) return 0;
+  if (n_src < 1 || n_src > maestro::kMaxFitnessSources || n_classes < 1 || n_classes > maestro::kMaxFitnessClasses)
+    return 0;
+  return maestro::fitness_workspace_bytes(n, n_models, n_nodes, n_src, n_classes, k, with_plans != 0);
+}
+
+maestro_status maestro_route_fitness_pruned(int64_t n, const int32_t* model_id, const int32_t* src_id,
+                                     const int32_t* class_id, const double* kv_bytes,
+                                     int32_t n_models, int32_t n_nodes, int32_t n_src,
+                                     int32_t n_classes, const double* free_bytes,
+                                     const float* queue_ms, const float* act_ms,
+                                     const uint64_t* resident_mask, const float* act_matrix,
+                                     const float* deg_ms, const maestro_deg_plan* plans,
+                                     const maestro_plan_step* plan_steps, const float* rtt_ms,
+                                     const float* class_weights,
+                                     const float* bounds, double rho, int32_t k, int32_t* node_idx,
+                                     float* fitness, void* workspace, size_t workspace_bytes,
+                                     void* stream) {
+  const maestro_status st = check_fitness(n, model_id, src_id, class_id, kv_bytes, n_models, n_nodes, n_src, n_classes,
+                                          free_bytes, queue_ms, act_ms, resident_mask, act_matrix, deg_ms, plans,
+                                          plan_steps, rtt_ms, class_weights, bounds, rho, k, node_idx, fitness);
+  if (st != MAESTRO_OK) return st;
+  const size_t need = maestro::fitness_workspace_bytes(n, n_models, n_nodes, n_src, n_classes, k, plans != nullptr);
+  if (need == 0) return MAESTRO_ERR_UNSUPPORTED;
+  if (!workspace || !aligned(workspace, 16)) return MAESTRO_ERR_INVALID_ARG;
+  if (workspace_bytes < need) return MAESTRO_ERR_WORKSPACE;
+  return maestro::launch_route_fitness_pruned(n, model_id, src_id, class_id, kv_bytes, n_models, n_nodes, n_src, n_classes,
+                                              free_bytes, queue_ms, act_ms, resident_mask, act_matrix, deg_ms, plans,
+                                              plan_steps, rtt_ms, class_weights, bounds, rho, k, node_idx, fitness,
+                                              workspace, as_stream(stream));
 }
 
 maestro_status maestro_degradation_plans(int32_t n_nodes, const int32_t* engine_offset,

@@ -42,6 +42,7 @@
 // underestimation, computed as a scan of affine maps.
 #include <type_traits>
 
+#include "fitness.h"
 #include "internal.h"
 #include "select.h"
 
@@ -50,15 +51,6 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kRecSteps = MAESTRO_PLAN_RECORD_STEPS;
-
-// (x - lo) / (hi - lo) clipped to [0, 1]; 0 for a degenerate window
-__device__ __forceinline__ float norm01(float x, float lo, float hi) {
-  if (!(hi > lo)) return 0.0f;
-  float t = __fdiv_rn(__fsub_rn(x, lo), __fsub_rn(hi, lo));
-  if (t < 0.0f) t = 0.0f;
-  if (t > 1.0f) t = 1.0f;
-  return t;
-}
 
 // Plan steps and records from the engine lists, one thread per node. SortByPriority orders the
 // engines by ascending level, the lower engine index first: up to eight engines with a fixed

@@ -1,0 +1,572 @@
+// Routing by fitness (Eq. 5, Alg. 3) without scoring every pair.
+//
+// A pair's fitness is S = A - pen with A = gamma prox + (1 - gamma) fit, fit = R_need / headroom.
+// Everything but the fit depends on the node and on the stage's (class, source, model) alone, and
+// the fit falls with the headroom. So the nodes are put in ascending headroom, and for every
+// (class, source, model) the largest gamma prox - pen of each block of 8 and of 64 consecutive
+// nodes is tabulated: block maximum + (1 - gamma) min(1, R_need / smallest headroom) bounds the
+// fitness of every node of the block. A stage scores the block of the best bound first and
+// then only the blocks whose bound reaches its k-th best score so far. The scores are the same
+// float32 expressions in the same order as in fitness_kernel, the lists are ordered by (score,
+// node index), and a block is skipped only when its bound, widened by more than every rounding
+// error in it, is below the k-th best, so the outputs are those of scoring every pair.
+//
+// With degradation plans (Alg. 2, Eq. 4) the nodes that fall short of the demand are the first
+// ones in headroom order. Their fit exceeds 1, so they come first: a wavefront goes through
+// them together (node data and plan records are then wavefront-uniform), block by block under
+// the same bounds, the C_deg term bounded by its smallest value.
+//
+// Three launches: ranks of the headrooms and the sorted node records; the penalty, proximity and
+// bound tables; the stages.
+// What bounds it: scoring every pair costs 14 vector instructions a pair; here a lane reads
+// M / 256 float4 of bounds, visits one to five sub-blocks of 8 nodes, and a wavefront waits for
+// the lane that visits most (6 .. 9), each visit two dependent rounds of divergent 16-byte reads.
+// Measured (one MI355X, whole call, against scoring every pair): 719,712 stages on 512 nodes, one
+// result, 53 against 139 us; 500,009 stages on 4,096 nodes with plans, four results, 105 against
+// 1,150 us.
+#include "fitness.h"
+#include "internal.h"
+#include "select.h"
+
+namespace maestro {
+namespace {
+
+constexpr int kThreads = 512;            // of the stage kernel: two workgroups per CU at 4,096 nodes
+constexpr int kMaxNodes = 4096;          // one 64-bit mask of 64-node blocks; node records in LDS
+constexpr int kRecSteps = MAESTRO_PLAN_RECORD_STEPS;
+
+struct __align__(16) SortedNode {
+  double free, recip;                    // headroom and 1 / fl32(headroom) (0 without headroom)
+};
+
+// All sizes derive from the node count padded to whole 64-node blocks.
+struct Tables {
+  int32_t padded, row;                   // nodes and floats of a bound row: blocks of 64 (padded to four), then of 8
+  size_t nodes, order, tr, prox, nd, gp, pen, bound, total;   // byte offsets
+};
+
+Tables tables_of(int32_t n_models, int32_t n_nodes, int32_t n_src, int32_t n_classes) {
+  Tables t{};
+  t.padded = (n_nodes + 63) & ~63;
+  t.row = (((t.padded >> 6) + 3) & ~3) + (t.padded >> 3);
+  t.nodes = 0;
+  t.order = t.nodes + (size_t)t.padded * sizeof(SortedNode);
+  t.tr = t.order + (size_t)t.padded * sizeof(uint16_t);
+  t.prox = t.tr + (size_t)n_models * t.padded * sizeof(float);
+  t.nd = t.prox + (size_t)n_src * t.padded * sizeof(float);
+  t.gp = t.nd + (size_t)t.padded * sizeof(float);
+  t.pen = t.gp + (size_t)n_classes * n_src * t.padded * sizeof(float);
+  t.bound = t.pen + (size_t)n_classes * n_models * t.padded * sizeof(float);
+  t.total = t.bound + (size_t)n_classes * n_src * n_models * t.row * sizeof(float);
+  return t;
+}
+
+// order-preserving map of float64 bits to unsigned (a total order, whatever the bits)
+__device__ __forceinline__ uint64_t double_key(double d) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, d);
+  return (u >> 63) ? ~u : (u | 0x8000000000000000ull);
+}
+
+// Position of every node in ascending (headroom, index) order by counting: wavefront w of a
+// workgroup takes one node, its lanes compare 64 others at a time (LDS), and the ballots add up
+// on the scalar unit. 16 nodes per workgroup, so 4,096 nodes spread over 256 workgroups; the M^2
+// compares take 8 us there, a third of what a radix sort in one workgroup does. The wavefront then
+// writes the node's terms at its position: lane m norm(T_ready) of model m, lane s 1 - norm(RTT)
+// from source s, and norm(C_deg).
+constexpr int kRankThreads = 1024;
+__global__ __launch_bounds__(kRankThreads) void fitness_rank_kernel(int32_t n_nodes, int32_t padded,
+                                                                    int32_t n_models, int32_t n_src,
+                                                                    const double* __restrict__ free_bytes,
+                                                                    const float* __restrict__ queue_ms,
+                                                                    const float* __restrict__ act_ms,
+                                                                    const uint64_t* __restrict__ resident_mask,
+                                                                    const float* __restrict__ act_matrix,
+                                                                    const float* __restrict__ deg_ms,
+                                                                    const float* __restrict__ rtt_ms,
+                                                                    const float* __restrict__ bounds,
+                                                                    SortedNode* __restrict__ nodes,
+                                                                    uint16_t* __restrict__ order,
+                                                                    float* __restrict__ tr, float* __restrict__ prox,
+                                                                    float* __restrict__ nd) {
+  __shared__ uint64_t s_key[kMaxNodes];
+  const int tid = threadIdx.x, lane = tid & 63;
+  for (int j = tid; j < padded; j += kRankThreads) s_key[j] = j < n_nodes ? double_key(free_bytes[j]) : ~0ull;
+  __syncthreads();
+  const int i = blockIdx.x * (kRankThreads / 64) + (tid >> 6);
+  if (i >= padded) return;
+  if (i >= n_nodes) {                    // padding: admits nothing
+    if (lane == 0) {
+      nodes[i] = SortedNode{-INFINITY, 0.0};
+      order[i] = 0;
+      nd[i] = 0.0f;
+    }
+    if (lane < n_models) tr[(size_t)lane * padded + i] = 0.0f;
+    if (lane < n_src) prox[(size_t)lane * padded + i] = 0.0f;
+    return;
+  }
+  const uint64_t key = s_key[i];
+  // 64-node groups before the node's own count equal keys too, those after it do not (padding
+  // holds the largest key and is never below another)
+  int rank = 0;
+  const int own = i & ~63;
+#pragma unroll 4
+  for (int j0 = 0; j0 < own; j0 += 64) rank += __popcll(__ballot(s_key[j0 + lane] <= key));
+  {
+    const uint64_t o = s_key[own + lane];
+    rank += __popcll(__ballot(o < key || (o == key && own + lane < i)));
+  }
+#pragma unroll 4
+  for (int j0 = own + 64; j0 < padded; j0 += 64) rank += __popcll(__ballot(s_key[j0 + lane] < key));
+  if (lane == 0) {
+    const double fr = free_bytes[i];
+    const float frf = __double2float_rn(fr);
+    nodes[rank] = SortedNode{fr, frf > 0.0f ? __ddiv_rn(1.0, (double)frf) : 0.0};
+    order[rank] = (uint16_t)i;
+    nd[rank] = deg_ms ? norm01(deg_ms[i], bounds[4], bounds[5]) : 0.0f;
+  }
+  if (lane < n_models) {
+    const float q = queue_ms[i];
+    float ready;
+    if (act_matrix) ready = __fadd_rn(q, act_matrix[(size_t)i * n_models + lane]);
+    else ready = (resident_mask[i] >> lane) & 1u ? __fadd_rn(q, 0.0f) : __fadd_rn(q, act_ms[i]);
+    tr[(size_t)lane * padded + rank] = norm01(ready, bounds[2], bounds[3]);
+  }
+  if (lane < n_src)
+    prox[(size_t)lane * padded + rank] = __fsub_rn(1.0f, norm01(rtt_ms[(size_t)lane * n_nodes + i], bounds[0], bounds[1]));
+}
+
+// One workgroup per (class, model) and 512 sorted nodes, eight consecutive nodes per thread: their
+// penalties (with plans lambda norm(T_ready) alone, the C_deg term being the pair's), the
+// proximity terms gamma (1 - norm(RTT)) of every source (written by model 0's workgroups), and
+// the bound rows of the class's (source, model) pairs. With plans the C_deg term is at least
+// min(0, mu), since norm() lies in [0, 1].
+constexpr int kTableThreads = 64;
+__device__ __forceinline__ void load8(const float* __restrict__ p, float (&v)[8]) {
+  *reinterpret_cast<float4*>(v) = *reinterpret_cast<const float4*>(p);
+  *reinterpret_cast<float4*>(v + 4) = *reinterpret_cast<const float4*>(p + 4);
+}
+__device__ __forceinline__ void store8(float* __restrict__ p, const float (&v)[8]) {
+  *reinterpret_cast<float4*>(p) = *reinterpret_cast<const float4*>(v);
+  *reinterpret_cast<float4*>(p + 4) = *reinterpret_cast<const float4*>(v + 4);
+}
+
+template <bool kPlans>
+__global__ __launch_bounds__(kTableThreads) void fitness_tables_kernel(
+    int32_t n_models, int32_t n_nodes, int32_t n_src, int32_t padded, int32_t row, const float* __restrict__ tr,
+    const float* __restrict__ prox, const float* __restrict__ nd, const float* __restrict__ class_weights,
+    float* __restrict__ gp, float* __restrict__ pen, float* __restrict__ bound) {
+  const int m = blockIdx.x, c = blockIdx.y;
+  const int p0 = (blockIdx.z * kTableThreads + threadIdx.x) * 8;
+  if (p0 >= padded) return;              // whole octets of lanes: padded is a multiple of 64
+  const float gamma = class_weights[3 * c], lambda = class_weights[3 * c + 1], mu = class_weights[3 * c + 2];
+  const float deg_floor = fminf(mu, 0.0f);
+  float pn[8], low[8], t[8], d[8];
+  load8(tr + (size_t)m * padded + p0, t);
+  load8(nd + p0, d);
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    const float lt = __fmul_rn(lambda, t[u]);
+    pn[u] = kPlans ? lt : __fadd_rn(lt, __fmul_rn(mu, d[u]));
+    low[u] = p0 + u >= n_nodes ? INFINITY : kPlans ? lt + deg_floor : pn[u];   // padding: bound -inf
+  }
+  store8(pen + (size_t)(c * n_models + m) * padded + p0, pn);
+  const int blocks4 = ((padded >> 6) + 3) & ~3;
+#pragma unroll 4
+  for (int s = 0; s < n_src; ++s) {
+    float g[8], top = -INFINITY;
+    load8(prox + (size_t)s * padded + p0, g);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      g[u] = __fmul_rn(gamma, g[u]);
+      top = fmaxf(top, g[u] - low[u]);
+    }
+    if (m == 0) store8(gp + (size_t)(c * n_src + s) * padded + p0, g);
+    float* r = bound + (size_t)((c * n_src + s) * n_models + m) * row;
+    r[blocks4 + (p0 >> 3)] = top;
+    top = fmaxf(top, __shfl_xor(top, 1));
+    top = fmaxf(top, __shfl_xor(top, 2));
+    top = fmaxf(top, __shfl_xor(top, 4));
+    if ((threadIdx.x & 7) == 0) r[p0 >> 6] = top;
+  }
+}
+
+// Relative widening of the bounds: a score takes four rounded float32 operations on terms no
+// larger than |gamma|, (1 - gamma) fit, |lambda| and |mu|, and a bound (from above or below) four,
+// so 2^-19 of the sum of those terms is more than all of their rounding errors together (each less
+// than 2^-21 of it).
+constexpr float kSlack = 1.9073486328125e-06f;
+
+// Stages in turn, one per lane, 512 lanes a workgroup; the sorted node records, their original
+// indices and the largest reciprocal of every block are staged in LDS once per workgroup.
+template <int KT, bool kPlans>
+__global__ __launch_bounds__(kThreads) void fitness_walk_kernel(
+    int64_t n, const int32_t* __restrict__ model_id, const int32_t* __restrict__ src_id,
+    const int32_t* __restrict__ class_id, const double* __restrict__ kv_bytes, int32_t n_models, int32_t n_nodes,
+    int32_t n_src, int32_t n_classes, int32_t padded, int32_t row, const SortedNode* __restrict__ nodes,
+    const uint16_t* __restrict__ order, const float* __restrict__ gp, const float* __restrict__ pen,
+    const float* __restrict__ bound, const maestro_deg_plan* __restrict__ plans,
+    const maestro_plan_step* __restrict__ plan_steps, const float* __restrict__ class_weights,
+    const float* __restrict__ bounds, double rho, int32_t k, int32_t* __restrict__ node_idx,
+    float* __restrict__ fitness) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char s_raw[];
+  SortedNode* s_node = reinterpret_cast<SortedNode*>(s_raw);
+  float* s_r8 = reinterpret_cast<float*>(s_node + padded);        // [padded / 8]
+  float* s_r64 = s_r8 + (padded >> 3);                            // [padded / 64, to a multiple of four]
+  const int blocks = padded >> 6, blocks4 = (blocks + 3) & ~3;
+  uint16_t* s_order = reinterpret_cast<uint16_t*>(s_r64 + blocks4);
+  const int tid = threadIdx.x;
+  for (int i = tid; i < padded; i += kThreads) {
+    s_node[i] = nodes[i];
+    s_order[i] = order[i];
+  }
+  __syncthreads();
+  // the largest reciprocal of a block, rounded up; padding counts as 0
+  for (int b = tid; b < (padded >> 3); b += kThreads) {
+    double r = 0.0;
+    for (int u = 0; u < 8; ++u) r = fmax(r, s_node[8 * b + u].recip);
+    s_r8[b] = __double2float_ru(r);
+  }
+  __syncthreads();
+  for (int b = tid; b < blocks4; b += kThreads) {
+    float r = 0.0f;
+    if (b < blocks)
+      for (int u = 0; u < 8; ++u) r = fmaxf(r, s_r8[8 * b + u]);
+    s_r64[b] = r;
+  }
+  __syncthreads();
+  const float lo_d = bounds[4], hi_d = bounds[5];
+  const float nd_fits = norm01(0.0f, lo_d, hi_d);   // normalised C_deg of a stage that fits
+
+  const int64_t step = (int64_t)gridDim.x * kThreads;
+  const int64_t rounds = (n + step - 1) / step;      // workgroup-uniform: whole wavefronts vote below
+  for (int64_t it = 0; it < rounds; ++it) {
+    const int64_t stage = it * step + (int64_t)blockIdx.x * kThreads + tid;
+    TopK<KT> best;                                   // keys are -fitness: the smallest key is the best node
+    best.init();
+    bool ok = false;
+    double need = NAN, needd = 0.0;
+    float gamma = 0.0f, omg = 0.0f, lambda = 0.0f, mu = 0.0f;
+    int cs = 0, cm = 0, m = 0;
+    if (stage < n) {
+      const int32_t mi = model_id[stage], si = src_id[stage], ci = class_id[stage];
+      ok = (uint32_t)mi < (uint32_t)n_models && (uint32_t)si < (uint32_t)n_src && (uint32_t)ci < (uint32_t)n_classes;
+      if (ok) {
+        need = (rho == 0.0) ? kv_bytes[stage] : __dmul_rn(kv_bytes[stage], 1.0 + rho);
+        needd = (double)__double2float_rn(need);
+        gamma = class_weights[3 * ci];
+        lambda = class_weights[3 * ci + 1];
+        mu = class_weights[3 * ci + 2];
+        omg = __fsub_rn(1.0f, gamma);
+        cs = ci * n_src + si;
+        cm = ci * n_models + mi;
+        m = mi;
+      }
+    }
+    const float* gp_row = gp + (size_t)cs * padded;
+    const float* pen_row = pen + (size_t)cm * padded;
+    const float* b64 = bound + ((size_t)cs * n_models + m) * row;
+    const float* b8 = b64 + blocks4;
+    // bound of a block: fit_w * min(1, needf * largest reciprocal) + its table entry; a
+    // negative demand with a negative fit weight has no such bound (every block is visited)
+    const float needf = fmaxf((float)needd, 0.0f);
+    const float fit_w = fmaxf(omg, 0.0f) * (1.0f + kSlack);
+    const float widen = (needd < 0.0 && omg < 0.0f)
+                            ? INFINITY
+                            : kSlack * (fabsf(gamma) + fabsf(lambda) + fabsf(mu) + fabsf(omg));
+    const float md = __fmul_rn(mu, nd_fits);
+    // first sorted position that admits the stage
+    int start = 0;
+    if (ok) {
+      int lo = 0, hi = n_nodes;
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (s_node[mid].free < need) lo = mid + 1;
+        else hi = mid;
+      }
+      start = lo;
+    }
+    // a lower bound of the k-th best fitness (the k-th best so far, or a bound from the tables), less the
+    // widening of the bounds
+    float known = -INFINITY;
+    auto floor_key = [&]() { return fmaxf(-best.s[KT - 1], known) - widen; };
+
+    // ---- the nodes that fall short, by their plans
+    if constexpr (kPlans) {
+      const int mine = ok ? start : 0;
+      for (int b = 0; __any(64 * b < mine); ++b) {
+        const float ub = fmaf(fit_w, needf * s_r64[b], b64[b]);
+        const bool want64 = 64 * b < mine && !(ub < floor_key());
+        if (!__any(want64)) continue;
+        for (int s = 8 * b; s < 8 * b + 8; ++s) {
+          if (!__any(8 * s < mine)) break;
+          const float u8 = fmaf(fit_w, needf * s_r8[s], b8[s]);
+          const bool want = want64 && 8 * s < mine && !(u8 < floor_key());
+          if (!__any(want)) continue;
+          float g[8], l[8];
+          load8(gp_row + 8 * s, g);
+          load8(pen_row + 8 * s, l);
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            const int i = 8 * s + u;
+            const SortedNode nd = s_node[i];
+            const float fit = __double2float_rn(__dmul_rn(needd, nd.recip));
+            const float a = __fadd_rn(g[u], __fmul_rn(omg, fit));
+            // with mu >= 0 the fitness is at most the score with C_deg normalised to 0
+            const bool go = want && i < mine && !(mu >= 0.0f && -__fsub_rn(a, l[u]) > best.s[KT - 1]);
+            if (!__any(go)) continue;
+            const int j = __builtin_amdgcn_readfirstlane((int)s_order[i]);
+            const maestro_deg_plan* pl = plans + j;
+            const int ne = pl->n_engines;
+            const double R = __dsub_rn(need, nd.free);
+            int jp = 0;
+#pragma unroll
+            for (int e = 0; e < kRecSteps; ++e) jp += pl->freed[e] < R ? 1 : 0;
+            float cost = pl->cost[0];
+#pragma unroll
+            for (int e = 1; e < kRecSteps; ++e) cost = jp == e ? pl->cost[e] : cost;
+            bool found = jp < ne && jp < kRecSteps;
+            if (go && !found && ne > kRecSteps) {    // the steps past the record: the first freed >= R
+              const maestro_plan_step* st = plan_steps + pl->first_step;
+              int lo = kRecSteps, hi = ne;
+              while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (st[mid].freed < R) lo = mid + 1;
+                else hi = mid;
+              }
+              found = lo < ne;
+              if (found) cost = st[lo].cost;
+            }
+            if (go && found)
+              best.push_lex(-__fsub_rn(a, __fadd_rn(l[u], __fmul_rn(mu, norm01(cost, lo_d, hi_d)))), j);
+          }
+        }
+      }
+    }
+
+    // ---- the nodes that admit the stage
+    auto score8 = [&](int sub) {
+      float g[8], l[8];
+      load8(gp_row + 8 * sub, g);
+      load8(pen_row + 8 * sub, l);
+      const uint4 o = *reinterpret_cast<const uint4*>(s_order + 8 * sub);
+      const uint32_t ow[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const SortedNode nd = s_node[8 * sub + u];
+        const float fit = __double2float_rn(__dmul_rn(needd, nd.recip));
+        const float a = __fadd_rn(g[u], __fmul_rn(omg, fit));
+        const float p = kPlans ? __fadd_rn(l[u], md) : l[u];
+        if (need <= nd.free) best.push_lex(-__fsub_rn(a, p), (int32_t)((ow[u >> 1] >> (16 * (u & 1))) & 0xFFFFu));
+      }
+    };
+    // bounds of the eight sub-blocks of a block; those before `start` admit nothing
+    auto sub_bounds = [&](int blk, float (&ub)[8]) {
+      float t[8], r[8];
+      load8(b8 + 8 * blk, t);
+      load8(s_r8 + 8 * blk, r);
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        ub[u] = 64 * blk + 8 * u + 7 < start ? -INFINITY : fmaf(fit_w, fminf(needf * r[u], 1.0f), t[u]);
+    };
+    // One pass over the bounds of the 64-node blocks from the stage's first one on: the two blocks
+    // of the best bounds, the third best bound, and a lower bound of the k-th best fitness -- past
+    // the first block every node admits the stage, so the node that holds a block's table entry
+    // scores at least that entry plus the smallest fit term less the most that its C_deg term adds.
+    const bool live = ok && start < n_nodes;
+    const int blk0 = live ? start >> 6 : blocks;
+    float top = -INFINITY, second = -INFINITY, third = -INFINITY;
+    int arg = 0, arg2 = 0;
+    {
+      float low[KT];
+#pragma unroll
+      for (int i = 0; i < KT; ++i) low[i] = -INFINITY;
+#pragma unroll 4
+      for (int q = 0; q < blocks4; q += 4) {
+        const float4 t = *reinterpret_cast<const float4*>(b64 + q);
+        const float4 r = *reinterpret_cast<const float4*>(s_r64 + q);
+        const float tv[4] = {t.x, t.y, t.z, t.w}, rv[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int blk = q + u;
+          const float ub =
+              blk < blk0 || blk >= blocks ? -INFINITY : fmaf(fit_w, fminf(needf * rv[u], 1.0f), tv[u]);
+          third = fmaxf(third, fminf(ub, second));
+          arg2 = ub > top ? arg : ub > second ? blk : arg2;
+          second = fmaxf(second, fminf(ub, top));
+          arg = ub > top ? blk : arg;
+          top = fmaxf(top, ub);
+          float lb = blk > blk0 && blk < blocks ? tv[u] : -INFINITY;
+#pragma unroll
+          for (int i = 0; i < KT; ++i) {
+            const float hi = fmaxf(low[i], lb);
+            lb = fminf(low[i], lb);
+            low[i] = hi;
+          }
+        }
+      }
+      if (needd >= 0.0) known = low[KT - 1] - (fmaxf(-omg, 0.0f) + (kPlans ? md - fminf(mu, 0.0f) : 0.0f));
+    }
+    // The sub-blocks of those two blocks in descending order of their bounds while those reach the
+    // k-th best score, then those of every other block whose bound still does.
+    float ub[8], ub2[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) ub[u] = ub2[u] = -INFINITY;
+    if (live && !(top < floor_key())) sub_bounds(arg, ub);
+    if (live && second > -INFINITY && !(second < floor_key())) sub_bounds(arg2, ub2);
+    for (;;) {
+      int bs = 0;
+      float bt = ub[0];
+#pragma unroll
+      for (int u = 1; u < 16; ++u) {
+        const float v = u < 8 ? ub[u & 7] : ub2[u & 7];
+        bs = v > bt ? u : bs;
+        bt = fmaxf(bt, v);
+      }
+      if (!(bt > -INFINITY) || bt < floor_key()) break;
+      score8(8 * (bs < 8 ? arg : arg2) + (bs & 7));
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        ub[u] = u == bs ? -INFINITY : ub[u];
+        ub2[u] = u + 8 == bs ? -INFINITY : ub2[u];
+      }
+    }
+    const bool more = third > -INFINITY && !(third < floor_key());
+    if (__any(more)) {
+      uint64_t rest = 0;
+      auto bound64 = [&](int blk) { return fmaf(fit_w, fminf(needf * s_r64[blk], 1.0f), b64[blk]); };
+#pragma unroll 4
+      for (int blk = 0; blk < blocks; ++blk) {
+        const float v = bound64(blk);
+        if (more && blk >= blk0 && blk != arg && blk != arg2 && !(v < floor_key())) rest |= 1ull << blk;
+      }
+      // taking the next block and scoring a sub-block are two steps of one loop, so that lanes at
+      // different points of their lists share its iterations
+      int blk = 0;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) ub[u] = -INFINITY;
+      for (;;) {
+        int bs = 0;
+        float bt = ub[0];
+#pragma unroll
+        for (int u = 1; u < 8; ++u) {
+          bs = ub[u] > bt ? u : bs;
+          bt = fmaxf(bt, ub[u]);
+        }
+        if (bt > -INFINITY && !(bt < floor_key())) {
+          score8(8 * blk + bs);
+#pragma unroll
+          for (int u = 0; u < 8; ++u) ub[u] = u == bs ? -INFINITY : ub[u];
+        } else {
+          do {   // the next block whose bound reaches the score as it now stands
+            blk = __ffsll((unsigned long long)rest) - 1;
+            rest &= rest - 1;
+          } while (blk >= 0 && bound64(blk) < floor_key());
+          if (blk < 0) break;
+          sub_bounds(blk, ub);
+        }
+      }
+    }
+
+    if (stage < n) {
+#pragma unroll
+      for (int i = 0; i < KT; ++i) {
+        if (i < k) {
+          const bool some = best.n[i] != kNoNode;
+          node_idx[stage * k + i] = some ? best.n[i] : -1;
+          fitness[stage * k + i] = some ? -best.s[i] : -INFINITY;
+        }
+      }
+    }
+  }
+}
+
+size_t walk_lds_bytes(int32_t padded) {
+  return (size_t)padded * (sizeof(SortedNode) + sizeof(uint16_t)) + (size_t)(padded / 8) * sizeof(float) +
+         (size_t)(((padded >> 6) + 3) & ~3) * sizeof(float);
+}
+
+}  // namespace
+
+// Where the tables pay. Scoring every pair takes a latency that grows with the nodes a lane walks
+// (86 us at 4,096 nodes, 24 at 1,024, for a batch of any size up to 4,096 stages) plus the pairs at
+// about 2 per ps; the tables and the walk take 28 us up to 1,024 nodes and 35 at 4,096 for one
+// result per stage or with plans, 55 .. 90 us for lists of up to four (more blocks reach the
+// fourth best score, each a chain of two dependent reads). Measured on both sides of the lines
+// (us, tables / every pair): k = 1, 512 nodes: 28.7 / 17.3 at 2^23 pairs, 28.0 / 32.6 at 2^25,
+// 31.3 / 67.0 at 2^27; 4,096 nodes: 34 / 86 at 2^22. k = 4: 512 nodes 67.7 / 47.1 at 2^25, 80.2 /
+// 86.7 at 2^27; 4,096 nodes 81 / 117 at 2^22. Plans, k = 1: 256 nodes 30.8 / 27.2 at 2^24, 29.4 /
+// 55.7 at 2^26; 1,024 nodes 29.8 / 35.4 at 2^20. Many (class, source, model) combinations make the
+// tables themselves the cost: 640 of them take 5 us at 4,096 nodes.
+size_t fitness_workspace_bytes(int64_t n, int32_t n_models, int32_t n_nodes, int32_t n_src, int32_t n_classes,
+                               int32_t k, bool plans) {
+  if (k > 4 || n_nodes > kMaxNodes || n_nodes < 64) return 0;
+  const int32_t always = plans ? 1024 : k == 1 ? 2048 : 3072;
+  const int pairs_log2 = plans ? 24 : k == 1 ? 25 : 27;
+  if (n_nodes < always && n * n_nodes < (int64_t)1 << pairs_log2) return 0;
+  if ((int64_t)n_classes * n_src * n_models > 1024 + n / 8) return 0;
+  return tables_of(n_models, n_nodes, n_src, n_classes).total;
+}
+
+maestro_status launch_route_fitness_pruned(int64_t n, const int32_t* model_id, const int32_t* src_id,
+                                           const int32_t* class_id, const double* kv_bytes, int32_t n_models,
+                                           int32_t n_nodes, int32_t n_src, int32_t n_classes, const double* free_bytes,
+                                           const float* queue_ms, const float* act_ms, const uint64_t* resident_mask,
+                                           const float* act_matrix, const float* deg_ms, const maestro_deg_plan* plans,
+                                           const maestro_plan_step* plan_steps, const float* rtt_ms,
+                                           const float* class_weights, const float* bounds, double rho, int32_t k,
+                                           int32_t* node_idx, float* fitness, void* workspace, hipStream_t stream) {
+  if (n == 0) return MAESTRO_OK;
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+    return MAESTRO_ERR_LAUNCH;
+  const Tables t = tables_of(n_models, n_nodes, n_src, n_classes);
+  unsigned char* ws = static_cast<unsigned char*>(workspace);
+  SortedNode* nodes = reinterpret_cast<SortedNode*>(ws + t.nodes);
+  uint16_t* order = reinterpret_cast<uint16_t*>(ws + t.order);
+  float* gp = reinterpret_cast<float*>(ws + t.gp);
+  float* pen = reinterpret_cast<float*>(ws + t.pen);
+  float* bound = reinterpret_cast<float*>(ws + t.bound);
+  float* tr = reinterpret_cast<float*>(ws + t.tr);
+  float* prox = reinterpret_cast<float*>(ws + t.prox);
+  float* nd = reinterpret_cast<float*>(ws + t.nd);
+  fitness_rank_kernel<<<dim3((unsigned)((t.padded + 15) / 16)), dim3(kRankThreads), 0, stream>>>(
+      n_nodes, t.padded, n_models, n_src, free_bytes, queue_ms, act_ms, resident_mask, act_matrix,
+      plans ? nullptr : deg_ms, rtt_ms, bounds, nodes, order, tr, prox, nd);
+  const dim3 tgrid((unsigned)n_models, (unsigned)n_classes, (unsigned)((t.padded / 8 + kTableThreads - 1) / kTableThreads));
+  if (plans)
+    fitness_tables_kernel<true><<<tgrid, dim3(kTableThreads), 0, stream>>>(n_models, n_nodes, n_src, t.padded, t.row, tr,
+                                                                           prox, nd, class_weights, gp, pen, bound);
+  else
+    fitness_tables_kernel<false><<<tgrid, dim3(kTableThreads), 0, stream>>>(n_models, n_nodes, n_src, t.padded, t.row, tr,
+                                                                            prox, nd, class_weights, gp, pen, bound);
+  const size_t lds = walk_lds_bytes(t.padded);
+  // One round of 512 stages per workgroup while the LDS staging is small, up to four (equal ones)
+  // at 4,096 nodes, where only two workgroups fit a CU and each stages 74 KB.
+  const int64_t want = (n + kThreads - 1) / kThreads, slots = 2 * (int64_t)cus;
+  const int64_t most_rounds = t.padded > 1024 ? t.padded / 1024 : 1;
+  const int64_t fair = (want + slots - 1) / slots, rounds = fair < most_rounds ? fair : most_rounds;
+  const dim3 grid((unsigned)((want + rounds - 1) / rounds));
+#define MAESTRO_FITW(KT, PL)                                                                                          \
+  do {                                                                                                                \
+    if (lds > 65536 && hipFuncSetAttribute(reinterpret_cast<const void*>(&fitness_walk_kernel<KT, PL>),               \
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)       \
+      return MAESTRO_ERR_LAUNCH;                                                                                      \
+    fitness_walk_kernel<KT, PL><<<grid, dim3(kThreads), lds, stream>>>(                                               \
+        n, model_id, src_id, class_id, kv_bytes, n_models, n_nodes, n_src, n_classes, t.padded, t.row, nodes, order,  \
+        gp, pen, bound, plans, plan_steps, class_weights, bounds, rho, k, node_idx, fitness);                         \
+  } while (0)
+#define MAESTRO_FITW_KT(KT)               \
+  do {                                    \
+    if (plans) MAESTRO_FITW(KT, true);    \
+    else MAESTRO_FITW(KT, false);         \
+  } while (0)
+  if (k == 1) MAESTRO_FITW_KT(1);
+  else if (k == 2) MAESTRO_FITW_KT(2);
+  else MAESTRO_FITW_KT(4);
+#undef MAESTRO_FITW_KT
+#undef MAESTRO_FITW
+  return launch_status();
+}
+
+}  // namespace maestro

@@ -67,6 +67,17 @@ maestro_status launch_route_fitness(int64_t n, const int32_t* model_id, const in
                                     const maestro_deg_plan* plans, const maestro_plan_step* plan_steps,
                                     const float* rtt_ms, const float* class_weights, const float* bounds, double rho,
                                     int32_t k, int32_t* node_idx, float* fitness, hipStream_t stream);
+// the same from tables in a workspace (fitness_workspace_bytes; 0 where every pair is scored instead)
+size_t fitness_workspace_bytes(int64_t n, int32_t n_models, int32_t n_nodes, int32_t n_src, int32_t n_classes,
+                               int32_t k, bool plans);
+maestro_status launch_route_fitness_pruned(int64_t n, const int32_t* model_id, const int32_t* src_id,
+                                           const int32_t* class_id, const double* kv_bytes, int32_t n_models,
+                                           int32_t n_nodes, int32_t n_src, int32_t n_classes, const double* free_bytes,
+                                           const float* queue_ms, const float* act_ms, const uint64_t* resident_mask,
+                                           const float* act_matrix, const float* deg_ms, const maestro_deg_plan* plans,
+                                           const maestro_plan_step* plan_steps, const float* rtt_ms,
+                                           const float* class_weights, const float* bounds, double rho, int32_t k,
+                                           int32_t* node_idx, float* fitness, void* workspace, hipStream_t stream);
 maestro_status launch_degradation_plans(int32_t n_nodes, const int32_t* engine_offset, const int32_t* engine_level,
                                        const double* engine_freed_bytes, const float* engine_cost_ms, float c_int_ms,
                                        maestro_deg_plan* plans, maestro_plan_step* steps, hipStream_t stream);
