@@ -320,9 +320,9 @@ typedef struct maestro_deg_plan {
  *   steps (out)         [E] maestro_plan_step, 16-byte aligned, E = engine_offset[n_nodes]:
  *                       node j's steps at [engine_offset[j], engine_offset[j+1]), in order
  * A shortfall R > 0 is met by the first step with freed >= R, at that step's cost; no such step
- * means the plan fails (the node cannot admit the stage). One thread per node: a node of up to
- * 8 engines is sorted in registers, a larger one by counting ranks (time quadratic in its
- * engine count). Device pointers, no workspace; n_nodes == 0 launches nothing. The engine
+ * means the plan fails (the node cannot admit the stage). One wavefront per node: up to 64
+ * engines one per lane, more by counting ranks in strides of 64 (time quadratic in the engine
+ * count). Device pointers, no workspace; n_nodes == 0 launches nothing. The engine
  * arrays may be NULL when E == 0. Errors: INVALID_ARG for n_nodes < 0, a NaN c_int_ms, a NULL
  * or misaligned offset, plan or step array, or a misaligned engine array. */
 MAESTRO_API maestro_status maestro_degradation_plans(int32_t n_nodes, const int32_t* engine_offset,

@@ -52,90 +52,109 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kRecSteps = MAESTRO_PLAN_RECORD_STEPS;
 
-// Plan steps and records from the engine lists, one thread per node. SortByPriority orders the
-// engines by ascending level, the lower engine index first: up to eight engines with a fixed
-// compare-exchange network over keys level:index in registers, more by counting each engine's
-// rank among the node's keys (the keys are distinct). The running sums then follow that order:
-// freed bytes in float64, costs in float32, and c_int added to every prefix that holds an engine
-// of level 4 or 5. The freed column keeps the largest running sum so far, so it never decreases
-// (it is the running sum itself when no action frees a negative amount): the first prefix whose
-// running sum reaches a shortfall is then also the first whose entry does, which a stage finds
-// by counting (record) or by binary search (steps). Record entries past the node's engines hold
-// +inf.
+// Plan steps and records from the engine lists, one wavefront per node. SortByPriority orders the
+// engines by ascending level, the lower engine index first: lane i holds engine i and counts the
+// engines of a smaller key level:index (the keys are distinct). The running sums then follow that
+// order: freed bytes in float64, costs in float32, and c_int added to every prefix that holds an
+// engine of level 4 or 5. The freed column keeps the largest running sum so far, so it never
+// decreases (it is the running sum itself when no action frees a negative amount): the first prefix
+// whose running sum reaches a shortfall is then also the first whose entry does, which a stage
+// finds by counting (record) or by binary search (steps). Record entries past the node's engines
+// hold +inf.
+// Bound by the latency of one chain of reads and sums per node. One thread per node (a sorting
+// network of eight keys, larger nodes by counting in global memory) left 16 wavefronts to 4,096
+// nodes, each as slow as its most crowded node: 54 us where 10% of the nodes carry 9-20 engines.
+// Here lane p adds up the first p + 1 engines itself, in order, from LDS: the same sums, every
+// prefix at once, and steps and records leave in whole rows; 4,096 wavefronts, 5.9 us.
 __device__ __forceinline__ int64_t engine_key(int32_t level, int32_t i) {
   return (int64_t)level * ((int64_t)1 << 32) + (int64_t)(uint32_t)i;
 }
 
+constexpr int kPlanWaves = kThreads / 64;
 __global__ __launch_bounds__(kThreads) void plan_kernel(int32_t n_nodes, const int32_t* __restrict__ engine_offset,
                                                         const int32_t* __restrict__ engine_level,
                                                         const double* __restrict__ engine_freed,
                                                         const float* __restrict__ engine_cost, float c_int,
                                                         maestro_deg_plan* __restrict__ plans,
-                                                        maestro_plan_step* __restrict__ steps) {
-  const int32_t j = blockIdx.x * kThreads + threadIdx.x;
-  if (j >= n_nodes) return;
+                                                        maestro_plan_step* steps) {
+  __shared__ double s_freed[kPlanWaves][64];
+  __shared__ float s_cost[kPlanWaves][64];
+  __shared__ int32_t s_engine[kPlanWaves][64];   // engine within the node, its level in the top bits
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int32_t j = blockIdx.x * kPlanWaves + wave;
+  if (j >= n_nodes) return;              // whole wavefronts: nothing below crosses wavefronts
   const int32_t e0 = engine_offset[j];
   int32_t ne = engine_offset[j + 1] - e0;
   ne = ne < 0 ? 0 : ne;
-  maestro_deg_plan out;
-  double freed = 0.0, top = 0.0;
-  float cost = 0.0f;
-  bool interrupt = false;
-  // one step of the running sums: engine e (global index) of level lv at position p
-  auto step = [&](int32_t p, int32_t e, int32_t lv) {
-    interrupt = interrupt || lv >= 4;   // Preempt / Abort interrupt active work
-    freed = __dadd_rn(freed, engine_freed[e]);
-    cost = __fadd_rn(cost, engine_cost[e]);
-    top = p == 0 ? freed : fmax(top, freed);
-    const float c = __fadd_rn(cost, interrupt ? c_int : 0.0f);
-    steps[e0 + p] = maestro_plan_step{top, c, e};
-    if (p < kRecSteps) {
-      out.freed[p] = top;
-      out.cost[p] = c;
+  double top = INFINITY;                 // this lane's prefix: engines 0 .. lane in priority order
+  float total = 0.0f;
+  if (ne <= 64) {
+    const bool mine = lane < ne;
+    const int32_t level = mine ? engine_level[e0 + lane] : 0;
+    const double fr = mine ? engine_freed[e0 + lane] : 0.0;
+    const float co = mine ? engine_cost[e0 + lane] : 0.0f;
+    int rank = 0;
+    for (int q = 0; q < ne; ++q) {
+      const int32_t lq = __builtin_amdgcn_readlane(level, q);
+      rank += lq < level || (lq == level && q < lane) ? 1 : 0;
     }
-  };
-  if (ne <= kRecSteps) {
-    int64_t key[kRecSteps];
-#pragma unroll
-    for (int i = 0; i < kRecSteps; ++i) key[i] = i < ne ? engine_key(engine_level[e0 + i], i) : INT64_MAX;
-#pragma unroll
-    for (int pass = 0; pass < kRecSteps; ++pass) {
-#pragma unroll
-      for (int q = pass & 1; q + 1 < kRecSteps; q += 2) {   // odd-even transposition sort
-        const int64_t a = key[q], b = key[q + 1];
-        key[q] = a < b ? a : b;
-        key[q + 1] = a < b ? b : a;
+    if (mine) {
+      s_freed[wave][rank] = fr;
+      s_cost[wave][rank] = co;
+      s_engine[wave][rank] = lane | (level >= 4 ? 0x40 : 0);
+    }
+    __builtin_amdgcn_wave_barrier();     // one wavefront's LDS accesses stay in program order
+    double freed = 0.0;
+    float cost = 0.0f;
+    bool interrupt = false;
+    for (int q = 0; q < ne; ++q) {
+      const double f = s_freed[wave][q];
+      const float c = s_cost[wave][q];
+      const int32_t e = s_engine[wave][q];
+      if (q <= lane) {
+        freed = __dadd_rn(freed, f);
+        cost = __fadd_rn(cost, c);
+        top = q == 0 ? freed : fmax(top, freed);
+        interrupt = interrupt || (e & 0x40);   // Preempt / Abort interrupt active work
       }
     }
-#pragma unroll
-    for (int p = 0; p < kRecSteps; ++p)
-      if (p < ne) step(p, e0 + (int32_t)(uint32_t)key[p], (int32_t)(key[p] >> 32));
+    if (mine) {
+      total = __fadd_rn(cost, interrupt ? c_int : 0.0f);
+      steps[e0 + lane] = maestro_plan_step{top, total, e0 + (s_engine[wave][lane] & 0x3F)};
+    }
   } else {
-    // the rank of engine i among the node's keys is its position in priority order; the step
-    // array holds the order (engine of each position) before the running sums overwrite it
-    for (int32_t i = 0; i < ne; ++i) {
+    // the step array holds the order (engine of each position) before the running sums overwrite it
+    for (int32_t i = lane; i < ne; i += 64) {
       const int64_t ki = engine_key(engine_level[e0 + i], i);
       int32_t rank = 0;
       for (int32_t q = 0; q < ne; ++q) rank += engine_key(engine_level[e0 + q], q) < ki ? 1 : 0;
       steps[e0 + rank].engine = e0 + i;
     }
-    for (int32_t p = 0; p < ne; ++p) {
-      const int32_t e = steps[e0 + p].engine;
-      step(p, e, engine_level[e]);
+    __threadfence();                     // the order is read below by other lanes than wrote it
+    double freed = 0.0, run = 0.0;
+    float cost = 0.0f;
+    bool interrupt = false;
+    for (int32_t p = 0; p < ne; ++p) {   // every lane the same sums; lane p % 64 stores step p
+      const int32_t e = __builtin_amdgcn_readfirstlane(__hip_atomic_load(&steps[e0 + p].engine, __ATOMIC_RELAXED,
+                                                                         __HIP_MEMORY_SCOPE_WORKGROUP));
+      interrupt = interrupt || engine_level[e] >= 4;
+      freed = __dadd_rn(freed, engine_freed[e]);
+      cost = __fadd_rn(cost, engine_cost[e]);
+      run = p == 0 ? freed : fmax(run, freed);
+      const float c = __fadd_rn(cost, interrupt ? c_int : 0.0f);
+      if (lane == (p & 63)) steps[e0 + p] = maestro_plan_step{run, c, e};
+      if (p == lane) {
+        top = run;
+        total = c;
+      }
     }
   }
-#pragma unroll
-  for (int p = 0; p < kRecSteps; ++p) {
-    if (p >= ne) {
-      out.freed[p] = INFINITY;
-      out.cost[p] = 0.0f;
-    }
+  if (lane < kRecSteps) {
+    plans[j].freed[lane] = lane < ne ? top : INFINITY;
+    plans[j].cost[lane] = lane < ne ? total : 0.0f;
   }
-  out.n_engines = ne;
-  out.first_step = e0;
-#pragma unroll
-  for (int i = 0; i < 6; ++i) out.reserved[i] = 0;
-  plans[j] = out;
+  // n_engines, first_step and the reserved words
+  if (lane < 8) (&plans[j].n_engines)[lane] = lane == 0 ? ne : lane == 1 ? e0 : 0;
 }
 
 // How T_act(N, M(T)) of Eq. 6 reaches the kernel: a node's activation latency unless the
@@ -1036,7 +1055,7 @@ maestro_status launch_degradation_plans(int32_t n_nodes, const int32_t* engine_o
                                        const double* engine_freed_bytes, const float* engine_cost_ms, float c_int_ms,
                                        maestro_deg_plan* plans, maestro_plan_step* steps, hipStream_t stream) {
   if (n_nodes == 0) return MAESTRO_OK;
-  plan_kernel<<<dim3((unsigned)((n_nodes + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream>>>(
+  plan_kernel<<<dim3((unsigned)((n_nodes + kPlanWaves - 1) / kPlanWaves)), dim3(kThreads), 0, stream>>>(
       n_nodes, engine_offset, engine_level, engine_freed_bytes, engine_cost_ms, c_int_ms, plans, steps);
   return launch_status();
 }
