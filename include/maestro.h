@@ -405,8 +405,8 @@ MAESTRO_API maestro_status maestro_activation_latency(int32_t n_nodes, int32_t n
  *   rho[0]  = the value of rank ceil(q (m - 1)) (0-based, ascending) among ewma[0 .. m-1]
  * kv_actual, kv_pred [m] float64 (device; kv_pred > 0, both finite); 0 < beta <= 1; 0 <= q <= 1
  * (a high quantile, 0.9 - 0.95). ewma doubles as the selection's input, and for windows longer
- * than 16,384 stages as the call's scratch (per-tile scan state in the first words of each
- * 8,192-stage range): its contents are defined once the stream reaches the call's end. The
+ * than 4,096 stages as the call's scratch (per-tile scan state in the first words of each
+ * 2,048-stage range): its contents are defined once the stream reaches the call's end. The
  * float64 EWMA is a parallel scan, so ewma can differ from a sequential evaluation in the last
  * place. Workspace: maestro_quantiles_workspace(m) bytes (0 below 32,768 stages; NULL allowed
  * then). Errors: INVALID_ARG for m < 1, beta or q out of range, a NULL or misaligned array;
@@ -420,9 +420,9 @@ MAESTRO_API maestro_status maestro_adaptive_rho(const double* kv_actual, const d
  * floor(q_lo * (m - 1)) and ceil(q_hi * (m - 1)) of values[0 .. m-1] (device, finite), ranks
  * counted from 0 in ascending order of the float values (-0 before +0); no interpolation.
  * 0 <= q_lo <= q_hi <= 1, 1 <= m < 2^32. Below 32,768 values one workgroup selects (no
- * workspace); from there on 256 workgroups count each 8-bit digit pass into histograms of
- * their own in the workspace (maestro_quantiles_workspace(m) bytes) and one workgroup picks
- * the bins, eight launches in all. WORKSPACE for a workspace that is too small. */
+ * workspace); from there on a workgroup per 4,096 values, up to 128, counts each 8-bit digit into
+ * histograms of its own in the workspace (maestro_quantiles_workspace(m) bytes) and picks the
+ * digit before from its predecessors', five launches in all. WORKSPACE for a workspace that is too small. */
 MAESTRO_API maestro_status maestro_quantiles(const float* values, int64_t m, double q_lo, double q_hi,
                              float* out, void* workspace, size_t workspace_bytes, void* stream);
 /* Workspace bytes of maestro_quantiles and maestro_adaptive_rho over m values (0 when none is
