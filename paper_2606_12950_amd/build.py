@@ -17,7 +17,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libmaestro.so")
-SOURCES = ("api.hip", "predict.hip", "roles.hip", "route.hip", "fitness.hip", "fitness_pruned.hip", "prioritize.hip")
+SOURCES = ("api.hip", "predict.hip", "predict_split.hip", "roles.hip", "route.hip", "fitness.hip", "fitness_pruned.hip", "prioritize.hip")
 CALIBRATE_LIB = os.path.join(PKG, "libmaestro_calibrate.so")
 CALIBRATE_SOURCE = "calibrate.hip"
 
@@ -34,10 +34,10 @@ FLAGS = [
     "-Wall", "-Wno-unused-function",
     f"-I{INCLUDE}", f"-I{CSRC}",
 ]
-# per-source additions: the predictor converts its MFMA accumulators with vector ALU
+# per-source additions: the predictors convert their MFMA accumulators with vector ALU
 # instructions, which read only architectural VGPRs; keeping MFMA results there avoids a copy
 # out of the accumulation registers for every converted value
-EXTRA = {"predict.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+EXTRA = {src: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for src in ("predict.hip", "predict_split.hip")}
 
 
 def _compile(src: str, outdir: str, verbose: bool) -> str:

@@ -22,6 +22,20 @@ maestro_status launch_predict_two_phase(const maestro_predictor& p, const maestr
                                         const float* kv_bytes_per_token, int32_t n_models, float* p_tool,
                                         float* pred_len, double* kv_bytes, hipStream_t stream);
 
+// The same predictions by the small-batch kernel (bfloat16 networks; tp: the two-phase form).
+struct TwoPhaseArgs;
+int32_t split_tile_rows(const maestro_predictor& p);
+maestro_status launch_predict_split(const maestro_predictor& p, const TwoPhaseArgs* tp, int64_t n, const void* x,
+                                    const int32_t* prompt_len, const int32_t* model_id,
+                                    const float* kv_bytes_per_token, int32_t n_models, float* pred_len,
+                                    double* kv_bytes, hipStream_t stream);
+// group_tile: the tile count, then the first tile of every regressor
+maestro_status launch_roles_split(const maestro_predictor& p, int64_t n, const void* x, const float* coef,
+                                  float max_len, const int32_t* group_tile, int32_t n_groups, const int32_t* perm,
+                                  const int32_t* prompt_p, const int32_t* model_p, const int32_t* p_bits,
+                                  int64_t max_tiles, const float* kv_bytes_per_token, int32_t n_models,
+                                  float* pred_len, double* kv_bytes, hipStream_t stream);
+
 // Per-role regressors: bucketing by regressor, then the fused predictor as a grouped GEMM.
 maestro_status launch_role_lengths(const maestro_predictor& p, const maestro_role_regressors& r, int64_t n,
                                    const void* x, const int32_t* prompt_len, const int32_t* model_id,
@@ -31,6 +45,8 @@ maestro_status launch_role_lengths(const maestro_predictor& p, const maestro_rol
 size_t role_lengths_workspace_bytes(int64_t n, int32_t n_groups);
 // rows of one tile of the role regressors' grouped launch for the predictor's shape
 int32_t role_tile_rows(const maestro_predictor& p);
+// whether the small-batch kernel takes the regressors of n stages (tiles of split_tile_rows(p))
+bool roles_split(const maestro_predictor& p, int64_t n);
 maestro_status launch_role_regressors(const maestro_predictor& p, int64_t n, const void* x, const float* coef,
                                       float max_len, const int32_t* tile_group, const int32_t* perm,
                                       const int32_t* prompt_p, const int32_t* model_p, const int32_t* p_bits,

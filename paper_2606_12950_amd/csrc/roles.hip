@@ -97,16 +97,18 @@ __global__ __launch_bounds__(kBlock) void role_plan_kernel(int32_t n_blocks, int
       run += counts[(size_t)b * kMaxGroups + g];
     }
     const int32_t padded = (total + tile_rows - 1) / tile_rows * tile_rows;
+    if (t == 0) n_tiles[1 + g] = base / tile_rows;
     for (int32_t r = base + total + t; r < base + padded; r += kBlock) {   // padding rows
       perm[r] = -1;
       prompt_p[r] = 0;
       model_p[r] = 0;
       p_bits[r] = 0;
     }
-    for (int32_t tt = base / tile_rows + t; tt < (base + padded) / tile_rows; tt += kBlock) tile_group[tt] = g;
+    if (tile_group)
+      for (int32_t tt = base / tile_rows + t; tt < (base + padded) / tile_rows; tt += kBlock) tile_group[tt] = g;
     base += padded;
   }
-  if (t == 0) n_tiles[0] = base / tile_rows;
+  if (t == 0) n_tiles[0] = base / tile_rows;   // n_tiles[1 + g]: the first tile of regressor g
 }
 
 __global__ __launch_bounds__(kBlock) void role_scatter_kernel(
@@ -192,16 +194,23 @@ maestro_status launch_role_lengths(const maestro_predictor& p, const maestro_rol
   int32_t* offsets = reinterpret_cast<int32_t*>(ws + L.offsets);
   int32_t* tile_group = reinterpret_cast<int32_t*>(ws + L.tile_group);
   int32_t* n_tiles = reinterpret_cast<int32_t*>(ws + L.n_tiles);
-  const int32_t tile_rows = role_tile_rows(p);
-  const int64_t tiles_max = (L.rows_max + tile_rows - 1) / tile_rows;
+  // the small-batch kernel's tiles are shorter: it finds a tile's regressor from the regressors' first
+  // tiles, since the per-tile table is sized for 128 rows a tile
+  const bool split = roles_split(p, n);
+  const int32_t tile_rows = split ? split_tile_rows(p) : role_tile_rows(p);
+  const int64_t tiles_max =
+      split ? (n + (int64_t)r.n_regressors * (tile_rows - 1)) / tile_rows : (L.rows_max + tile_rows - 1) / tile_rows;
   const dim3 grid((unsigned)L.n_blocks), block(kBlock);
   role_count_kernel<<<grid, block, 0, stream>>>(n, role_id, r.n_roles, r.role_regressor, r.n_regressors, counts);
   role_plan_kernel<<<dim3(1), block, 0, stream>>>((int32_t)L.n_blocks, r.n_regressors, tile_rows, counts, offsets,
-                                                 tile_group, perm, prompt_p, model_p, p_bits, n_tiles);
+                                                 split ? nullptr : tile_group, perm, prompt_p, model_p, p_bits, n_tiles);
   role_scatter_kernel<<<grid, block, 0, stream>>>(n, role_id, r.n_roles, r.role_regressor, r.n_regressors, offsets,
                                                   prompt_len, model_id, p_tool, perm, prompt_p, model_p, p_bits);
   const maestro_status st = launch_status();
   if (st != MAESTRO_OK) return st;
+  if (split)
+    return launch_roles_split(p, n, x, r.tool_coef, r.max_len, n_tiles, r.n_regressors, perm, prompt_p, model_p, p_bits,
+                              tiles_max, kv_bytes_per_token, n_models, pred_len, kv_bytes, stream);
   return launch_role_regressors(p, n, x, r.tool_coef, r.max_len, tile_group, perm, prompt_p, model_p, p_bits, n_tiles,
                                 tiles_max, kv_bytes_per_token, n_models, pred_len, kv_bytes, stream);
 }
