@@ -13,15 +13,15 @@
 //     summation order. The block also counts the first radix digit of its tile.
 //  2. stable LSD radix sort of the (slack, workflow) pairs, 4 passes of 8-bit digits over the
 //     order-preserving unsigned image of the key, on 1024-key tiles, one key per thread of a
-//     1024-thread block. Each pass: per-tile digit counts (for the first pass, from the chain
-//     kernel); the global offset of every (digit, tile), i.e. the exclusive scan of the count
-//     table in digit-major order, which each scatter block derives itself from the table when
-//     there are few tiles (four threads per digit read it, one memory round trip); with many
-//     tiles a group scan (prefix of each digit within groups of 16 .. 256 tiles, in place, plus
-//     the group totals) and a one-block scan over the group totals and the digits prepare it, and
-//     the scatter adds two table entries; and a scatter in which each wavefront ranks its keys
+//     1024-thread block (4096-key tiles beyond 128 of them). Each pass: per-tile digit counts (for
+//     the first pass of small tiles, from the chain kernel); the global offset of every (digit,
+//     tile), i.e. the exclusive scan of the count table in digit-major order, which each scatter
+//     block derives itself -- from the whole table when there are few tiles, from group totals and its
+//     own group's rows up to 1,024 tiles, and beyond that from the results of a group scan (prefix of
+//     each digit within groups of 16 .. 256 tiles, in place, plus the group totals) and a one-block
+//     scan over the group totals and the digits; and a scatter in which each wavefront ranks its keys
 //     digit by digit with ballots (wave multisplit) in input order, so equal digits keep their
-//     relative order.
+//     relative order. Up to 4,096 workflows one workgroup does all of it in one launch.
 //     The key array is padded to whole tiles with all-ones keys, which always sort last and
 //     never reach the caller's output.
 #include <atomic>
@@ -45,6 +45,8 @@ constexpr int kRadixBits = 8;
 constexpr int kBuckets = 1 << kRadixBits;
 constexpr int kPasses = 32 / kRadixBits;
 // count table: counts[t * kBuckets + d] = keys of tile t with digit d (tile-major)
+constexpr int kSumTiles = 64;                      // tiles per group total of a middling batch
+constexpr int kSumMaxTiles = 1024;                 // more tiles take the scans
 
 constexpr int64_t kLatSat = INT64_MAX;             // infinitely late (absorbing)
 constexpr double kLatUsLimit = 1099511627776.0;    // 2^40 microseconds
@@ -155,6 +157,51 @@ __device__ int64_t long_chain_suffix(int64_t first, int64_t end, int64_t head, i
   return r;
 }
 
+// deadline - now - remaining, clamped to int32 (|rem_head| <= 2^62, so saturating the two differences
+// keeps the clamp exact); INT32_MIN when the remaining time is infinite
+__device__ __forceinline__ int32_t slack_of(int64_t rem_head, int64_t deadline_us, int64_t now_us) {
+  if (rem_head == kLatSat) return INT32_MIN;
+  const int64_t slack = sat_sub(sat_sub(deadline_us, now_us), rem_head);
+  return slack > INT32_MAX ? INT32_MAX : (slack < INT32_MIN ? INT32_MIN : (int32_t)slack);
+}
+
+// Exclusive prefix sum of v over threads 0 .. 255 in thread order (called by the whole block; the
+// other threads' results are meaningless). Two barriers; wsum holds one sum per wavefront and may be
+// reused after the next barrier.
+__device__ __forceinline__ uint32_t digit_exclusive(uint32_t v, uint32_t (&wsum)[kBuckets / 64]) {
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  uint32_t incl = v;
+  if (tid < kBuckets) {
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t y = __shfl_up(incl, off);
+      if (lane >= off) incl += y;
+    }
+    if (lane == 63) wsum[wave] = incl;
+  }
+  __syncthreads();
+  uint32_t add = 0;
+#pragma unroll
+  for (int w = 0; w < kBuckets / 64 - 1; ++w) add += w < wave ? wsum[w] : 0u;
+  __syncthreads();
+  return add + incl - v;
+}
+
+// Rank of a key among its wavefront's keys of the same digit, in lane order, after the `count` of
+// earlier ones that the wavefront keeps in LDS (its own accesses stay in program order).
+__device__ __forceinline__ uint32_t wave_rank(uint32_t d, uint32_t* count, uint64_t lanes_below) {
+  uint64_t same = ~0ull;
+#pragma unroll
+  for (int b = 0; b < kRadixBits; ++b) {
+    const bool bit = (d >> b) & 1u;
+    const uint64_t ones = __ballot(bit);
+    same &= bit ? ones : ~ones;
+  }
+  const uint32_t before = count[d];
+  if ((same & lanes_below) == 0ull) count[d] = before + (uint32_t)__popcll(same);   // first lane of the digit
+  return before + (uint32_t)__popcll(same & lanes_below);
+}
+
 // One block per sort tile, one workflow per thread; also writes the tile's counts of the
 // first digit. When the block's workflows span at most kStageCap stages (the usual case), the
 // stage latencies pass through LDS: quantised by a coalesced sweep over the block's stage
@@ -166,11 +213,13 @@ __global__ __launch_bounds__(kTile) void chain_kernel(
     const float* __restrict__ stage_latency_s, const int32_t* __restrict__ cursor,
     const int64_t* __restrict__ deadline_us, int64_t now_us, int64_t* __restrict__ remaining_us,
     int32_t* __restrict__ slack_key, uint32_t* __restrict__ keys, uint32_t* __restrict__ vals,
-    uint32_t* __restrict__ counts, uint32_t* __restrict__ long_flag, uint32_t epoch) {
+    uint32_t* __restrict__ counts, uint32_t* __restrict__ long_flag, uint32_t epoch, uint32_t* __restrict__ gsum,
+    int n_groups) {
   __shared__ uint32_t hist[kBuckets];
   __shared__ int64_t stage_us[kStageCap];
   const int tid = threadIdx.x, tile = blockIdx.x;
   if (tid < kBuckets) hist[tid] = 0;
+  if (tile < n_groups && tid < kBuckets) gsum[(int64_t)tile * kBuckets + tid] = 0;   // of the first pass
   const int64_t w = (int64_t)tile * kTile + tid;
   // blocks past the last workflow (padding of large batches) have an empty stage range
   const int64_t w_lo = min((int64_t)n_workflows, (int64_t)tile * kTile);
@@ -217,14 +266,7 @@ __global__ __launch_bounds__(kTile) void chain_kernel(
         }
       }
     }
-    int32_t key;
-    if (rem_head == kLatSat) {
-      key = INT32_MIN;
-    } else {
-      // |rem_head| <= 2^62, so saturating the two differences keeps the int32 clamp exact
-      const int64_t slack = sat_sub(sat_sub(deadline_us[w], now_us), rem_head);
-      key = slack > INT32_MAX ? INT32_MAX : (slack < INT32_MIN ? INT32_MIN : (int32_t)slack);
-    }
+    const int32_t key = slack_of(rem_head, deadline_us[w], now_us);
     slack_key[w] = key;
     ukey = (uint32_t)key ^ 0x80000000u;   // order-preserving unsigned image
   }
@@ -294,13 +336,7 @@ __global__ __launch_bounds__(kTile) void long_chain_kernel(
         if (tid == t) rem_head = r;
       }
       if (is_long) {
-        int32_t key;
-        if (rem_head == kLatSat) {
-          key = INT32_MIN;
-        } else {
-          const int64_t slack = sat_sub(sat_sub(deadline_us[w], now_us), rem_head);
-          key = slack > INT32_MAX ? INT32_MAX : (slack < INT32_MIN ? INT32_MIN : (int32_t)slack);
-        }
+        const int32_t key = slack_of(rem_head, deadline_us[w], now_us);
         slack_key[w] = key;
         const uint32_t ukey = (uint32_t)key ^ 0x80000000u;
         const uint32_t placeholder = keys[w];
@@ -316,10 +352,12 @@ __global__ __launch_bounds__(kTile) void long_chain_kernel(
   }
 }
 
-// Per-tile digit counts of the digit at `shift`; tiles of kTile * ITEMS keys.
+// Per-tile digit counts of the digit at `shift`; tiles of kTile * ITEMS keys. With gsum (zeroed by the
+// kernel before) also the totals of groups of kSumTiles tiles.
 template <int ITEMS>
 __global__ __launch_bounds__(kTile) void radix_count_kernel(const uint32_t* __restrict__ keys, int shift,
-                                                            uint32_t* __restrict__ counts) {
+                                                            uint32_t* __restrict__ counts,
+                                                            uint32_t* __restrict__ gsum) {
   __shared__ uint32_t hist[kBuckets];
   const int tid = threadIdx.x, tile = blockIdx.x;
   if (tid < kBuckets) hist[tid] = 0;
@@ -330,7 +368,11 @@ __global__ __launch_bounds__(kTile) void radix_count_kernel(const uint32_t* __re
 #pragma unroll
   for (int i = 0; i < ITEMS; ++i) atomicAdd(&hist[(k[i] >> shift) & (kBuckets - 1)], 1u);
   __syncthreads();
-  if (tid < kBuckets) counts[(int64_t)tile * kBuckets + tid] = hist[tid];
+  if (tid < kBuckets) {
+    const uint32_t c = hist[tid];
+    counts[(int64_t)tile * kBuckets + tid] = c;
+    if (gsum && c) atomicAdd(&gsum[(int64_t)(tile / kSumTiles) * kBuckets + tid], c);
+  }
 }
 
 // Many tiles, step 1: one block per group of group_tiles tiles (a power of two, 16 .. 256, so
@@ -415,25 +457,36 @@ __global__ __launch_bounds__(1024) void radix_top_scan_kernel(uint32_t* __restri
 
 // Stable scatter of one tile of kTile * ITEMS keys by the digit at `shift`: wavefront w holds
 // tile positions [64 ITEMS w, 64 ITEMS (w + 1)), item i the 64 of them from 64 (ITEMS w + i).
-// out_keys may be null (last pass); positions >= out_limit are padding and are dropped. With
-// kFusedScan (few tiles, one key per thread) the block derives its digit offsets from the count
-// table (digit totals over all tiles, exclusive-scanned, plus the counts of the earlier tiles)
-// and writes each key straight to its place; otherwise `table` holds the in-group prefixes of
-// the group scan and `gtable` the group offsets of the top scan, and the tile is first placed
-// in digit order in LDS so that consecutive threads write consecutive addresses.
+// out_keys may be null (last pass); positions >= out_limit are padding and are dropped. The place of
+// a digit's first key of this tile comes from
+//   kFusedScan  few tiles, one key per thread: the block adds up the whole count table (digit totals,
+//               exclusive-scanned, plus the counts of the earlier tiles) and writes each key
+//               straight to its place;
+//   kFromSums   up to kSumMaxTiles tiles: the block adds up the group totals (gtable) and the counts
+//               of the earlier tiles of its own group, 20 words a thread at most, instead of two
+//               launches between count and scatter (7.5 us a pass at 2^20 keys; beyond 1,024
+//               tiles every block reading 64 KB would cost more); it also zeroes the totals of the
+//               next pass;
+//   kScanned    `table` holds the in-group prefixes of the group scan and `gtable` the group offsets
+//               of the top scan.
+// With the latter two the tile is first placed in digit order in LDS so that consecutive threads write
+// consecutive addresses.
 constexpr int kFusedScanMaxTiles = 128;
-template <bool kFusedScan, int ITEMS>
+enum Offsets { kFusedScan, kFromSums, kScanned };
+template <Offsets kOff, int ITEMS>
 __global__ __launch_bounds__(kTile) void radix_scatter_kernel(
     const uint32_t* __restrict__ keys, const uint32_t* __restrict__ vals, int shift, int n_tiles,
     const uint32_t* __restrict__ table, const uint32_t* __restrict__ gtable, int group_tiles,
-    uint32_t* __restrict__ out_keys, uint32_t* __restrict__ out_vals, int64_t out_limit) {
-  static_assert(!kFusedScan || ITEMS == 1, "the fused offsets path handles one key per thread");
+    uint32_t* __restrict__ out_keys, uint32_t* __restrict__ out_vals, int64_t out_limit,
+    uint32_t* __restrict__ next_gsum) {
+  static_assert(kOff != kFusedScan || ITEMS == 1, "the fused offsets path handles one key per thread");
   constexpr int TK = kTile * ITEMS;
-  constexpr int kStage = kFusedScan ? 1 : TK;
+  constexpr int kStage = kOff == kFusedScan ? 1 : TK;
   __shared__ uint32_t wcount[kWaves][kBuckets];
   __shared__ uint32_t base[kBuckets];
   __shared__ uint32_t part_before[4][kBuckets], part_total[4][kBuckets];
-  __shared__ uint32_t lbase[kBuckets];                  // tile-local digit counts, then their scan
+  __shared__ uint32_t lbase[kBuckets];                  // tile-local place of each digit's first key
+  __shared__ uint32_t wsum[kBuckets / 64];
   __shared__ uint32_t s_key[kStage], s_val[kStage];     // the tile in digit order
   const int tid = threadIdx.x, tile = blockIdx.x;
   const int wave = tid >> 6, lane = tid & 63;
@@ -446,39 +499,44 @@ __global__ __launch_bounds__(kTile) void radix_scatter_kernel(
   }
   for (int i = tid; i < kWaves * kBuckets; i += kTile) (&wcount[0][0])[i] = 0;
 
-  if (kFusedScan) {
-    // thread (q, d), q = tid / 256: digit d over tiles q, q + 4, q + 8, ...: all loads of a
-    // thread are independent and go out together
+  if constexpr (kOff != kScanned) {
+    // thread (q, d), q = tid / 256: digit d over rows q, q + 4, q + 8, ... of the tables: all loads
+    // of a thread are independent and go out together
     const int d = tid & (kBuckets - 1), q = tid >> 8;
     uint32_t before = 0, total = 0;
-    constexpr int kUnroll = kFusedScanMaxTiles / 4;
+    if constexpr (kOff == kFusedScan) {
+      constexpr int kUnroll = kFusedScanMaxTiles / 4;
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const int t = q + 4 * u;
-      const uint32_t c = t < n_tiles ? table[(int64_t)t * kBuckets + d] : 0u;
-      total += c;
-      before += t < tile ? c : 0u;
+      for (int u = 0; u < kUnroll; ++u) {
+        const int t = q + 4 * u;
+        const uint32_t c = t < n_tiles ? table[(int64_t)t * kBuckets + d] : 0u;
+        total += c;
+        before += t < tile ? c : 0u;
+      }
+    } else {
+      const int group = tile / kSumTiles, n_groups = (n_tiles + kSumTiles - 1) / kSumTiles;
+      if (tile < n_groups && tid < kBuckets) next_gsum[(int64_t)tile * kBuckets + tid] = 0;
+#pragma unroll
+      for (int u = 0; u < kSumMaxTiles / kSumTiles / 4; ++u) {
+        const int g = q + 4 * u;
+        const uint32_t c = g < n_groups ? gtable[(int64_t)g * kBuckets + d] : 0u;
+        total += c;
+        before += g < group ? c : 0u;
+      }
+#pragma unroll
+      for (int u = 0; u < kSumTiles / 4; ++u) {
+        const int t = group * kSumTiles + q + 4 * u;
+        before += t < tile ? table[(int64_t)t * kBuckets + d] : 0u;
+      }
     }
     part_before[q][d] = before;
     part_total[q][d] = total;
     __syncthreads();
-    if (tid < kBuckets) {
-      base[tid] = part_total[0][tid] + part_total[1][tid] + part_total[2][tid] + part_total[3][tid];
-      part_before[0][tid] += part_before[1][tid] + part_before[2][tid] + part_before[3][tid];
-    }
-    __syncthreads();
-    for (int off = 1; off < kBuckets; off <<= 1) {   // inclusive scan of the digit totals
-      uint32_t v = 0;
-      if (tid < kBuckets && tid >= off) v = base[tid - off];
-      __syncthreads();
-      if (tid < kBuckets) base[tid] += v;
-      __syncthreads();
-    }
-    if (tid < kBuckets) {
-      const uint32_t incl = base[tid];
-      const uint32_t own = part_total[0][tid] + part_total[1][tid] + part_total[2][tid] + part_total[3][tid];
-      base[tid] = incl - own + part_before[0][tid];
-    }
+    uint32_t own = 0;
+    if (tid < kBuckets) own = part_total[0][tid] + part_total[1][tid] + part_total[2][tid] + part_total[3][tid];
+    const uint32_t first = digit_exclusive(own, wsum);
+    if (tid < kBuckets)
+      base[tid] = first + part_before[0][tid] + part_before[1][tid] + part_before[2][tid] + part_before[3][tid];
   } else {
     if (tid < kBuckets)
       base[tid] = gtable[(int64_t)(tile / group_tiles) * kBuckets + tid] + table[(int64_t)tile * kBuckets + tid];
@@ -486,36 +544,25 @@ __global__ __launch_bounds__(kTile) void radix_scatter_kernel(
   __syncthreads();
 
   // rank among this wavefront's keys with the same digit, in position order: items in order,
-  // lanes in order within an item (the wavefront's own LDS accesses stay in program order)
+  // lanes in order within an item
   const uint64_t lanes_below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 #pragma unroll
   for (int i = 0; i < ITEMS; ++i) {
-    const uint32_t d = (key[i] >> shift) & (kBuckets - 1);
-    uint64_t same = ~0ull;
-#pragma unroll
-    for (int b = 0; b < kRadixBits; ++b) {
-      const bool bit = (d >> b) & 1u;
-      const uint64_t ones = __ballot(bit);
-      same &= bit ? ones : ~ones;
-    }
-    const uint32_t before = wcount[wave][d];
-    dig[i] = d;
-    rank[i] = before + (uint32_t)__popcll(same & lanes_below);
-    if ((same & lanes_below) == 0ull) wcount[wave][d] = before + (uint32_t)__popcll(same);   // first lane of the digit
+    dig[i] = (key[i] >> shift) & (kBuckets - 1);
+    rank[i] = wave_rank(dig[i], wcount[wave], lanes_below);
   }
   __syncthreads();
+  uint32_t in_tile = 0;
   if (tid < kBuckets) {   // offsets of each wavefront inside the tile's digit groups
-    uint32_t run = 0;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
       const uint32_t c = wcount[w][tid];
-      wcount[w][tid] = run;
-      run += c;
+      wcount[w][tid] = in_tile;
+      in_tile += c;
     }
-    lbase[tid] = run;                       // the tile's count of digit tid, scanned below
   }
-  __syncthreads();
-  if (kFusedScan) {   // few tiles: latency-bound, write straight from the ranks
+  if constexpr (kOff == kFusedScan) {   // few tiles: latency-bound, write straight from the ranks
+    __syncthreads();
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
       const int64_t pos = (int64_t)base[dig[i]] + wcount[wave][dig[i]] + rank[i];
@@ -526,19 +573,13 @@ __global__ __launch_bounds__(kTile) void radix_scatter_kernel(
     }
     return;
   }
-  for (int off = 1; off < kBuckets; off <<= 1) {   // inclusive scan of the tile's digit counts
-    uint32_t v = 0;
-    if (tid < kBuckets && tid >= off) v = lbase[tid - off];
-    __syncthreads();
-    if (tid < kBuckets) lbase[tid] += v;
-    __syncthreads();
-  }
-  // place the tile in digit order in LDS (lbase is now inclusive: digit d starts at
-  // lbase[d - 1]), then write it out
+  const uint32_t local = digit_exclusive(in_tile, wsum);
+  if (tid < kBuckets) lbase[tid] = local;
+  __syncthreads();
+  // place the tile in digit order in LDS, then write it out
 #pragma unroll
   for (int i = 0; i < ITEMS; ++i) {
-    const uint32_t d = dig[i];
-    const uint32_t lp = (d == 0 ? 0u : lbase[d - 1]) + wcount[wave][d] + rank[i];
+    const uint32_t lp = lbase[dig[i]] + wcount[wave][dig[i]] + rank[i];
     s_key[lp] = key[i];
     s_val[lp] = val[i];
   }
@@ -548,7 +589,7 @@ __global__ __launch_bounds__(kTile) void radix_scatter_kernel(
     const int e = i * kTile + tid;
     const uint32_t k2 = s_key[e], v2 = s_val[e];
     const uint32_t d2 = (k2 >> shift) & (kBuckets - 1);
-    const int64_t pos = (int64_t)base[d2] + (e - (d2 == 0 ? 0u : lbase[d2 - 1]));
+    const int64_t pos = (int64_t)base[d2] + (e - lbase[d2]);
     if (pos < out_limit) {
       if (out_keys) out_keys[pos] = k2;
       out_vals[pos] = v2;
@@ -556,12 +597,133 @@ __global__ __launch_bounds__(kTile) void radix_scatter_kernel(
   }
 }
 
+// The whole call in one workgroup, for up to ITEMS * kTile workflows: chain sums and keys as in the
+// chain kernel (one 1,024-workflow tile after the other), long chains by all threads, and the radix
+// sort with keys and indices in LDS. Nine launches, each a few microseconds of latency over a batch
+// this small, took 32 us a call for 300 workflows against 12, and 36 for 4,096 against 33 (where
+// sixteen wavefronts ranking four keys a lane take as long as the launches; beyond, tiles of their own
+// are faster).
+template <int ITEMS>
+__global__ __launch_bounds__(kTile) void small_batch_kernel(
+    int32_t n_workflows, const int64_t* __restrict__ chain_offset, const float* __restrict__ stage_latency_s,
+    const int32_t* __restrict__ cursor, const int64_t* __restrict__ deadline_us, int64_t now_us,
+    int64_t* __restrict__ remaining_us, int32_t* __restrict__ slack_key, int32_t* __restrict__ order) {
+  __shared__ int64_t stage_us[kStageCap];
+  __shared__ uint32_t wcount[kWaves][kBuckets];
+  __shared__ uint32_t lbase[kBuckets];
+  __shared__ uint32_t wsum[kBuckets / 64];
+  __shared__ int64_t wtot[kWaves];
+  __shared__ int64_t s_head_rem;
+  __shared__ int32_t s_long[kTile];
+  __shared__ int32_t s_n_long;
+  __shared__ uint32_t s_key[ITEMS * kTile], s_val[ITEMS * kTile];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  for (int tile = 0; tile * kTile < n_workflows; ++tile) {   // workgroup-uniform
+    const int w = tile * kTile + tid;
+    const int64_t s_lo = chain_offset[tile * kTile], s_hi = chain_offset[min(n_workflows, (tile + 1) * kTile)];
+    const bool staged = s_hi - s_lo <= kStageCap;
+    if (staged)
+      for (int64_t j = s_lo + tid; j < s_hi; j += kTile) stage_us[j - s_lo] = latency_us(stage_latency_s[j]);
+    if (tid == 0) s_n_long = 0;
+    __syncthreads();
+    int64_t rem_head = 0;
+    if (w < n_workflows) {
+      const int64_t first = chain_offset[w], end = chain_offset[w + 1];
+      const int64_t head = first + (cursor ? max(0, cursor[w]) : 0);
+      if (end - first > kLongChain) {
+        s_long[atomicAdd(&s_n_long, 1)] = tid;
+      } else {
+        int64_t suffix = 0;
+#pragma unroll 1
+        for (int64_t j = end - 1; j >= first; --j) {
+          suffix = sat_add(staged ? stage_us[j - s_lo] : latency_us(stage_latency_s[j]), suffix);
+          if (staged) stage_us[j - s_lo] = suffix;
+          else if (remaining_us) remaining_us[j] = suffix;
+          if (j == head) rem_head = suffix;
+        }
+      }
+    }
+    __syncthreads();
+    const int n_long = s_n_long;
+    for (int q = 0; q < n_long; ++q) {   // every thread takes part in each long chain
+      const int t = s_long[q];
+      const int64_t first = chain_offset[tile * kTile + t], end = chain_offset[tile * kTile + t + 1];
+      const int64_t head = first + (cursor ? max(0, cursor[tile * kTile + t]) : 0);
+      const int64_t r = staged ? long_chain_suffix<true>(first, end, head, s_lo, stage_us, stage_latency_s, nullptr,
+                                                         wtot, &s_head_rem)
+                               : long_chain_suffix<false>(first, end, head, 0, nullptr, stage_latency_s, remaining_us,
+                                                          wtot, &s_head_rem);
+      if (tid == t) rem_head = r;
+    }
+    if (staged && remaining_us)
+      for (int64_t j = s_lo + tid; j < s_hi; j += kTile) remaining_us[j] = stage_us[j - s_lo];
+    uint32_t ukey = 0xFFFFFFFFu;           // padding sorts after every real workflow
+    if (w < n_workflows) {
+      const int32_t key = slack_of(rem_head, deadline_us[w], now_us);
+      slack_key[w] = key;
+      ukey = (uint32_t)key ^ 0x80000000u;
+    }
+    s_key[w] = ukey;
+    __syncthreads();                       // stage_us and s_long are reused by the next tile
+  }
+
+  // wavefront w holds positions [64 ITEMS w, 64 ITEMS (w + 1)), item i the 64 from 64 (ITEMS w + i)
+  const int p0 = wave * (64 * ITEMS) + lane;
+  const int tiles = (n_workflows + kTile - 1) / kTile * kTile;
+  uint32_t key[ITEMS], val[ITEMS], dig[ITEMS], rank[ITEMS];
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i) {
+    val[i] = (uint32_t)(p0 + i * 64);
+    key[i] = p0 + i * 64 < tiles ? s_key[p0 + i * 64] : 0xFFFFFFFFu;
+  }
+  const uint64_t lanes_below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+#pragma unroll 1
+  for (int shift = 0; shift < 32; shift += kRadixBits) {
+    for (int i = lane; i < kBuckets; i += 64) wcount[wave][i] = 0;
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+      dig[i] = (key[i] >> shift) & (kBuckets - 1);
+      rank[i] = wave_rank(dig[i], wcount[wave], lanes_below);
+    }
+    __syncthreads();
+    uint32_t in_tile = 0;
+    if (tid < kBuckets) {
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) {
+        const uint32_t c = wcount[w][tid];
+        wcount[w][tid] = in_tile;
+        in_tile += c;
+      }
+    }
+    const uint32_t first = digit_exclusive(in_tile, wsum);
+    if (tid < kBuckets) lbase[tid] = first;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+      const uint32_t pos = lbase[dig[i]] + wcount[wave][dig[i]] + rank[i];
+      s_key[pos] = key[i];
+      s_val[pos] = val[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+      key[i] = s_key[p0 + i * 64];
+      val[i] = s_val[p0 + i * 64];
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i)
+    if (p0 + i * 64 < n_workflows) order[p0 + i * 64] = (int32_t)val[i];
+}
+
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
 // Few workflows (up to kFusedScanMaxTiles tiles of kTile keys): one key per thread, offsets
 // fused into the scatter. More: tiles of kTile * kBigItems keys and the group/top scans.
+constexpr int32_t kSmallWorkflows = 4 * kTile;   // up to here one workgroup does everything
 struct PrioLayout {
-  bool fused;
+  bool fused, sums;
   int64_t tile_keys, n_tiles, group_tiles, n_groups, padded;
   size_t keys_a, vals_a, keys_b, vals_b, counts, gsum, flag, total;
 };
@@ -574,16 +736,21 @@ PrioLayout prio_layout(int32_t n_workflows) {
   L.padded = L.n_tiles * L.tile_keys;
   const size_t kb = align256(sizeof(uint32_t) * (size_t)L.padded);
   const size_t cb = align256(sizeof(uint32_t) * kBuckets * (size_t)L.n_tiles);
+  // The group totals of two passes take no more room than one pass's scanned groups would: 64 tiles
+  // a group against 16.
+  L.sums = !L.fused && L.n_tiles <= kSumMaxTiles;
   L.group_tiles = kMinGroupTiles;
   while (L.group_tiles < kMaxGroupTiles && L.n_tiles > (int64_t)kTargetGroups * L.group_tiles) L.group_tiles *= 2;
   L.n_groups = (L.n_tiles + L.group_tiles - 1) / L.group_tiles;
+  const int64_t scanned_groups = L.n_groups;
+  if (L.sums) L.n_groups = (L.n_tiles + kSumTiles - 1) / kSumTiles;
   L.keys_a = 0;
   L.vals_a = L.keys_a + kb;
   L.keys_b = L.vals_a + kb;
   L.vals_b = L.keys_b + kb;
   L.counts = L.vals_b + kb;
   L.gsum = L.counts + cb;
-  L.flag = L.gsum + (L.fused ? 0 : align256(sizeof(uint32_t) * kBuckets * (size_t)L.n_groups));
+  L.flag = L.gsum + (L.fused ? 0 : align256(sizeof(uint32_t) * kBuckets * (size_t)scanned_groups));
   L.total = L.flag + 256;
   return L;
 }
@@ -623,6 +790,16 @@ maestro_status launch_prioritize(int32_t n_workflows, int64_t n_stages,
                                  int32_t* order, void* workspace, size_t, hipStream_t stream) {
   (void)n_stages;
   if (n_workflows == 0) return MAESTRO_OK;
+#define MAESTRO_SMALL(ITEMS)                                                                                       \
+  small_batch_kernel<ITEMS><<<dim3(1), dim3(kTile), 0, stream>>>(n_workflows, chain_offset, stage_latency_s, cursor, \
+                                                                 deadline_us, now_us, remaining_us, slack_key, order)
+  if (n_workflows <= kSmallWorkflows) {
+    if (n_workflows <= kTile) MAESTRO_SMALL(1);
+    else if (n_workflows <= 2 * kTile) MAESTRO_SMALL(2);
+    else MAESTRO_SMALL(4);
+    return launch_status();
+  }
+#undef MAESTRO_SMALL
   const PrioLayout L = prio_layout(n_workflows);
   unsigned char* ws = static_cast<unsigned char*>(workspace);
   uint32_t* keys[2] = {reinterpret_cast<uint32_t*>(ws + L.keys_a), reinterpret_cast<uint32_t*>(ws + L.keys_b)};
@@ -643,7 +820,7 @@ maestro_status launch_prioritize(int32_t n_workflows, int64_t n_stages,
   // (block = tile) it also counts the first digit
   chain_kernel<<<dim3((unsigned)(L.padded / kTile)), dim3(kTile), 0, stream>>>(
       n_workflows, chain_offset, stage_latency_s, cursor, deadline_us, now_us, remaining_us,
-      slack_key, keys[0], vals[0], L.fused ? counts : nullptr, long_flag, epoch);
+      slack_key, keys[0], vals[0], L.fused ? counts : nullptr, long_flag, epoch, gsum, L.sums ? (int)L.n_groups : 0);
   // one tile per workgroup while that fits kLongChainBlocks workgroups, more per barrier beyond
   const int64_t chain_tiles = (n_workflows + (int64_t)kTile - 1) / kTile;
   int tiles_per_check = 1;
@@ -663,16 +840,21 @@ maestro_status launch_prioritize(int32_t n_workflows, int64_t n_stages,
     const int64_t limit = last ? (int64_t)n_workflows : L.padded;
     if (L.fused) {
       if (pass > 0)
-        radix_count_kernel<1><<<dim3(nt), dim3(kTile), 0, stream>>>(keys[src], shift, counts);
-      radix_scatter_kernel<true, 1><<<dim3(nt), dim3(kTile), 0, stream>>>(
-          keys[src], vals[src], shift, nt, counts, nullptr, 0, out_k, out_v, limit);
+        radix_count_kernel<1><<<dim3(nt), dim3(kTile), 0, stream>>>(keys[src], shift, counts, nullptr);
+      radix_scatter_kernel<kFusedScan, 1><<<dim3(nt), dim3(kTile), 0, stream>>>(
+          keys[src], vals[src], shift, nt, counts, nullptr, 0, out_k, out_v, limit, nullptr);
+    } else if (L.sums) {
+      uint32_t* sums[2] = {gsum, gsum + L.n_groups * kBuckets};
+      radix_count_kernel<kBigItems><<<dim3(nt), dim3(kTile), 0, stream>>>(keys[src], shift, counts, sums[pass & 1]);
+      radix_scatter_kernel<kFromSums, kBigItems><<<dim3(nt), dim3(kTile), 0, stream>>>(
+          keys[src], vals[src], shift, nt, counts, sums[pass & 1], 0, out_k, out_v, limit, sums[(pass + 1) & 1]);
     } else {
       const int ng = (int)L.n_groups;
-      radix_count_kernel<kBigItems><<<dim3(nt), dim3(kTile), 0, stream>>>(keys[src], shift, counts);
+      radix_count_kernel<kBigItems><<<dim3(nt), dim3(kTile), 0, stream>>>(keys[src], shift, counts, nullptr);
       radix_group_scan_kernel<<<dim3(ng), dim3(1024), 0, stream>>>(counts, nt, (int)L.group_tiles, gsum);
       radix_top_scan_kernel<<<dim3(1), dim3(1024), 0, stream>>>(gsum, ng);
-      radix_scatter_kernel<false, kBigItems><<<dim3(nt), dim3(kTile), 0, stream>>>(
-          keys[src], vals[src], shift, nt, counts, gsum, (int)L.group_tiles, out_k, out_v, limit);
+      radix_scatter_kernel<kScanned, kBigItems><<<dim3(nt), dim3(kTile), 0, stream>>>(
+          keys[src], vals[src], shift, nt, counts, gsum, (int)L.group_tiles, out_k, out_v, limit, nullptr);
     }
   }
   return launch_status();
