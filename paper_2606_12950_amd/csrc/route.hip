@@ -167,15 +167,14 @@ struct __align__(16) NodeEntry {          // 16 bytes: one node in a model's rea
 };
 
 // After the lists, per model, the largest headroom of every block of 8, 64 and 512 consecutive
-// list entries, rounded up to float32 (-inf past the last node): past its first kPlainWalk
-// entries a walk skips every block whose largest headroom cannot admit its stage, so a stage that
+// list entries, rounded up to float32 (-inf past the last node): past the staged head of its list
+// a walk skips every block whose largest headroom cannot admit its stage, so a stage that
 // fits few nodes, or none, does not visit every infeasible node. Rounding up keeps the test exact:
-// a block is skipped only when its true largest headroom is below the demand too. Measured on c4
-// (one GPU): with every headroom divided by 48 (59% of the pairs infeasible, 922 list entries per
-// stage) the route call takes 0.44 instead of 9.26 ms; on c4 itself 77.5 instead of 73.4 us (the
-// tables cost the sort 1 us, their test the walk 3 us). Gating the walk on the whole list's largest
-// headroom, or testing the tables from the first entry past the staged head, cost the c4 walk 3-13
-// us more.
+// a block is skipped only when its true largest headroom is below the demand too. A walk waits for
+// one dependent read after another, so the eight maxima of a block, and the eight entries of an
+// admitting smallest block, are read together: with 59% of 262,144 x 4,096 pairs infeasible (64
+// models, 4 nodes a stage) the walk takes 34 us, against 64 when one maximum or entry was read at a
+// time from the 33rd entry on (9.26 ms with no tables at all); the whole call 54.8 against 85 us.
 __host__ __device__ constexpr int32_t skip_blocks(int32_t n_nodes, int shift) {
   return (n_nodes + (1 << shift) - 1) >> shift;
 }
@@ -338,7 +337,26 @@ __global__ __launch_bounds__(1024) void sort_nodes_kernel(
 // once per workgroup, and a walk split into a loop over the head and one over the rest of the
 // list, were both slower (120 and 110 us against 94 us per c4 route call on one GPU).
 constexpr int kWalkHead = 8;
-constexpr int kPlainWalk = 32;            // entries visited before the skip tables are consulted
+
+// a row of eight floats at any float alignment
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// Which of the entries 8 row .. 8 row + 7 of a table of `size` block maxima admit `need`.
+__device__ __forceinline__ uint32_t admitting(const float* __restrict__ table, int row, int size, double need) {
+  float f[8];
+  if (8 * row + 8 <= size) {
+    *reinterpret_cast<f32x4u*>(f) = *reinterpret_cast<const f32x4u*>(table + 8 * row);
+    *reinterpret_cast<f32x4u*>(f + 4) = *reinterpret_cast<const f32x4u*>(table + 8 * row + 4);
+  } else {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) f[u] = 8 * row + u < size ? table[8 * row + u] : -INFINITY;
+  }
+  const int count = min(8, size - 8 * row);
+  uint32_t mask = 0;
+#pragma unroll
+  for (int u = 0; u < 8; ++u) mask |= u < count && need <= (double)f[u] ? 1u << u : 0u;
+  return mask;
+}
 
 // one stage's walk down its model's list
 template <int KT>
@@ -374,19 +392,34 @@ __device__ __forceinline__ void walk_stage(
   const float* max64 = max8 + skip_blocks(n_nodes, 3);
   const float* max512 = max64 + skip_blocks(n_nodes, 6);
   bool done = false;
-  int32_t j = 0;
 #pragma unroll 1
-  for (; j < n_nodes && j < kPlainWalk; ++j)
-    if (visit(j < head ? lhead[j] : list[j])) {
+  for (int32_t j = 0; j < head; ++j)
+    if (visit(lhead[j])) {
       done = true;
       break;
     }
-  while (!done && j < n_nodes) {   // skip blocks whose largest headroom admits nothing
-    if ((j & 511) == 0 && !(need <= (double)max512[j >> 9])) { j += 512; continue; }
-    if ((j & 63) == 0 && !(need <= (double)max64[j >> 6])) { j += 64; continue; }
-    if ((j & 7) == 0 && !(need <= (double)max8[j >> 3])) { j += 8; continue; }
-    done = visit(list[j]);
-    ++j;
+  // Past the staged head, in list order, only the entries of blocks whose largest headroom admits
+  // the stage: the eight maxima below a block, and the eight entries of the smallest blocks, are read
+  // together, so that a stage that few nodes admit waits for a handful of reads rather than for one
+  // per block. (The head is the first block of eight.)
+  const int n8 = skip_blocks(n_nodes, 3), n64 = skip_blocks(n_nodes, 6), n512 = skip_blocks(n_nodes, 9);
+  for (int g = 0; g < n512 && !done; ++g) {
+    if (g > 0 && !(need <= (double)max512[g])) continue;
+    for (uint32_t m64 = admitting(max64, g, n64, need); m64 && !done; m64 &= m64 - 1) {
+      const int b64 = 8 * g + __ffs(m64) - 1;
+      uint32_t m8 = admitting(max8, b64, n8, need);
+      if (b64 == 0) m8 &= ~1u;
+      for (; m8 && !done; m8 &= m8 - 1) {
+        const int first = 64 * b64 + 8 * (__ffs(m8) - 1);
+        NodeEntry e[8];
+        const int count = min(8, n_nodes - first);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) e[u] = list[first + min(u, count - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (u < count && !done) done = visit(e[u]);
+      }
+    }
   }
   int32_t outn[KT];
   float outs[KT];
@@ -438,9 +471,14 @@ size_t sorted_lists_bytes(int32_t n_models, int32_t n_nodes) {
 
 bool sorted_possible(int32_t n_nodes) { return n_nodes <= kSortMax; }
 
-// the scan wins when there are too few stages to amortise the per-model sorts
-bool prefer_sorted(int64_t n, int32_t n_models, int32_t n_nodes) {
-  return sorted_possible(n_nodes) && n >= 4 * (int64_t)n_models;
+// The scan is one launch and reads every node, the sorted route two launches of which the sort takes 4
+// to 21 us whatever the batch. Best node alone: the scan takes 4.1 us for 16,384 x 64 pairs, 6.1 for
+// 16,384 x 256, 8.7 for 16,384 x 512 and 7.3 for 4,096 x 1,024, the sorted route 9.5, 9.6, 10.3
+// and 12.4; at 2^24 pairs they are 12.5 / 10.1 (64 nodes) and 12.8 / 9.8 (256). Lists of several
+// nodes: merging the lanes' lists makes the scan as slow as the sorts (9.8 against 11.1 us at 256 x 64,
+// 16.8 against 11.4 at 4,096 x 256), so only batches too small for the sorts take it.
+bool prefer_sorted(int64_t n, int32_t n_models, int32_t n_nodes, int32_t k) {
+  return sorted_possible(n_nodes) && n >= 4 * (int64_t)n_models && (k > 1 || n * n_nodes > (int64_t)1 << 23);
 }
 
 }  // namespace
@@ -508,7 +546,7 @@ maestro_status launch_route(int64_t n, const int32_t* model_id, const float* pre
   bool sorted;
   if (algo == MAESTRO_ROUTE_SCAN) sorted = false;
   else if (algo == MAESTRO_ROUTE_SORTED) sorted = true;
-  else sorted = prefer_sorted(n, n_models, n_nodes);
+  else sorted = prefer_sorted(n, n_models, n_nodes, k);
   if (sorted) {
     if (!sorted_possible(n_nodes)) return MAESTRO_ERR_UNSUPPORTED;
     if (!workspace || workspace_bytes < sorted_lists_bytes(n_models, n_nodes)) return MAESTRO_ERR_WORKSPACE;
