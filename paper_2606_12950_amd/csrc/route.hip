@@ -174,7 +174,7 @@ struct __align__(16) NodeEntry {          // 16 bytes: one node in a model's rea
 // one dependent read after another, so the eight maxima of a block, and the eight entries of an
 // admitting smallest block, are read together: with 59% of 262,144 x 4,096 pairs infeasible (64
 // models, 4 nodes a stage) the walk takes 34 us, against 64 when one maximum or entry was read at a
-// time from the 33rd entry on (9.26 ms with no tables at all); the whole call 54.8 against 85 us.
+// time from the 33rd entry on (9.26 ms with no tables at all); the whole call 49 against 85 us.
 __host__ __device__ constexpr int32_t skip_blocks(int32_t n_nodes, int shift) {
   return (n_nodes + (1 << shift) - 1) >> shift;
 }
@@ -182,30 +182,160 @@ __host__ __device__ constexpr int64_t skip_per_model(int32_t n_nodes) {
   return (int64_t)skip_blocks(n_nodes, 3) + skip_blocks(n_nodes, 6) + skip_blocks(n_nodes, 9);
 }
 
-// One workgroup per model puts every node in (ready time, node index) order: a stable LSD radix
-// sort of the 32-bit order-preserving image of the ready time (float_key) in four 8-bit passes,
-// starting from index order, so equal ready times keep increasing indices. Wavefront w holds
-// positions [64 IPT w, 64 IPT (w + 1)), item j the 64 positions from 64 (IPT w + j). There are
-// `padded` positions (a power of two, 256 .. 8192, with 256 to 1024 threads); those past the last
-// node hold all-ones keys, which a stable pass keeps behind every real key. Each pass ranks a
-// wavefront's keys digit by digit with ballots (wave multisplit, in position order), scans the
-// per-wavefront digit counts (digit-major, wavefront-minor; one thread per digit) and places keys
-// and indices at their new positions in LDS: five barriers per pass. A bitonic network over the
-// 64-bit keys (ready, index), with in-register and cross-lane stages and a barrier per cross-
-// wavefront stage, took 35 us on 64 models x 4,096 nodes against 20 us for this sort (calls back
-// to back, one GPU); taking the digit-count loads of the scan out of its loop (21.3 us), a scan
-// spread over all threads plus one wavefront (21.5 us) and 512 threads of 8 keys (23.1 us) were
-// slower. LDS: `padded` keys and indices (dynamic), 16 x 256 digit counts.
+// One workgroup per model puts every node in (ready time, node index) order. There are `padded`
+// positions (a power of two, 256 .. 8192, with 256 to 1024 threads); wavefront w holds positions
+// [64 IPT w, 64 IPT (w + 1)), item j the 64 positions from 64 (IPT w + j).
+//
+// Usual ready times: four buckets a thread of equal width from the smallest one on (the bucket
+// number never falls as the ready time rises, whatever the rounding), counted with LDS atomics; a
+// scan gives each bucket its place, and within its bucket a node's place is the number of smaller
+// (key, index) pairs there: six barriers in all. Ready times that are not finite, or crowd more
+// than kBucketMost nodes into one bucket, take a stable LSD radix sort of the 32-bit order-
+// preserving image of the ready time (float_key) in four 8-bit passes instead, starting from index order, so equal ready times keep
+// increasing indices; positions past the last node hold all-ones keys, which a stable pass keeps
+// behind every real key. Each pass ranks a wavefront's keys digit by digit with ballots (wave
+// multisplit, in position order), scans the per-wavefront digit counts (digit-major, wavefront-
+// minor; one thread per digit) and places keys and indices at their new positions in LDS: five
+// barriers per pass.
+// Both wait mostly for LDS and barriers, one workgroup a model. Measured (us, 64 models, buckets /
+// radix): 64 nodes 5.0 / 7.0, 512 nodes 6.0 / 7.8, 1,024 nodes 7.5 / 9.9, 4,096 nodes 14.2 / 21.3,
+// 8,192 nodes 24.9 / 37.8. Where a bucket overflows, the buckets' part of the time is lost: eight
+// distinct ready times on 512 nodes 9.4 against 7.7 with the radix passes alone, on 4,096 nodes
+// 24.1 against 20.2; hence the equal smallest and largest ready times, and outliers, get their own
+// treatment (1.4 us at 4,096 nodes). Not kept: twice the buckets (no change at 4,096 nodes), and a
+// thread's nodes compared round by round together (13.5 against 12.4).
+// LDS: `padded` (key, index) pairs (dynamic), 16 KB of counts.
 constexpr int kSortWaves = 16;
 constexpr int kSortBuckets = 256;
+constexpr uint32_t kBucketMost = 32;
+
+// Both outcomes are workgroup-uniform; starts with LDS that nobody reads or writes any more, ends
+// with a barrier. True: pair[0 .. n_nodes-1] holds (key, index) in order. False: LDS is free again.
+template <int IPT>
+__device__ __forceinline__ bool bucket_sort(const uint32_t (&key)[IPT], const uint32_t (&idx)[IPT], int32_t n_nodes,
+                                            uint64_t* __restrict__ pair, uint32_t* __restrict__ count) {
+  __shared__ uint32_t s_low[kSortWaves], s_high[kSortWaves], s_sum[kSortWaves], s_ends[kSortWaves], s_full;
+  const int t = threadIdx.x, wave = t >> 6, lane = t & 63, n_waves = blockDim.x >> 6;
+  uint4* own = reinterpret_cast<uint4*>(count) + t;      // four buckets a thread
+  *own = make_uint4(0u, 0u, 0u, 0u);
+  uint32_t low = 0xFFFFFFFFu, high = 0u;
+#pragma unroll
+  for (int j = 0; j < IPT; ++j)
+    if ((int)idx[j] < n_nodes) {
+      low = min(low, key[j]);
+      high = max(high, key[j]);
+    }
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    low = min(low, __shfl_xor(low, off));
+    high = max(high, __shfl_xor(high, off));
+  }
+  if (lane == 0) {
+    s_low[wave] = low;
+    s_high[wave] = high;
+  }
+  if (t == 0) s_full = 0u;
+  __syncthreads();
+  // the buckets end at the second largest of the wavefronts' largest keys, so that far outliers in
+  // one wavefront share the last bucket instead of leaving the others in the first
+  uint32_t second = 0u;
+  high = 0u;
+#pragma unroll
+  for (int w = 0; w < kSortWaves; ++w) {                 // reads in flight together
+    const uint32_t l = s_low[w], h = s_high[w];
+    if (w < n_waves) {
+      low = min(low, l);
+      second = max(second, min(high, h));
+      high = max(high, h);
+    }
+  }
+  const uint32_t edge = n_nodes > 3 * 64 * IPT ? second : high;
+  const float lo = key_float(low), span = key_float(edge > low ? edge : high) - lo;
+  const int last = 4 * (int)blockDim.x - 1;
+  const float scale = (float)last / span;
+  // infinite or NaN unless every ready time is finite
+  if (!(key_float(high) - lo < INFINITY) || (low != high && !(scale < INFINITY))) return false;
+  // Nodes with the smallest or the largest ready time (idle nodes' zeros) are not counted: their
+  // places are the first and the last ones, in index order.
+  const uint64_t lanes_below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  uint32_t bucket[IPT], arrived[IPT], n_low = 0u, n_high = 0u;
+  bool inner[IPT];
+#pragma unroll
+  for (int j = 0; j < IPT; ++j) {
+    const bool real = (int)idx[j] < n_nodes, is_low = real && key[j] == low,
+               is_high = real && key[j] == high && high != low;
+    const uint64_t lows = __ballot(is_low), highs = __ballot(is_high);
+    arrived[j] = is_low ? n_low + (uint32_t)__popcll(lows & lanes_below) : n_high + (uint32_t)__popcll(highs & lanes_below);
+    n_low += (uint32_t)__popcll(lows);
+    n_high += (uint32_t)__popcll(highs);
+    bucket[j] = 0u;
+    inner[j] = real && !is_low && !is_high;
+    if (inner[j]) {
+      bucket[j] = (uint32_t)fminf((key_float(key[j]) - lo) * scale, (float)last);
+      arrived[j] = atomicAdd(&count[bucket[j]], 1u);
+    }
+  }
+  if (lane == 0) s_ends[wave] = n_low | (n_high << 16);
+  __syncthreads();
+  const uint4 c = *own;
+  uint32_t incl = c.x + c.y + c.z + c.w;
+  const uint32_t mine = incl;
+  if (max(max(c.x, c.y), max(c.z, c.w)) > kBucketMost) s_full = 1u;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t v = __shfl_up(incl, off);
+    if (lane >= off) incl += v;
+  }
+  if (lane == 63) s_sum[wave] = incl;
+  __syncthreads();
+  if (s_full != 0u) {
+    __syncthreads();                     // read by all before the counts are used again
+    return false;
+  }
+  uint32_t ends = 0u, ends_before = 0u, first = incl - mine;
+#pragma unroll
+  for (int w = 0; w < kSortWaves; ++w) {
+    const uint32_t e = s_ends[w], f = s_sum[w];
+    ends_before += w < wave ? e : 0u;
+    ends += w < n_waves ? e : 0u;
+    first += w < wave ? f : 0u;
+  }
+  first += ends & 0xFFFFu;
+  const uint32_t inner_end = (uint32_t)n_nodes - (ends >> 16);
+  *own = make_uint4(first, first + c.x, first + c.x + c.y, first + c.x + c.y + c.z);
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < IPT; ++j)
+    if (inner[j]) pair[count[bucket[j]] + arrived[j]] = ((uint64_t)key[j] << 32) | idx[j];
+  __syncthreads();
+  uint32_t place[IPT];
+#pragma unroll
+  for (int j = 0; j < IPT; ++j) {
+    place[j] = arrived[j] + (key[j] == low ? ends_before & 0xFFFFu : inner_end + (ends_before >> 16));
+    if (inner[j]) {
+      const uint64_t self = ((uint64_t)key[j] << 32) | idx[j];
+      const uint32_t begin = count[bucket[j]];
+      const uint32_t end = (int)bucket[j] < last ? count[bucket[j] + 1] : inner_end;
+      place[j] = begin;
+      if (end - begin > 1u)
+        for (uint32_t u = begin; u < end; ++u) place[j] += pair[u] < self ? 1u : 0u;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < IPT; ++j)
+    if ((int)idx[j] < n_nodes) pair[place[j]] = ((uint64_t)key[j] << 32) | idx[j];
+  __syncthreads();
+  return true;
+}
 
 template <int IPT>
 __global__ __launch_bounds__(1024) void sort_nodes_kernel(
     int32_t n_nodes, int32_t padded, int32_t n_models, const float* __restrict__ queue_s,
     const float* __restrict__ cold_s, const uint64_t* __restrict__ resident_mask,
     const float* __restrict__ act_matrix, const double* __restrict__ free_bytes, NodeEntry* __restrict__ lists) {
-  extern __shared__ uint32_t s_sort[];                  // [padded] keys, then [padded] indices
-  __shared__ uint32_t wcount[kSortWaves][kSortBuckets];
+  extern __shared__ __attribute__((aligned(16))) uint32_t s_sort[];   // [padded] pairs, or keys, then indices
+  __shared__ __attribute__((aligned(16))) uint32_t wcount[kSortWaves][kSortBuckets];
   __shared__ uint32_t dbase[kSortBuckets];
   __shared__ uint32_t wsum[kSortBuckets / 64];
   uint32_t* s_key = s_sort;
@@ -231,67 +361,79 @@ __global__ __launch_bounds__(1024) void sort_nodes_kernel(
       key[j] = 0xFFFFFFFFu;               // padding sorts behind every real key
     }
   }
-  const uint64_t lanes_below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-#pragma unroll 1
-  for (int shift = 0; shift < 32; shift += 8) {
-#pragma unroll
-    for (int i = lane; i < kSortBuckets; i += 64) wcount[wave][i] = 0;
-    // rank among this wavefront's keys of the same digit, in position order (the wavefront's
-    // own LDS accesses stay in program order)
-    uint32_t dig[IPT], rank[IPT];
-#pragma unroll
-    for (int j = 0; j < IPT; ++j) {
-      const uint32_t d = (key[j] >> shift) & (kSortBuckets - 1);
-      uint64_t same = ~0ull;
-#pragma unroll
-      for (int b = 0; b < 8; ++b) {
-        const bool bit = (d >> b) & 1u;
-        const uint64_t ones = __ballot(bit);
-        same &= bit ? ones : ~ones;
-      }
-      const uint32_t before = wcount[wave][d];
-      dig[j] = d;
-      rank[j] = before + (uint32_t)__popcll(same & lanes_below);
-      if ((same & lanes_below) == 0ull) wcount[wave][d] = before + (uint32_t)__popcll(same);   // first lane of the digit
-    }
-    __syncthreads();
-    // digit d's wavefront offsets (in place) and total; then the exclusive scan of the totals
-    uint32_t tot = 0, incl = 0;
-    if (t < kSortBuckets) {
-      for (int w = 0; w < n_waves; ++w) {
-        const uint32_t c = wcount[w][t];
-        wcount[w][t] = tot;
-        tot += c;
-      }
-      incl = tot;
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t v = __shfl_up(incl, off);
-        if (lane >= off) incl += v;
-      }
-      if (lane == 63) wsum[wave] = incl;
-    }
-    __syncthreads();
-    if (t < kSortBuckets) {
-      uint32_t add = 0;
-      for (int w = 0; w < wave; ++w) add += wsum[w];
-      dbase[t] = add + incl - tot;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < IPT; ++j) {
-      const uint32_t pos = dbase[dig[j]] + wcount[wave][dig[j]] + rank[j];
-      s_key[pos] = key[j];
-      s_idx[pos] = idx[j];
-    }
-    __syncthreads();
+  uint64_t* pair = reinterpret_cast<uint64_t*>(s_sort);
+  if (bucket_sort<IPT>(key, idx, n_nodes, pair, &wcount[0][0])) {
 #pragma unroll
     for (int j = 0; j < IPT; ++j) {
       const int p = (IPT * wave + j) * 64 + lane;
-      key[j] = s_key[p];
-      idx[j] = s_idx[p];
+      if (p < n_nodes) {
+        key[j] = (uint32_t)(pair[p] >> 32);
+        idx[j] = (uint32_t)pair[p];
+      }
     }
-    __syncthreads();   // every thread has its keys and the counts are read before the next pass
+  } else {
+    const uint64_t lanes_below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+#pragma unroll 1
+    for (int shift = 0; shift < 32; shift += 8) {
+#pragma unroll
+      for (int i = lane; i < kSortBuckets; i += 64) wcount[wave][i] = 0;
+      // rank among this wavefront's keys of the same digit, in position order (the wavefront's
+      // own LDS accesses stay in program order)
+      uint32_t dig[IPT], rank[IPT];
+#pragma unroll
+      for (int j = 0; j < IPT; ++j) {
+        const uint32_t d = (key[j] >> shift) & (kSortBuckets - 1);
+        uint64_t same = ~0ull;
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+          const bool bit = (d >> b) & 1u;
+          const uint64_t ones = __ballot(bit);
+          same &= bit ? ones : ~ones;
+        }
+        const uint32_t before = wcount[wave][d];
+        dig[j] = d;
+        rank[j] = before + (uint32_t)__popcll(same & lanes_below);
+        if ((same & lanes_below) == 0ull) wcount[wave][d] = before + (uint32_t)__popcll(same);   // first lane of the digit
+      }
+      __syncthreads();
+      // digit d's wavefront offsets (in place) and total; then the exclusive scan of the totals
+      uint32_t tot = 0, incl = 0;
+      if (t < kSortBuckets) {
+        for (int w = 0; w < n_waves; ++w) {
+          const uint32_t c = wcount[w][t];
+          wcount[w][t] = tot;
+          tot += c;
+        }
+        incl = tot;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+          const uint32_t v = __shfl_up(incl, off);
+          if (lane >= off) incl += v;
+        }
+        if (lane == 63) wsum[wave] = incl;
+      }
+      __syncthreads();
+      if (t < kSortBuckets) {
+        uint32_t add = 0;
+        for (int w = 0; w < wave; ++w) add += wsum[w];
+        dbase[t] = add + incl - tot;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < IPT; ++j) {
+        const uint32_t pos = dbase[dig[j]] + wcount[wave][dig[j]] + rank[j];
+        s_key[pos] = key[j];
+        s_idx[pos] = idx[j];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < IPT; ++j) {
+        const int p = (IPT * wave + j) * 64 + lane;
+        key[j] = s_key[p];
+        idx[j] = s_idx[p];
+      }
+      __syncthreads();   // every thread has its keys and the counts are read before the next pass
+    }
   }
   NodeEntry* out = lists + (size_t)m * n_nodes;
   float* max8 = reinterpret_cast<float*>(lists + (size_t)n_models * n_nodes) + (size_t)m * skip_per_model(n_nodes);
@@ -471,12 +613,13 @@ size_t sorted_lists_bytes(int32_t n_models, int32_t n_nodes) {
 
 bool sorted_possible(int32_t n_nodes) { return n_nodes <= kSortMax; }
 
-// The scan is one launch and reads every node, the sorted route two launches of which the sort takes 4
-// to 21 us whatever the batch. Best node alone: the scan takes 4.1 us for 16,384 x 64 pairs, 6.1 for
-// 16,384 x 256, 8.7 for 16,384 x 512 and 7.3 for 4,096 x 1,024, the sorted route 9.5, 9.6, 10.3
-// and 12.4; at 2^24 pairs they are 12.5 / 10.1 (64 nodes) and 12.8 / 9.8 (256). Lists of several
-// nodes: merging the lanes' lists makes the scan as slow as the sorts (9.8 against 11.1 us at 256 x 64,
-// 16.8 against 11.4 at 4,096 x 256), so only batches too small for the sorts take it.
+// The scan is one launch and reads every node, the sorted route two launches of which the sort takes
+// 4 to 23 us whatever the batch. Best node alone: the scan takes 4.2 us for 16,384 x 64 pairs, 6.0
+// for 16,384 x 256, 7.3 for 4,096 x 1,024 and 8.7 for 16,384 x 512, however contended the nodes
+// are; the sorted route 7.4 .. 9.1 there, 12.6 .. 15 on contended nodes. At 2^24 pairs they are 12.5
+// / 7.9 (64 nodes) and 12.8 / 7.5 (256). Lists of several nodes: merging the lanes' lists makes the scan
+// as slow as the sorts (9.8 against 8.5 us at 256 x 64, 16.8 against 9.1 at 4,096 x 256), so only
+// batches too small for the sorts take it.
 bool prefer_sorted(int64_t n, int32_t n_models, int32_t n_nodes, int32_t k) {
   return sorted_possible(n_nodes) && n >= 4 * (int64_t)n_models && (k > 1 || n * n_nodes > (int64_t)1 << 23);
 }
