@@ -27,6 +27,7 @@
 #include <atomic>
 #include <mutex>
 
+#include "bucket_sort.h"
 #include "internal.h"
 
 // Scratch of maestro_prioritize_noalloc: the radix key/value buffers and count tables of the
@@ -598,25 +599,32 @@ __global__ __launch_bounds__(kTile) void radix_scatter_kernel(
 }
 
 // The whole call in one workgroup, for up to ITEMS * kTile workflows: chain sums and keys as in the
-// chain kernel (one 1,024-workflow tile after the other), long chains by all threads, and the radix
-// sort with keys and indices in LDS. Nine launches, each a few microseconds of latency over a batch
-// this small, took 32 us a call for 300 workflows against 12, and 36 for 4,096 against 33 (where
-// sixteen wavefronts ranking four keys a lane take as long as the launches; beyond, tiles of their own
-// are faster).
+// chain kernel (one 1,024-workflow tile after the other), long chains by all threads, and the sort
+// in LDS: buckets (bucket_sort.h), or four radix passes where many slacks are equal. Nine launches,
+// each a few microseconds of latency over a batch this small, took 32 us a call for 300 workflows, 35
+// for 2,048 and 36 for 4,096; one workgroup takes 9, 15 and 26 with the buckets, 12, 21 and 35.6
+// where twenty distinct slacks overflow them (their attempt included: 12, 19 and 33 without). From
+// 4,097 on, tiles of their own are faster.
+struct SlackAbove {
+  __device__ __forceinline__ float operator()(uint32_t key, uint32_t low) const { return (float)(key - low); }
+};
+
 template <int ITEMS>
 __global__ __launch_bounds__(kTile) void small_batch_kernel(
     int32_t n_workflows, const int64_t* __restrict__ chain_offset, const float* __restrict__ stage_latency_s,
     const int32_t* __restrict__ cursor, const int64_t* __restrict__ deadline_us, int64_t now_us,
     int64_t* __restrict__ remaining_us, int32_t* __restrict__ slack_key, int32_t* __restrict__ order) {
   __shared__ int64_t stage_us[kStageCap];
-  __shared__ uint32_t wcount[kWaves][kBuckets];
+  __shared__ __attribute__((aligned(16))) uint32_t wcount[kWaves][kBuckets];
   __shared__ uint32_t lbase[kBuckets];
   __shared__ uint32_t wsum[kBuckets / 64];
   __shared__ int64_t wtot[kWaves];
   __shared__ int64_t s_head_rem;
   __shared__ int32_t s_long[kTile];
   __shared__ int32_t s_n_long;
-  __shared__ uint32_t s_key[ITEMS * kTile], s_val[ITEMS * kTile];
+  __shared__ uint64_t s_pair[ITEMS * kTile];           // or keys, then indices
+  uint32_t* s_key = reinterpret_cast<uint32_t*>(s_pair);
+  uint32_t* s_val = s_key + ITEMS * kTile;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   for (int tile = 0; tile * kTile < n_workflows; ++tile) {   // workgroup-uniform
     const int w = tile * kTile + tid;
@@ -675,6 +683,11 @@ __global__ __launch_bounds__(kTile) void small_batch_kernel(
   for (int i = 0; i < ITEMS; ++i) {
     val[i] = (uint32_t)(p0 + i * 64);
     key[i] = p0 + i * 64 < tiles ? s_key[p0 + i * 64] : 0xFFFFFFFFu;
+  }
+  __syncthreads();                         // the keys are read before the pairs take their place
+  if (bucket_sort<ITEMS>(key, val, n_workflows, s_pair, &wcount[0][0], SlackAbove())) {
+    for (int p = tid; p < n_workflows; p += kTile) order[p] = (int32_t)(uint32_t)s_pair[p];
+    return;
   }
   const uint64_t lanes_below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 #pragma unroll 1

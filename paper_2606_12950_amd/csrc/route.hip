@@ -25,6 +25,7 @@
 // intrinsics, so nothing is fused or reassociated.
 #include <type_traits>
 
+#include "bucket_sort.h"
 #include "internal.h"
 #include "select.h"
 
@@ -186,12 +187,9 @@ __host__ __device__ constexpr int64_t skip_per_model(int32_t n_nodes) {
 // positions (a power of two, 256 .. 8192, with 256 to 1024 threads); wavefront w holds positions
 // [64 IPT w, 64 IPT (w + 1)), item j the 64 positions from 64 (IPT w + j).
 //
-// Usual ready times: four buckets a thread of equal width from the smallest one on (the bucket
-// number never falls as the ready time rises, whatever the rounding), counted with LDS atomics; a
-// scan gives each bucket its place, and within its bucket a node's place is the number of smaller
-// (key, index) pairs there: six barriers in all. Ready times that are not finite, or crowd more
-// than kBucketMost nodes into one bucket, take a stable LSD radix sort of the 32-bit order-
-// preserving image of the ready time (float_key) in four 8-bit passes instead, starting from index order, so equal ready times keep
+// Usual ready times go to buckets (bucket_sort.h). Those that are not finite, or crowd into few
+// buckets, take a stable LSD radix sort of the 32-bit order-preserving image of the ready time
+// (float_key) in four 8-bit passes instead, starting from index order, so equal ready times keep
 // increasing indices; positions past the last node hold all-ones keys, which a stable pass keeps
 // behind every real key. Each pass ranks a wavefront's keys digit by digit with ballots (wave
 // multisplit, in position order), scans the per-wavefront digit counts (digit-major, wavefront-
@@ -201,133 +199,15 @@ __host__ __device__ constexpr int64_t skip_per_model(int32_t n_nodes) {
 // radix): 64 nodes 5.0 / 7.0, 512 nodes 6.0 / 7.8, 1,024 nodes 7.5 / 9.9, 4,096 nodes 14.2 / 21.3,
 // 8,192 nodes 24.9 / 37.8. Where a bucket overflows, the buckets' part of the time is lost: eight
 // distinct ready times on 512 nodes 9.4 against 7.7 with the radix passes alone, on 4,096 nodes
-// 24.1 against 20.2; hence the equal smallest and largest ready times, and outliers, get their own
-// treatment (1.4 us at 4,096 nodes). Not kept: twice the buckets (no change at 4,096 nodes), and a
-// thread's nodes compared round by round together (13.5 against 12.4).
+// 24.1 against 20.2.
 // LDS: `padded` (key, index) pairs (dynamic), 16 KB of counts.
-constexpr int kSortWaves = 16;
+constexpr int kSortWaves = kBucketWaves;
 constexpr int kSortBuckets = 256;
-constexpr uint32_t kBucketMost = 32;
 
-// Both outcomes are workgroup-uniform; starts with LDS that nobody reads or writes any more, ends
-// with a barrier. True: pair[0 .. n_nodes-1] holds (key, index) in order. False: LDS is free again.
-template <int IPT>
-__device__ __forceinline__ bool bucket_sort(const uint32_t (&key)[IPT], const uint32_t (&idx)[IPT], int32_t n_nodes,
-                                            uint64_t* __restrict__ pair, uint32_t* __restrict__ count) {
-  __shared__ uint32_t s_low[kSortWaves], s_high[kSortWaves], s_sum[kSortWaves], s_ends[kSortWaves], s_full;
-  const int t = threadIdx.x, wave = t >> 6, lane = t & 63, n_waves = blockDim.x >> 6;
-  uint4* own = reinterpret_cast<uint4*>(count) + t;      // four buckets a thread
-  *own = make_uint4(0u, 0u, 0u, 0u);
-  uint32_t low = 0xFFFFFFFFu, high = 0u;
-#pragma unroll
-  for (int j = 0; j < IPT; ++j)
-    if ((int)idx[j] < n_nodes) {
-      low = min(low, key[j]);
-      high = max(high, key[j]);
-    }
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    low = min(low, __shfl_xor(low, off));
-    high = max(high, __shfl_xor(high, off));
-  }
-  if (lane == 0) {
-    s_low[wave] = low;
-    s_high[wave] = high;
-  }
-  if (t == 0) s_full = 0u;
-  __syncthreads();
-  // the buckets end at the second largest of the wavefronts' largest keys, so that far outliers in
-  // one wavefront share the last bucket instead of leaving the others in the first
-  uint32_t second = 0u;
-  high = 0u;
-#pragma unroll
-  for (int w = 0; w < kSortWaves; ++w) {                 // reads in flight together
-    const uint32_t l = s_low[w], h = s_high[w];
-    if (w < n_waves) {
-      low = min(low, l);
-      second = max(second, min(high, h));
-      high = max(high, h);
-    }
-  }
-  const uint32_t edge = n_nodes > 3 * 64 * IPT ? second : high;
-  const float lo = key_float(low), span = key_float(edge > low ? edge : high) - lo;
-  const int last = 4 * (int)blockDim.x - 1;
-  const float scale = (float)last / span;
-  // infinite or NaN unless every ready time is finite
-  if (!(key_float(high) - lo < INFINITY) || (low != high && !(scale < INFINITY))) return false;
-  // Nodes with the smallest or the largest ready time (idle nodes' zeros) are not counted: their
-  // places are the first and the last ones, in index order.
-  const uint64_t lanes_below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  uint32_t bucket[IPT], arrived[IPT], n_low = 0u, n_high = 0u;
-  bool inner[IPT];
-#pragma unroll
-  for (int j = 0; j < IPT; ++j) {
-    const bool real = (int)idx[j] < n_nodes, is_low = real && key[j] == low,
-               is_high = real && key[j] == high && high != low;
-    const uint64_t lows = __ballot(is_low), highs = __ballot(is_high);
-    arrived[j] = is_low ? n_low + (uint32_t)__popcll(lows & lanes_below) : n_high + (uint32_t)__popcll(highs & lanes_below);
-    n_low += (uint32_t)__popcll(lows);
-    n_high += (uint32_t)__popcll(highs);
-    bucket[j] = 0u;
-    inner[j] = real && !is_low && !is_high;
-    if (inner[j]) {
-      bucket[j] = (uint32_t)fminf((key_float(key[j]) - lo) * scale, (float)last);
-      arrived[j] = atomicAdd(&count[bucket[j]], 1u);
-    }
-  }
-  if (lane == 0) s_ends[wave] = n_low | (n_high << 16);
-  __syncthreads();
-  const uint4 c = *own;
-  uint32_t incl = c.x + c.y + c.z + c.w;
-  const uint32_t mine = incl;
-  if (max(max(c.x, c.y), max(c.z, c.w)) > kBucketMost) s_full = 1u;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t v = __shfl_up(incl, off);
-    if (lane >= off) incl += v;
-  }
-  if (lane == 63) s_sum[wave] = incl;
-  __syncthreads();
-  if (s_full != 0u) {
-    __syncthreads();                     // read by all before the counts are used again
-    return false;
-  }
-  uint32_t ends = 0u, ends_before = 0u, first = incl - mine;
-#pragma unroll
-  for (int w = 0; w < kSortWaves; ++w) {
-    const uint32_t e = s_ends[w], f = s_sum[w];
-    ends_before += w < wave ? e : 0u;
-    ends += w < n_waves ? e : 0u;
-    first += w < wave ? f : 0u;
-  }
-  first += ends & 0xFFFFu;
-  const uint32_t inner_end = (uint32_t)n_nodes - (ends >> 16);
-  *own = make_uint4(first, first + c.x, first + c.x + c.y, first + c.x + c.y + c.z);
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < IPT; ++j)
-    if (inner[j]) pair[count[bucket[j]] + arrived[j]] = ((uint64_t)key[j] << 32) | idx[j];
-  __syncthreads();
-  uint32_t place[IPT];
-#pragma unroll
-  for (int j = 0; j < IPT; ++j) {
-    place[j] = arrived[j] + (key[j] == low ? ends_before & 0xFFFFu : inner_end + (ends_before >> 16));
-    if (inner[j]) {
-      const uint64_t self = ((uint64_t)key[j] << 32) | idx[j];
-      const uint32_t begin = count[bucket[j]];
-      const uint32_t end = (int)bucket[j] < last ? count[bucket[j] + 1] : inner_end;
-      place[j] = begin;
-      if (end - begin > 1u)
-        for (uint32_t u = begin; u < end; ++u) place[j] += pair[u] < self ? 1u : 0u;
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < IPT; ++j)
-    if ((int)idx[j] < n_nodes) pair[place[j]] = ((uint64_t)key[j] << 32) | idx[j];
-  __syncthreads();
-  return true;
-}
+// ready times above the smallest one
+struct ReadyAbove {
+  __device__ __forceinline__ float operator()(uint32_t key, uint32_t low) const { return key_float(key) - key_float(low); }
+};
 
 template <int IPT>
 __global__ __launch_bounds__(1024) void sort_nodes_kernel(
@@ -362,7 +242,7 @@ __global__ __launch_bounds__(1024) void sort_nodes_kernel(
     }
   }
   uint64_t* pair = reinterpret_cast<uint64_t*>(s_sort);
-  if (bucket_sort<IPT>(key, idx, n_nodes, pair, &wcount[0][0])) {
+  if (bucket_sort<IPT>(key, idx, n_nodes, pair, &wcount[0][0], ReadyAbove())) {
 #pragma unroll
     for (int j = 0; j < IPT; ++j) {
       const int p = (IPT * wave + j) * 64 + lane;

@@ -50,3 +50,33 @@ def test_long_chains_in_one_workgroup(W, long_len):
         lens = rng.integers(0, hi, W)
         lens[rng.integers(0, W, 3)] = long_len
         _check(rng, lens, cursor=hi == 2, remaining=W != 1000)
+
+
+@pytest.mark.parametrize("W", [1, 2, 64, 65, 300, 1024, 1025, 2049, 4096])
+@pytest.mark.parametrize("kind", ["spread", "equal", "two", "most", "crowded", "saturated", "outlier"])
+def test_one_workgroup_where_buckets_fill(W, kind):
+    # keys that spread, that the buckets' special cases take, just fill a bucket, or overflow one
+    rng = np.random.default_rng(W)
+    lens = rng.integers(0, 4, W)
+    off = np.zeros(W + 1, np.int64)
+    np.cumsum(lens, out=off[1:])
+    lat = np.zeros(int(off[-1]), np.float32)         # the deadline alone sets the slack
+    deadline = rng.integers(0, 2**31, W).astype(np.int64)
+    if kind == "equal":
+        deadline[:] = 123
+    elif kind == "two":
+        deadline = np.where(rng.random(W) < 0.5, 5, 9).astype(np.int64)
+    elif kind in ("most", "crowded"):
+        size = 32 if kind == "most" else 33
+        deadline = rng.permutation(np.arange(W) // size * 1_000_000).astype(np.int64)
+    elif kind == "saturated":
+        deadline[rng.random(W) < 0.4] = 2**62
+        deadline[rng.random(W) < 0.4] = -(2**62)
+    elif kind == "outlier":
+        deadline = rng.integers(0, 100_000, W).astype(np.int64)
+        deadline[W // 2] = 2**62
+    print(f"prioritize {kind} W={W}", flush=True)
+    _, key, order = M.prioritize(t(off), t(lat), t(deadline), 1_000)
+    torch.cuda.synchronize()
+    want = oracle.prioritize(off, lat, deadline, 1_000)
+    assert np.array_equal(key.cpu().numpy(), want[1]) and np.array_equal(order.cpu().numpy(), want[2])
