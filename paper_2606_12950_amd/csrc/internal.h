@@ -44,7 +44,7 @@ maestro_status launch_role_lengths(const maestro_predictor& p, const maestro_rol
                                    hipStream_t stream);
 size_t role_lengths_workspace_bytes(int64_t n, int32_t n_groups);
 // rows of one tile of the role regressors' grouped launch for the predictor's shape
-int32_t role_tile_rows(const maestro_predictor& p);
+int32_t role_tile_rows(const maestro_predictor& p, int64_t n);
 // whether the small-batch kernel takes the regressors of n stages (tiles of split_tile_rows(p))
 bool roles_split(const maestro_predictor& p, int64_t n);
 maestro_status launch_role_regressors(const maestro_predictor& p, int64_t n, const void* x, const float* coef,

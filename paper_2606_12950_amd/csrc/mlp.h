@@ -87,6 +87,14 @@ struct TwoPhaseArgs {
   int32_t n_knots;
   float max_len;
   float* p_tool;
+
+  TwoPhaseArgs from(int64_t row) const {   // the same for the rows from `row` on
+    TwoPhaseArgs t = *this;
+    if (t.role_id) t.role_id += row;
+    if (t.tool_avail) t.tool_avail += row;
+    if (t.p_tool) t.p_tool += row;
+    return t;
+  }
 };
 
 // The B = 32*BT outputs of each row read as heads (Sec. III-B): output 0 the tool-intent

@@ -930,6 +930,14 @@ constexpr int kMidGroups = 2;
 // than that kernel's one (20,000 rows: 41 against 35 us; 16,384 rows of the wide network 71 against 56).
 int64_t split_rows(const maestro_predictor& p, int cus) { return (int64_t)cus * split_tile_rows(p); }
 
+// Whether the 512-wide network's tiles are of one row group, for the rows past the last whole round of
+// two-group tiles (all of a batch that fills less than one): up to one such tile per compute unit.
+// 20,000 rows 23.9 against 35.2 us, 32,768 rows 26.4 against 36.5; 90,000 rows 64.9 against 71.0.
+// A second round would take as long as one round of the taller tiles.
+bool one_group(const maestro_predictor& p, int64_t rest, int cus) {
+  return p.dims[1] == 512 && rest > 0 && rest <= (int64_t)cus * kRowsPerBlock;
+}
+
 bool cu_count(int* cus) {
   int dev = 0;
   return hipGetDevice(&dev) == hipSuccess &&
@@ -954,17 +962,23 @@ maestro_status launch_mlp3(const maestro_predictor& p, int64_t n, const void* x,
                                                        pred_len, kv_bytes, tp, stream);
       if (st != MAESTRO_OK) return st;
     }
-    TwoPhaseArgs t = tp;
-    if (kTwoPhase) {
-      t.role_id += whole;
-      t.tool_avail += whole;
-      if (t.p_tool) t.p_tool += whole;
-    }
+    const TwoPhaseArgs t = tp.from(whole);
     return launch_predict_split(p, kTwoPhase ? &t : nullptr, rest, static_cast<const uint16_t*>(x) + whole * p.dims[0],
                                 prompt_len + whole, model_id + whole, kv_bytes_per_token, n_models, pred_len + whole,
                                 kv_bytes + whole, stream);
   }
-  const int64_t n_tiles = (n + tile_rows - 1) / tile_rows;
+  const bool half = one_group(p, rest, cus);
+  if (half && n > rest) {
+    const int64_t whole = n - rest;
+    const maestro_status st = launch_mlp3<kTwoPhase>(p, whole, x, prompt_len, model_id, kv_bytes_per_token, n_models,
+                                                     pred_len, kv_bytes, tp, stream);
+    if (st != MAESTRO_OK) return st;
+    return launch_mlp3<kTwoPhase>(p, rest, static_cast<const uint16_t*>(x) + whole * p.dims[0], prompt_len + whole,
+                                  model_id + whole, kv_bytes_per_token, n_models, pred_len + whole, kv_bytes + whole,
+                                  tp.from(whole), stream);
+  }
+  const int64_t rows = half ? kRowsPerBlock : tile_rows;
+  const int64_t n_tiles = (n + rows - 1) / rows;
   const dim3 pgrid((unsigned)(n_tiles < cus ? n_tiles : cus)), block(kThreads);
   auto args = [&](auto kernel) {
     kernel<<<pgrid, block, 0, stream>>>(
@@ -973,7 +987,8 @@ maestro_status launch_mlp3(const maestro_predictor& p, int64_t n, const void* x,
         p.bias[0], p.bias[1], p.bias[2], kTwoPhase ? nullptr : p.bin_centre, n, n_tiles, prompt_len, model_id,
         kv_bytes_per_token, n_models, pred_len, kv_bytes, tp, nullptr, nullptr, nullptr, nullptr, nullptr, 0.0f);
   };
-  if (mid) args(mlp3_bf16_kernel<256, 512, 512, 64, kMidGroups, kTwoPhase>);
+  if (half) args(mlp3_bf16_kernel<256, 512, 512, 64, 1, kTwoPhase>);
+  else if (mid) args(mlp3_bf16_kernel<256, 512, 512, 64, kMidGroups, kTwoPhase>);
   else args(mlp3_bf16_kernel<256, 1024, 1024, 64, 1, kTwoPhase>);
   return launch_status();
 }
@@ -1022,13 +1037,17 @@ maestro_status launch_role_regressors(const maestro_predictor& p, int64_t n, con
         p.bias[1], p.bias[2], nullptr, n, 0, prompt_p, model_p, kv_bytes_per_token, n_models, pred_len, kv_bytes,
         TwoPhaseArgs{}, tile_group, perm, p_bits, n_tiles, coef, max_len);
   };
-  if (p.dims[1] == 512) args(mlp3_bf16_kernel<256, 512, 512, 64, kMidGroups, false, true>);
-  else args(mlp3_bf16_kernel<256, 1024, 1024, 64, 1, false, true>);
+  if (p.dims[1] != 512) args(mlp3_bf16_kernel<256, 1024, 1024, 64, 1, false, true>);
+  else if (role_tile_rows(p, n) == kRowsPerBlock) args(mlp3_bf16_kernel<256, 512, 512, 64, 1, false, true>);
+  else args(mlp3_bf16_kernel<256, 512, 512, 64, kMidGroups, false, true>);
   return launch_status();
 }
 
-int32_t role_tile_rows(const maestro_predictor& p) {
-  return (p.dims[1] == 512 ? kMidGroups : 1) * kRowsPerBlock;
+// at most n rows in tiles: the shorter tiles of the 512-wide network as for a batch of n stages
+int32_t role_tile_rows(const maestro_predictor& p, int64_t n) {
+  int cus = 0;
+  const bool two = p.dims[1] == 512 && !(cu_count(&cus) && one_group(p, n, cus));
+  return (two ? kMidGroups : 1) * kRowsPerBlock;
 }
 
 bool roles_split(const maestro_predictor& p, int64_t n) {

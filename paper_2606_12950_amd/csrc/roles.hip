@@ -8,7 +8,7 @@
 //
 //   1. role_count_kernel   per 1024-stage block, the number of stages of each regressor;
 //   2. role_plan_kernel    one workgroup: each regressor's rows padded to whole tiles of the
-//                          predictor (128 rows, 256 for the 512-wide network's two row groups)
+//                          predictor (128 rows, 256 for two row groups of the 512-wide network)
 //                          and laid out one regressor after another; the start of every
 //                          (block, regressor) run, the regressor of every tile, the padding
 //                          rows (stage -1) and the tile count (up to 1,024 blocks by the scatter
@@ -250,7 +250,7 @@ maestro_status launch_role_lengths(const maestro_predictor& p, const maestro_rol
   // the small-batch kernel's tiles are shorter: it finds a tile's regressor from the regressors' first
   // tiles, since the per-tile table is sized for 128 rows a tile
   const bool split = roles_split(p, n);
-  const int32_t tile_rows = split ? split_tile_rows(p) : role_tile_rows(p);
+  const int32_t tile_rows = split ? split_tile_rows(p) : role_tile_rows(p, n);
   const int64_t tiles_max =
       split ? (n + (int64_t)r.n_regressors * (tile_rows - 1)) / tile_rows : (L.rows_max + tile_rows - 1) / tile_rows;
   const dim3 grid((unsigned)L.n_blocks), block(kBlock);

@@ -85,3 +85,42 @@ def test_small_role_batches_have_the_large_batch_bits(net, groups):
             assert torch.equal(got, ref[:m]), m
     b["role"].fill_(4 if groups == 1 else 3)   # no stage has a regressor: nothing is written
     assert (run(sizes[4])[0] == -1.0).all()
+
+
+def _one_group_sizes():
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    small, half, full = 64 * cus, 128 * cus, 256 * cus
+    return [small + 1, small + 129, half - 1, half, half + 1, full + small + 1, full + half, full + half + 1], 2 * full
+
+
+@pytest.mark.parametrize("form", [_bins, _heads])
+def test_one_row_group_has_the_bits_of_two(form):
+    # the 512-wide network's 128-row tiles, for the rows past the last whole round of 256-row ones
+    sizes, n = _one_group_sizes()
+    b = _batch("mid", n, 14)
+    want = form(b, n)
+    for m in sizes:
+        print(f"one group {form.__name__} n={m}", flush=True)
+        for got, ref in zip(form(b, m), want):
+            assert torch.equal(got.view(torch.uint8), ref[:m].contiguous().view(torch.uint8)), m
+
+
+@pytest.mark.parametrize("groups", [1, 3, 16])
+def test_one_row_group_role_tiles_have_the_bits_of_two(groups):
+    sizes, n = _one_group_sizes()
+    b = _batch("mid", n, 15)
+    w = _batch("mid", 1, 16, groups)
+    reg = torch.tensor([0, groups - 1, groups // 2, -1, 0, 0], device="cuda", dtype=torch.int32)
+    coef = torch.linspace(-2.0, 0.5, groups, device="cuda")
+    p = torch.rand(n, device="cuda")
+
+    def run(m):
+        length, kv = torch.full((m,), -1.0, device="cuda"), torch.full((m,), -1.0, device="cuda", dtype=torch.float64)
+        return M.predict_role_lengths(b["x"][:m], w["ws"], w["bs"], reg, coef, 1e5, b["prompt"][:m], b["model"][:m],
+                                      b["role"][:m], p[:m], b["alpha"], length, kv)
+
+    want = run(n)
+    for m in sizes[:5]:
+        print(f"one group roles groups={groups} n={m}", flush=True)
+        for got, ref in zip(run(m), want):
+            assert torch.equal(got, ref[:m]), m
