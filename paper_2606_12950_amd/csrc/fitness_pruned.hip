@@ -5,7 +5,7 @@
 // the fit falls with the headroom. So the nodes are put in ascending headroom, and for every
 // (class, source, model) the largest gamma prox - pen of each block of 8 and of 64 consecutive
 // nodes is tabulated: block maximum + (1 - gamma) min(1, R_need / smallest headroom) bounds the
-// fitness of every node of the block. A stage scores the block of the best bound first and
+// fitness of every node of the block. A stage scores the sub-blocks of the best bounds first and
 // then only the blocks whose bound reaches its k-th best score so far. The scores are the same
 // float32 expressions in the same order as in fitness_kernel, the lists are ordered by (score,
 // node index), and a block is skipped only when its bound, widened by more than every rounding
@@ -18,12 +18,18 @@
 //
 // Three launches: ranks of the headrooms and the sorted node records; the penalty, proximity and
 // bound tables; the stages.
-// What bounds it: scoring every pair costs 14 vector instructions a pair; here a lane reads
+// What bounds it: scoring every pair costs 14 vector instructions a pair; here a lane reads up to
 // M / 256 float4 of bounds, visits one to five sub-blocks of 8 nodes, and a wavefront waits for
-// the lane that visits most (6 .. 9), each visit two dependent rounds of divergent 16-byte reads.
+// the lane that visits most, each visit two dependent rounds of divergent 16-byte reads. On 512
+// nodes a wavefront takes 1,400 vector instructions (26 us of the kernel's 43 for 719,712 stages,
+// 38 of 64 lanes active); on 4,096 nodes 3,900 for its two rounds with plans, and the slowest
+// wavefront twice the average one's time.
 // Measured (one MI355X, whole call, against scoring every pair): 719,712 stages on 512 nodes, one
-// result, 53 against 139 us; 500,009 stages on 4,096 nodes with plans, four results, 105 against
-// 1,150 us.
+// result, 44 .. 49 against 139 us; 500,009 stages on 4,096 nodes with plans, four results, 69
+// against 1,150 us. The pass over the 64-node bounds of 4,096 nodes took half of all vector
+// instructions (7,200 a wavefront, 88 us) before it ended early. Slower or no faster: plan records
+// read eight at a time by the lanes and broadcast (no change), 80 registers for a sixth wavefront
+// per SIMD (51 against 43 us on 512 nodes).
 #include "fitness.h"
 #include "internal.h"
 #include "select.h"
@@ -31,7 +37,9 @@
 namespace maestro {
 namespace {
 
-constexpr int kThreads = 512;            // of the stage kernel: two workgroups per CU at 4,096 nodes
+// of the stage kernel: 512 where the LDS of 4,096 nodes admits two workgroups a CU, half that up to 1,024
+// nodes (registers admit four or five wavefronts a SIMD: 43 against 47 us on 512 nodes)
+constexpr int kThreads = 512;
 constexpr int kMaxNodes = 4096;          // one 64-bit mask of 64-node blocks; node records in LDS
 constexpr int kRecSteps = MAESTRO_PLAN_RECORD_STEPS;
 
@@ -41,14 +49,15 @@ struct __align__(16) SortedNode {
 
 // All sizes derive from the node count padded to whole 64-node blocks.
 struct Tables {
-  int32_t padded, row;                   // nodes and floats of a bound row: blocks of 64 (padded to four), then of 8
+  // nodes, and floats of a bound row: blocks of 64 (padded to four), of 8, then the largest of the 64s from each on
+  int32_t padded, row;
   size_t nodes, order, tr, prox, nd, gp, pen, bound, total;   // byte offsets
 };
 
 Tables tables_of(int32_t n_models, int32_t n_nodes, int32_t n_src, int32_t n_classes) {
   Tables t{};
   t.padded = (n_nodes + 63) & ~63;
-  t.row = (((t.padded >> 6) + 3) & ~3) + (t.padded >> 3);
+  t.row = 2 * (((t.padded >> 6) + 3) & ~3) + (t.padded >> 3);
   t.nodes = 0;
   t.order = t.nodes + (size_t)t.padded * sizeof(SortedNode);
   t.tr = t.order + (size_t)t.padded * sizeof(uint16_t);
@@ -135,12 +144,11 @@ __global__ __launch_bounds__(kRankThreads) void fitness_rank_kernel(int32_t n_no
     prox[(size_t)lane * padded + rank] = __fsub_rn(1.0f, norm01(rtt_ms[(size_t)lane * n_nodes + i], bounds[0], bounds[1]));
 }
 
-// One workgroup per (class, model) and 512 sorted nodes, eight consecutive nodes per thread: their
-// penalties (with plans lambda norm(T_ready) alone, the C_deg term being the pair's), the
-// proximity terms gamma (1 - norm(RTT)) of every source (written by model 0's workgroups), and
-// the bound rows of the class's (source, model) pairs. With plans the C_deg term is at least
+// One workgroup per (class, model), and from 513 nodes on per source, eight consecutive sorted nodes
+// per thread: their penalties (with plans lambda norm(T_ready) alone, the C_deg term being the
+// pair's), the proximity terms gamma (1 - norm(RTT)) (written by model 0's workgroups), and the
+// bound rows of the class's (source, model) pairs. With plans the C_deg term is at least
 // min(0, mu), since norm() lies in [0, 1].
-constexpr int kTableThreads = 64;
 __device__ __forceinline__ void load8(const float* __restrict__ p, float (&v)[8]) {
   *reinterpret_cast<float4*>(v) = *reinterpret_cast<const float4*>(p);
   *reinterpret_cast<float4*>(v + 4) = *reinterpret_cast<const float4*>(p + 4);
@@ -150,14 +158,18 @@ __device__ __forceinline__ void store8(float* __restrict__ p, const float (&v)[8
   *reinterpret_cast<float4*>(p + 4) = *reinterpret_cast<const float4*>(v + 4);
 }
 
+// Whether a stage's pass over the 64-node bounds ends early: it costs a visit of the stage's first
+// sub-blocks ahead of the pass, more than the pass itself over up to 16 blocks when one node is wanted.
+__host__ __device__ constexpr bool early_end(int32_t padded) { return padded > 1024; }
+
 template <bool kPlans>
-__global__ __launch_bounds__(kTableThreads) void fitness_tables_kernel(
+__global__ __launch_bounds__(kMaxNodes / 8) void fitness_tables_kernel(
     int32_t n_models, int32_t n_nodes, int32_t n_src, int32_t padded, int32_t row, const float* __restrict__ tr,
     const float* __restrict__ prox, const float* __restrict__ nd, const float* __restrict__ class_weights,
     float* __restrict__ gp, float* __restrict__ pen, float* __restrict__ bound) {
+  __shared__ float s_top[64];
   const int m = blockIdx.x, c = blockIdx.y;
-  const int p0 = (blockIdx.z * kTableThreads + threadIdx.x) * 8;
-  if (p0 >= padded) return;              // whole octets of lanes: padded is a multiple of 64
+  const int p0 = threadIdx.x * 8;        // blockDim.x is padded / 8
   const float gamma = class_weights[3 * c], lambda = class_weights[3 * c + 1], mu = class_weights[3 * c + 2];
   const float deg_floor = fminf(mu, 0.0f);
   float pn[8], low[8], t[8], d[8];
@@ -169,10 +181,9 @@ __global__ __launch_bounds__(kTableThreads) void fitness_tables_kernel(
     pn[u] = kPlans ? lt : __fadd_rn(lt, __fmul_rn(mu, d[u]));
     low[u] = p0 + u >= n_nodes ? INFINITY : kPlans ? lt + deg_floor : pn[u];   // padding: bound -inf
   }
-  store8(pen + (size_t)(c * n_models + m) * padded + p0, pn);
+  if (blockIdx.z == 0) store8(pen + (size_t)(c * n_models + m) * padded + p0, pn);
   const int blocks4 = ((padded >> 6) + 3) & ~3;
-#pragma unroll 4
-  for (int s = 0; s < n_src; ++s) {
+  for (int s = blockIdx.z; s < n_src; s += gridDim.z) {    // workgroup-uniform
     float g[8], top = -INFINITY;
     load8(prox + (size_t)s * padded + p0, g);
 #pragma unroll
@@ -187,6 +198,21 @@ __global__ __launch_bounds__(kTableThreads) void fitness_tables_kernel(
     top = fmaxf(top, __shfl_xor(top, 2));
     top = fmaxf(top, __shfl_xor(top, 4));
     if ((threadIdx.x & 7) == 0) r[p0 >> 6] = top;
+    if (early_end(padded)) {               // the largest entry of each block of 64 and those after it
+      if ((threadIdx.x & 7) == 0) s_top[p0 >> 6] = top;
+      __syncthreads();
+      if (threadIdx.x < 64) {              // a whole wavefront: padded exceeds 1,024
+        const int lane = threadIdx.x;
+        float v = lane < (padded >> 6) ? s_top[lane] : -INFINITY;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+          const float w = __shfl_down(v, off);
+          if (lane + off < 64) v = fmaxf(v, w);
+        }
+        if (lane < blocks4) r[blocks4 + (padded >> 3) + lane] = v;
+      }
+      __syncthreads();
+    }
   }
 }
 
@@ -196,7 +222,7 @@ __global__ __launch_bounds__(kTableThreads) void fitness_tables_kernel(
 // than 2^-21 of it).
 constexpr float kSlack = 1.9073486328125e-06f;
 
-// Stages in turn, one per lane, 512 lanes a workgroup; the sorted node records, their original
+// Stages in turn, one per lane; the sorted node records, their original
 // indices and the largest reciprocal of every block are staged in LDS once per workgroup.
 template <int KT, bool kPlans>
 __global__ __launch_bounds__(kThreads) void fitness_walk_kernel(
@@ -209,25 +235,28 @@ __global__ __launch_bounds__(kThreads) void fitness_walk_kernel(
     const float* __restrict__ bounds, double rho, int32_t k, int32_t* __restrict__ node_idx,
     float* __restrict__ fitness) {
   extern __shared__ __attribute__((aligned(16))) unsigned char s_raw[];
-  SortedNode* s_node = reinterpret_cast<SortedNode*>(s_raw);
-  float* s_r8 = reinterpret_cast<float*>(s_node + padded);        // [padded / 8]
+  double* s_free = reinterpret_cast<double*>(s_raw);
+  double* s_recip = s_free + padded;
+  float* s_r8 = reinterpret_cast<float*>(s_recip + padded);       // [padded / 8]
   float* s_r64 = s_r8 + (padded >> 3);                            // [padded / 64, to a multiple of four]
   const int blocks = padded >> 6, blocks4 = (blocks + 3) & ~3;
   uint16_t* s_order = reinterpret_cast<uint16_t*>(s_r64 + blocks4);
-  const int tid = threadIdx.x;
-  for (int i = tid; i < padded; i += kThreads) {
-    s_node[i] = nodes[i];
+  const int tid = threadIdx.x, threads = blockDim.x;
+  for (int i = tid; i < padded; i += threads) {
+    const SortedNode nd = nodes[i];
+    s_free[i] = nd.free;
+    s_recip[i] = nd.recip;
     s_order[i] = order[i];
   }
   __syncthreads();
   // the largest reciprocal of a block, rounded up; padding counts as 0
-  for (int b = tid; b < (padded >> 3); b += kThreads) {
+  for (int b = tid; b < (padded >> 3); b += threads) {
     double r = 0.0;
-    for (int u = 0; u < 8; ++u) r = fmax(r, s_node[8 * b + u].recip);
+    for (int u = 0; u < 8; ++u) r = fmax(r, s_recip[8 * b + u]);
     s_r8[b] = __double2float_ru(r);
   }
   __syncthreads();
-  for (int b = tid; b < blocks4; b += kThreads) {
+  for (int b = tid; b < blocks4; b += threads) {
     float r = 0.0f;
     if (b < blocks)
       for (int u = 0; u < 8; ++u) r = fmaxf(r, s_r8[8 * b + u]);
@@ -237,10 +266,10 @@ __global__ __launch_bounds__(kThreads) void fitness_walk_kernel(
   const float lo_d = bounds[4], hi_d = bounds[5];
   const float nd_fits = norm01(0.0f, lo_d, hi_d);   // normalised C_deg of a stage that fits
 
-  const int64_t step = (int64_t)gridDim.x * kThreads;
+  const int64_t step = (int64_t)gridDim.x * threads;
   const int64_t rounds = (n + step - 1) / step;      // workgroup-uniform: whole wavefronts vote below
   for (int64_t it = 0; it < rounds; ++it) {
-    const int64_t stage = it * step + (int64_t)blockIdx.x * kThreads + tid;
+    const int64_t stage = it * step + (int64_t)blockIdx.x * threads + tid;
     TopK<KT> best;                                   // keys are -fitness: the smallest key is the best node
     best.init();
     bool ok = false;
@@ -266,6 +295,7 @@ __global__ __launch_bounds__(kThreads) void fitness_walk_kernel(
     const float* pen_row = pen + (size_t)cm * padded;
     const float* b64 = bound + ((size_t)cs * n_models + m) * row;
     const float* b8 = b64 + blocks4;
+    const float* after = b8 + (padded >> 3);
     // bound of a block: fit_w * min(1, needf * largest reciprocal) + its table entry; a
     // negative demand with a negative fit weight has no such bound (every block is visited)
     const float needf = fmaxf((float)needd, 0.0f);
@@ -280,7 +310,7 @@ __global__ __launch_bounds__(kThreads) void fitness_walk_kernel(
       int lo = 0, hi = n_nodes;
       while (lo < hi) {
         const int mid = (lo + hi) >> 1;
-        if (s_node[mid].free < need) lo = mid + 1;
+        if (s_free[mid] < need) lo = mid + 1;
         else hi = mid;
       }
       start = lo;
@@ -308,8 +338,7 @@ __global__ __launch_bounds__(kThreads) void fitness_walk_kernel(
 #pragma unroll
           for (int u = 0; u < 8; ++u) {
             const int i = 8 * s + u;
-            const SortedNode nd = s_node[i];
-            const float fit = __double2float_rn(__dmul_rn(needd, nd.recip));
+            const float fit = __double2float_rn(__dmul_rn(needd, s_recip[i]));
             const float a = __fadd_rn(g[u], __fmul_rn(omg, fit));
             // with mu >= 0 the fitness is at most the score with C_deg normalised to 0
             const bool go = want && i < mine && !(mu >= 0.0f && -__fsub_rn(a, l[u]) > best.s[KT - 1]);
@@ -317,7 +346,7 @@ __global__ __launch_bounds__(kThreads) void fitness_walk_kernel(
             const int j = __builtin_amdgcn_readfirstlane((int)s_order[i]);
             const maestro_deg_plan* pl = plans + j;
             const int ne = pl->n_engines;
-            const double R = __dsub_rn(need, nd.free);
+            const double R = __dsub_rn(need, s_free[i]);
             int jp = 0;
 #pragma unroll
             for (int e = 0; e < kRecSteps; ++e) jp += pl->freed[e] < R ? 1 : 0;
@@ -343,45 +372,64 @@ __global__ __launch_bounds__(kThreads) void fitness_walk_kernel(
       }
     }
 
-    // ---- the nodes that admit the stage
+    // ---- the nodes that admit the stage: those from `start` on
+    const bool live = ok && start < n_nodes && need == need;
+    const uint32_t room = (uint32_t)(n_nodes - start);
     auto score8 = [&](int sub) {
       float g[8], l[8];
+      double r[8];
       load8(gp_row + 8 * sub, g);
       load8(pen_row + 8 * sub, l);
       const uint4 o = *reinterpret_cast<const uint4*>(s_order + 8 * sub);
       const uint32_t ow[4] = {o.x, o.y, o.z, o.w};
 #pragma unroll
+      for (int u = 0; u < 8; u += 2) {
+        const double2 d = *reinterpret_cast<const double2*>(s_recip + 8 * sub + u);
+        r[u] = d.x;
+        r[u + 1] = d.y;
+      }
+#pragma unroll
       for (int u = 0; u < 8; ++u) {
-        const SortedNode nd = s_node[8 * sub + u];
-        const float fit = __double2float_rn(__dmul_rn(needd, nd.recip));
+        const float fit = __double2float_rn(__dmul_rn(needd, r[u]));
         const float a = __fadd_rn(g[u], __fmul_rn(omg, fit));
         const float p = kPlans ? __fadd_rn(l[u], md) : l[u];
-        if (need <= nd.free) best.push_lex(-__fsub_rn(a, p), (int32_t)((ow[u >> 1] >> (16 * (u & 1))) & 0xFFFFu));
+        if ((uint32_t)(8 * sub + u - start) < room)
+          best.push_lex(-__fsub_rn(a, p), (int32_t)((ow[u >> 1] >> (16 * (u & 1))) & 0xFFFFu));
       }
     };
-    // bounds of the eight sub-blocks of a block; those before `start` admit nothing
+    // The nodes that just fit come first, since the fit falls from there on: the sub-block where they
+    // begin (and, for a list, the next one) gives a k-th best score that ends the pass over the bounds early.
+    int seen = start >> 3;                                  // sub-blocks before it are done
+    const bool ends_early = early_end(padded);
+    if (live && ends_early) {
+      score8(seen++);
+      if (KT > 1 && 8 * seen < padded) score8(seen++);
+    }
+    // bounds of the eight sub-blocks of a block; those before `seen` are done
     auto sub_bounds = [&](int blk, float (&ub)[8]) {
       float t[8], r[8];
       load8(b8 + 8 * blk, t);
       load8(s_r8 + 8 * blk, r);
 #pragma unroll
       for (int u = 0; u < 8; ++u)
-        ub[u] = 64 * blk + 8 * u + 7 < start ? -INFINITY : fmaf(fit_w, fminf(needf * r[u], 1.0f), t[u]);
+        ub[u] = 8 * blk + u < seen ? -INFINITY : fmaf(fit_w, fminf(needf * r[u], 1.0f), t[u]);
     };
     // One pass over the bounds of the 64-node blocks from the stage's first one on: the two blocks
     // of the best bounds, the third best bound, and a lower bound of the k-th best fitness -- past
     // the first block every node admits the stage, so the node that holds a block's table entry
     // scores at least that entry plus the smallest fit term less the most that its C_deg term adds.
-    const bool live = ok && start < n_nodes;
-    const int blk0 = live ? start >> 6 : blocks;
+    // The pass ends where the largest table entry of all further blocks, with the fit term of the
+    // next one (the largest of theirs), is below the k-th best score.
+    const int blk0 = start >> 6;
     float top = -INFINITY, second = -INFINITY, third = -INFINITY;
-    int arg = 0, arg2 = 0;
-    {
+    int arg = 0, arg2 = 0, end = blk0;
+    if (live) {
+      const float reach = floor_key();
       float low[KT];
 #pragma unroll
       for (int i = 0; i < KT; ++i) low[i] = -INFINITY;
-#pragma unroll 4
-      for (int q = 0; q < blocks4; q += 4) {
+      int q = blk0 & ~3;
+      do {
         const float4 t = *reinterpret_cast<const float4*>(b64 + q);
         const float4 r = *reinterpret_cast<const float4*>(s_r64 + q);
         const float tv[4] = {t.x, t.y, t.z, t.w}, rv[4] = {r.x, r.y, r.z, r.w};
@@ -403,7 +451,9 @@ __global__ __launch_bounds__(kThreads) void fitness_walk_kernel(
             low[i] = hi;
           }
         }
-      }
+        q += 4;
+      } while (q < blocks && !(ends_early && fmaf(fit_w, fminf(needf * s_r64[q], 1.0f), after[q]) < reach));
+      end = min(q, blocks);
       if (needd >= 0.0) known = low[KT - 1] - (fmaxf(-omg, 0.0f) + (kPlans ? md - fminf(mu, 0.0f) : 0.0f));
     }
     // The sub-blocks of those two blocks in descending order of their bounds while those reach the
@@ -434,10 +484,20 @@ __global__ __launch_bounds__(kThreads) void fitness_walk_kernel(
     if (__any(more)) {
       uint64_t rest = 0;
       auto bound64 = [&](int blk) { return fmaf(fit_w, fminf(needf * s_r64[blk], 1.0f), b64[blk]); };
-#pragma unroll 4
-      for (int blk = 0; blk < blocks; ++blk) {
-        const float v = bound64(blk);
-        if (more && blk >= blk0 && blk != arg && blk != arg2 && !(v < floor_key())) rest |= 1ull << blk;
+      if (more) {
+        const float reach = floor_key();
+#pragma unroll 2
+        for (int q = blk0 & ~3; q < end; q += 4) {
+          const float4 t = *reinterpret_cast<const float4*>(b64 + q);
+          const float4 r = *reinterpret_cast<const float4*>(s_r64 + q);
+          const float tv[4] = {t.x, t.y, t.z, t.w}, rv[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int blk = q + u;
+            const bool in = blk >= blk0 && blk < end && blk != arg && blk != arg2;
+            if (in && !(fmaf(fit_w, fminf(needf * rv[u], 1.0f), tv[u]) < reach)) rest |= 1ull << blk;
+          }
+        }
       }
       // taking the next block and scoring a sub-block are two steps of one loop, so that lanes at
       // different points of their lists share its iterations
@@ -481,7 +541,7 @@ __global__ __launch_bounds__(kThreads) void fitness_walk_kernel(
 }
 
 size_t walk_lds_bytes(int32_t padded) {
-  return (size_t)padded * (sizeof(SortedNode) + sizeof(uint16_t)) + (size_t)(padded / 8) * sizeof(float) +
+  return (size_t)padded * (2 * sizeof(double) + sizeof(uint16_t)) + (size_t)(padded / 8) * sizeof(float) +
          (size_t)(((padded >> 6) + 3) & ~3) * sizeof(float);
 }
 
@@ -533,17 +593,19 @@ maestro_status launch_route_fitness_pruned(int64_t n, const int32_t* model_id, c
   fitness_rank_kernel<<<dim3((unsigned)((t.padded + 15) / 16)), dim3(kRankThreads), 0, stream>>>(
       n_nodes, t.padded, n_models, n_src, free_bytes, queue_ms, act_ms, resident_mask, act_matrix,
       plans ? nullptr : deg_ms, rtt_ms, bounds, nodes, order, tr, prox, nd);
-  const dim3 tgrid((unsigned)n_models, (unsigned)n_classes, (unsigned)((t.padded / 8 + kTableThreads - 1) / kTableThreads));
+  const dim3 tgrid((unsigned)n_models, (unsigned)n_classes, (unsigned)(t.padded > 512 ? n_src : 1));
+  const dim3 tblock((unsigned)(t.padded / 8));
   if (plans)
-    fitness_tables_kernel<true><<<tgrid, dim3(kTableThreads), 0, stream>>>(n_models, n_nodes, n_src, t.padded, t.row, tr,
+    fitness_tables_kernel<true><<<tgrid, tblock, 0, stream>>>(n_models, n_nodes, n_src, t.padded, t.row, tr,
                                                                            prox, nd, class_weights, gp, pen, bound);
   else
-    fitness_tables_kernel<false><<<tgrid, dim3(kTableThreads), 0, stream>>>(n_models, n_nodes, n_src, t.padded, t.row, tr,
+    fitness_tables_kernel<false><<<tgrid, tblock, 0, stream>>>(n_models, n_nodes, n_src, t.padded, t.row, tr,
                                                                             prox, nd, class_weights, gp, pen, bound);
   const size_t lds = walk_lds_bytes(t.padded);
-  // One round of 512 stages per workgroup while the LDS staging is small, up to four (equal ones)
+  // One round of stages per workgroup while the LDS staging is small, up to four (equal ones)
   // at 4,096 nodes, where only two workgroups fit a CU and each stages 74 KB.
-  const int64_t want = (n + kThreads - 1) / kThreads, slots = 2 * (int64_t)cus;
+  const int threads = t.padded > 1024 ? kThreads : kThreads / 2;
+  const int64_t want = (n + threads - 1) / threads, slots = 2 * (int64_t)cus;
   const int64_t most_rounds = t.padded > 1024 ? t.padded / 1024 : 1;
   const int64_t fair = (want + slots - 1) / slots, rounds = fair < most_rounds ? fair : most_rounds;
   const dim3 grid((unsigned)((want + rounds - 1) / rounds));
@@ -552,7 +614,7 @@ maestro_status launch_route_fitness_pruned(int64_t n, const int32_t* model_id, c
     if (lds > 65536 && hipFuncSetAttribute(reinterpret_cast<const void*>(&fitness_walk_kernel<KT, PL>),               \
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)       \
       return MAESTRO_ERR_LAUNCH;                                                                                      \
-    fitness_walk_kernel<KT, PL><<<grid, dim3(kThreads), lds, stream>>>(                                               \
+    fitness_walk_kernel<KT, PL><<<grid, dim3(threads), lds, stream>>>(                                               \
         n, model_id, src_id, class_id, kv_bytes, n_models, n_nodes, n_src, n_classes, t.padded, t.row, nodes, order,  \
         gp, pen, bound, plans, plan_steps, class_weights, bounds, rho, k, node_idx, fitness);                         \
   } while (0)

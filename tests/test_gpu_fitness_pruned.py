@@ -80,7 +80,8 @@ ODD = [[0.25, 1, 1], [1.5, 0.5, 2.0], [-0.3, 1, 0.0], [0.4, -0.7, 1.0], [0.2, 1.
 
 @pytest.mark.parametrize("m,models,k,n_src,free_gb,kv_gb,rho", [
     (64, 8, 1, 5, 288.0, 60.0, 0.0), (65, 33, 4, 1, 30.0, 10.0, 0.2), (127, 16, 2, 16, 30.0, 40.0, 0.0),
-    (512, 16, 1, 5, 288.0, 2.0, 0.1), (1000, 64, 3, 5, 30.0, 3.0, 0.0), (2049, 7, 4, 3, 30.0, 25.0, 0.1),
+    (512, 16, 1, 5, 288.0, 2.0, 0.1), (1024, 8, 1, 2, 288.0, 4.0, 0.0), (1025, 8, 1, 3, 288.0, 0.5, 0.0),
+    (1088, 5, 4, 2, 288.0, 1.0, 0.1), (1000, 64, 3, 5, 30.0, 3.0, 0.0), (2049, 7, 4, 3, 30.0, 25.0, 0.1),
     (4096, 64, 4, 5, 30.0, 2.0, 0.0), (4033, 1, 1, 2, 288.0, 2.0, 0.0)])
 @pytest.mark.parametrize("plans", [False, True])
 @pytest.mark.parametrize("tiers", [False, True])
