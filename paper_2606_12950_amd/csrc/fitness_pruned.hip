@@ -29,7 +29,8 @@
 // against 1,150 us. The pass over the 64-node bounds of 4,096 nodes took half of all vector
 // instructions (7,200 a wavefront, 88 us) before it ended early. Slower or no faster: plan records
 // read eight at a time by the lanes and broadcast (no change), 80 registers for a sixth wavefront
-// per SIMD (51 against 43 us on 512 nodes).
+// per SIMD (51 against 43 us on 512 nodes), all tables in LDS with 1,024 lanes a CU (61 against 50
+// us a call), sub-block bounds as packed integer keys (no change).
 #include "fitness.h"
 #include "internal.h"
 #include "select.h"
