@@ -175,7 +175,10 @@ def _workspace(t: Optional[torch.Tensor], name: str = "workspace") -> Optional[t
 
 def _scratch(n_bytes: int, device, stream) -> Optional[torch.Tensor]:
     """Scratch for one call on ``stream`` (None: the current one), from that stream's own allocator
-    pool, so that freeing it on return orders its reuse behind the call; None under graph capture."""
+    pool, so that freeing it on return orders its reuse behind the call; None under graph capture,
+    and for a stream that is not torch's (any object with a ``cuda_stream`` handle), which has no pool."""
+    if stream is not None and not isinstance(stream, torch.cuda.Stream):
+        return None
     if stream is None:
         if torch.cuda.is_current_stream_capturing():
             return None

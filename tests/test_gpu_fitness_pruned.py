@@ -120,6 +120,35 @@ def test_pruned_on_a_stream_of_its_own(monkeypatch):
         assert np.array_equal(fit.cpu().numpy().view(np.uint32), want[1].view(np.uint32))
 
 
+def test_streams_that_are_not_torchs_and_capture_take_no_scratch(monkeypatch):
+    kw = _inputs(7, 70_001, 3200, 16, 5, USUAL, 30.0, 2.0, False, False)
+    want = _both(monkeypatch, **kw, k=4)
+    torch.cuda.synchronize()
+
+    class Handle:
+        cuda_stream = torch.cuda.current_stream().cuda_stream
+
+    lib = _native.load()
+    out = (torch.empty(70_001, 4, dtype=torch.int32, device="cuda"), torch.empty(70_001, 4, device="cuda"))
+    with monkeypatch.context() as mp:
+        mp.setattr(lib, "maestro_route_fitness_pruned", None)      # not to be called
+        M.route_fitness(**kw, k=4, out=out, stream=Handle())
+        torch.cuda.synchronize()
+        first = [a.cpu().numpy() for a in out]
+        for a in out:
+            a.zero_()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            M.route_fitness(**kw, k=4, out=out)
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        for got in (first, [a.cpu().numpy() for a in out]):
+            assert np.array_equal(got[0], want[0]) and np.array_equal(got[1].view(np.uint32), want[1].view(np.uint32))
+        for a in out:
+            a.zero_()
+
+
 def test_pruned_argument_checks():
     lib = _native.load()
     assert lib.maestro_route_fitness_workspace(1000, 16, 512, 5, 2, 1, 0) == 0          # small batch
