@@ -219,8 +219,10 @@ __device__ __forceinline__ bf16x8 relu_bf16(const f32x16& acc, int half) {
 }
 
 // Direct global->LDS loads through a raw buffer resource: lane l's 16 (or 4) bytes at byte offset
-// voff + soff of the buffer land at LDS byte address lds_base + lds_off + 16 l (or 4 l); lanes
-// whose voff is at or past the buffer's size read zeros and touch no memory. Issued as inline
+// voff + soff of the buffer land at LDS byte address lds_base + lds_off + 16 l (or 4 l). Without soff,
+// lanes whose voff is at or past the buffer's size read zeros and touch no memory; a load that may pass
+// the buffer's end therefore carries its whole offset in voff (dma16_once, dma4: the outcome of a size
+// smaller than soff is not defined), and soff is for loads that stay inside the buffer. Issued as inline
 // assembly so that the compiler's automatic wait insertion, which would conservatively drain
 // every such load before any LDS read, does not see them; the kernel waits for them itself
 // (wait_chunk). rsrc, soff and lds_base are wavefront-uniform; lds_off is a compile-time constant.
@@ -243,18 +245,17 @@ __device__ __forceinline__ i32x4 buffer_rsrc(const void* base, uint32_t bytes) {
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return (uint32_t)(uintptr_t)(const lds_uchar*)(p);
 }
-// kStream marks the load non-temporal (nt): data read once (features, per-stage inputs) is
-// then a candidate for early eviction and does not push the weights, which every tile re-reads,
-// out of the L2 cache.
-template <bool kStream = false>
 __device__ __forceinline__ void dma16(const i32x4& rsrc, uint32_t voff, uint32_t soff, uint32_t lds_base,
                                       int lds_off) {
-  if constexpr (kStream)
-    asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, %4 offen nt lds"
-                 ::"s"(lds_base), "i"(lds_off), "v"(voff), "s"(rsrc), "s"(soff) : "m0", "scc");
-  else
-    asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds"
-                 ::"s"(lds_base), "i"(lds_off), "v"(voff), "s"(rsrc), "s"(soff) : "m0", "scc");
+  asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds"
+               ::"s"(lds_base), "i"(lds_off), "v"(voff), "s"(rsrc), "s"(soff) : "m0", "scc");
+}
+// For data read once (features, per-stage inputs), which may pass the buffer's end: no scalar offset,
+// and non-temporal (nt), a candidate for early eviction that does not push the weights, which every
+// tile re-reads, out of the L2 cache.
+__device__ __forceinline__ void dma16_once(const i32x4& rsrc, uint32_t voff, uint32_t lds_base, int lds_off) {
+  asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen nt lds"
+               ::"s"(lds_base), "i"(lds_off), "v"(voff), "s"(rsrc) : "m0", "scc");
 }
 __device__ __forceinline__ void dma4(const i32x4& rsrc, uint32_t voff, uint32_t lds_base) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen nt lds"

@@ -22,6 +22,7 @@
 // in LDS so that the 16 rows a half-wavefront reads at one column fall in distinct banks.
 #include <type_traits>
 
+#include "feature_load.h"
 #include "internal.h"
 #include "mlp.h"
 
@@ -252,21 +253,8 @@ void mlp3_bf16_kernel(
   const uint32_t voff1 = (uint32_t)(((lane >> 5) * D + (((lane & 31) ^ ((lane >> 5) << 3)) * 8)) * 2);
   const uint32_t voff2 = (uint32_t)(lane * 16);
   const uint32_t voff3 = (uint32_t)(((lane >> 2) * H2 + (((lane & 3) ^ ((lane >> 4) & 3)) * 8)) * 2);
-  // feature load q of a chunk: tile row rho = 64j + 2i + (lane / 32), i = wave + 4q, 16-byte unit
-  // (lane % 32) ^ (rho % 16); rho % 16 depends on q only through q % 2
-  uint32_t voffx[2];
-#pragma unroll
-  for (int p = 0; p < 2; ++p) {
-    const int rho = 2 * wave + h + 8 * p;
-    voffx[p] = (uint32_t)((2 * wave + h) * D * 2 + (((lane & 31) ^ (rho & 15)) << 4));
-  }
-  // G = 2: feature chunk j is K-slice j instead (columns 64j .. 64j+63 of all 256 tile rows, 128
-  // bytes per row, the 16-byte unit u of row r stored at u ^ ((r / 2) % 8)), so that every
-  // wavefront reads its B operands from every feature chunk. A load brings 8 rows; lane l fills
-  // row l / 8, position l % 8, and since (r / 2) % 8 = 4 (i % 2) + l / 16 for row r = 8i + l / 8
-  // with i = wave + 4q, one offset per lane serves every load of the wavefront.
-  const uint32_t voffk =
-      (uint32_t)((lane >> 3) * D * 2 + (((lane & 7) ^ (4 * (wave & 1) + (lane >> 4))) << 4));
+  // G = 2: feature chunk j is K-slice j (columns 64j .. 64j+63 of all 256 tile rows) instead of 64
+  // rows, so that every wavefront reads its B operands from every feature chunk (feature_load.h).
   // The per-stage inputs (prompt lengths, model ids, and for the two-phase predictor role ids
   // and tool availability) travel in 64-row pieces with the feature chunks: piece p = 4j + wave
   // rides on feature chunk j and holds rows 64 (p % R) .. 64 (p % R) + 63 of input p / R
@@ -295,7 +283,7 @@ void mlp3_bf16_kernel(
           const int32_t st = h ? s1 : s0;
           const uint32_t unit = (uint32_t)(((lane & 31) ^ ((rho0 + h) & 15)) << 4);
           const uint32_t voff = st >= 0 ? (uint32_t)st * (uint32_t)(D * 2) + unit : 0x80000000u;
-          dma16<true>(rs, voff, 0u, base, q * kWaves * 1024);
+          dma16_once(rs, voff, base, q * kWaves * 1024);
         }
       } else {
         // K-slice j of tile rows 8i .. 8i+7 (i = wave + 4q) as in the contiguous layout, each
@@ -306,18 +294,15 @@ void mlp3_bf16_kernel(
           int32_t st = -1;
           if (live) st = scalar_load8_pick(perm + row0 + 8 * (wave + 4 * q), lane >> 3);
           const uint32_t voff = st >= 0 ? (uint32_t)st * (uint32_t)(D * 2) + unit : 0x80000000u;
-          dma16<true>(rs, voff, 0u, base, q * kWaves * 1024);
+          dma16_once(rs, voff, base, q * kWaves * 1024);
         }
       }
     } else {
-      const i32x4 rs = buffer_rsrc(x + row0 * D, rows * (D * 2));
+      const i32x4 rs = buffer_rsrc(x + row0 * D, rows * kFeatureRow);
 #pragma unroll
-      for (int q = 0; q < kDmaPerChunk; ++q) {
-        if constexpr (G == 1)
-          dma16<true>(rs, voffx[q & 1] + (uint32_t)((64 * j + 8 * q) * D * 2), 0u, base, q * kWaves * 1024);
-        else   // rows 8i .. 8i+7, i = wave + 4q, of K-slice j
-          dma16<true>(rs, voffk, (uint32_t)(8 * (wave + 4 * q) * D * 2 + 128 * j), base, q * kWaves * 1024);
-      }
+      for (int q = 0; q < kDmaPerChunk; ++q)
+        dma16_once(rs, G == 1 ? feature_offset_rows(j, q, wave, lane) : feature_offset_slice(j, q, wave, lane), base,
+                    q * kWaves * 1024);
     }
     const int piece = 4 * j + wave;
     if (piece < kMeta * kPiecesPerInput) {

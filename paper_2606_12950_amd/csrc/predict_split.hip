@@ -24,6 +24,7 @@
 // over ascending blocks), so a stage's prediction has the same bits whichever kernel ran.
 #include <type_traits>
 
+#include "feature_load.h"
 #include "internal.h"
 #include "mlp.h"
 
@@ -114,8 +115,7 @@ void mlp3_split_kernel(const SplitArgs a) {
   const int64_t row0 = tile * R;
   const uint32_t rows = kRoles ? (uint32_t)R : (uint32_t)(a.n - row0 < R ? a.n - row0 : R);
   {
-    // feature load q: rows 2i (lanes 0-31) and 2i + 1, i = wave + 4q; 16-byte unit u of row r is
-    // stored at u ^ (r % 16)
+    // feature load q: rows 2i (lanes 0-31) and 2i + 1, i = wave + 4q (feature_load.h)
     const uint32_t base = lds_addr(s_act) + wave * 1024;
     if constexpr (kRoles) {
       const i32x4 rs = buffer_rsrc(a.x, (uint32_t)(a.n * (kD * 2)));
@@ -125,15 +125,12 @@ void mlp3_split_kernel(const SplitArgs a) {
 #pragma unroll
       for (int q = 0; q < R / 8; ++q) {
         const uint32_t unit = (uint32_t)(((lane & 31) ^ ((2 * (wave + 4 * q) + h) & 15)) << 4);
-        dma16<true>(rs, st[q] >= 0 ? (uint32_t)st[q] * (uint32_t)(kD * 2) + unit : 0x80000000u, 0u, base, q * 4096);
+        dma16_once(rs, st[q] >= 0 ? (uint32_t)st[q] * (uint32_t)(kD * 2) + unit : 0x80000000u, base, q * 4096);
       }
     } else {
-      const i32x4 rs = buffer_rsrc(a.x + row0 * kD, rows * (kD * 2));
+      const i32x4 rs = buffer_rsrc(a.x + row0 * kD, rows * kFeatureRow);
 #pragma unroll
-      for (int q = 0; q < R / 8; ++q) {
-        const uint32_t unit = (uint32_t)(((lane & 31) ^ ((2 * wave + h + 8 * (q & 1)) & 15)) << 4);
-        dma16<true>(rs, (uint32_t)((2 * wave + h) * kD * 2) + unit, (uint32_t)(8 * q * kD * 2), base, q * 4096);
-      }
+      for (int q = 0; q < R / 8; ++q) dma16_once(rs, feature_offset_split(q, wave, lane), base, q * 4096);
     }
     const i32x4 rb1 = buffer_rsrc(a.b1 + (size_t)grp * H, H * 4), rb2 = buffer_rsrc(a.b2 + (size_t)grp * H, H * 4);
     for (int i = wave; i < H / 256; i += 4) {
