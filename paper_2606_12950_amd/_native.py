@@ -173,18 +173,27 @@ def _workspace(t: Optional[torch.Tensor], name: str = "workspace") -> Optional[t
     return t
 
 
-def _scratch(n_bytes: int, device, stream) -> Optional[torch.Tensor]:
-    """Scratch for one call on ``stream`` (None: the current one), from that stream's own allocator
-    pool, so that freeing it on return orders its reuse behind the call; None under graph capture,
-    and for a stream that is not torch's (any object with a ``cuda_stream`` handle), which has no pool."""
-    if stream is not None and not isinstance(stream, torch.cuda.Stream):
-        return None
+def _scratch(n_bytes: int, device, stream) -> torch.Tensor:
+    """Scratch for one call on ``stream`` (None: the current one; torch's, or any object with a
+    ``cuda_stream`` handle), from that stream's own allocator pool: dropped on return, its block goes
+    to later work of the same stream only, and it is not one that another stream's work still uses."""
     if stream is None:
-        if torch.cuda.is_current_stream_capturing():
-            return None
         return torch.empty(n_bytes, dtype=torch.uint8, device=device)
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(stream.cuda_stream, device=device)
     with torch.cuda.stream(stream):
-        return _scratch(n_bytes, device, None)
+        return torch.empty(n_bytes, dtype=torch.uint8, device=device)
+
+
+def _may_allocate(stream) -> bool:
+    """Whether a call that can do without scratch may allocate it: not under graph capture, and not
+    for a stream that is not torch's, of which that cannot be asked."""
+    if stream is None:
+        return not torch.cuda.is_current_stream_capturing()
+    if not isinstance(stream, torch.cuda.Stream):
+        return False
+    with torch.cuda.stream(stream):
+        return not torch.cuda.is_current_stream_capturing()
 
 
 def _check(fn: str, status: int):
@@ -247,7 +256,7 @@ def predict(x: torch.Tensor, weights: Sequence[torch.Tensor], biases: Sequence[t
     _shape(_dev(pred, "pred_len", torch.float32), "pred_len", (n,))
     _shape(_dev(kv, "kv_bytes", torch.float64), "kv_bytes", (n,))
     ws_bytes = lib.maestro_predict_workspace(ctypes.byref(p), n)
-    ws = torch.empty(max(ws_bytes, 1), dtype=torch.uint8, device=x.device) if ws_bytes else None
+    ws = _scratch(ws_bytes, x.device, stream) if ws_bytes else None
     st = lib.maestro_predict(ctypes.byref(p), n, _ptr(x), _ptr(prompt_len), _ptr(model_id),
                              _ptr(kv_bytes_per_token), kv_bytes_per_token.shape[0], _ptr(pred),
                              _ptr(kv), _ptr(ws), ws_bytes, _stream(stream))
@@ -357,7 +366,7 @@ def predict_role_lengths(x: torch.Tensor, weights: Sequence[torch.Tensor], biase
     need = lib.maestro_role_lengths_workspace(n, G)
     _workspace(workspace)
     if workspace is None:
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=x.device)
+        workspace = _scratch(max(need, 256), x.device, stream)
     st = lib.maestro_predict_role_lengths(ctypes.byref(p), ctypes.byref(r), n, _ptr(x), _ptr(prompt_len),
                                           _ptr(model_id), _ptr(role_id), _ptr(p_tool), _ptr(kv_bytes_per_token),
                                           kv_bytes_per_token.shape[0], _ptr(pred_len), _ptr(kv_bytes),
@@ -411,7 +420,7 @@ def route(model_id: torch.Tensor, pred_len: torch.Tensor, kv_bytes: torch.Tensor
     _workspace(workspace)
     ws_bytes = route_workspace_bytes(n, decode_s_per_token.shape[0], M, k)
     if ws_bytes and workspace is None:
-        workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=model_id.device)
+        workspace = _scratch(ws_bytes, model_id.device, stream)
     ws = (_ptr(workspace) if workspace is not None else None, workspace.numel() if workspace is not None else 0)
     if act_s is not None:
         st = lib.maestro_route_tiered(n, _ptr(model_id), _ptr(pred_len), _ptr(kv_bytes), _ptr(decode_s_per_token),
@@ -501,12 +510,11 @@ def route_fitness(model_id: torch.Tensor, src_id: torch.Tensor, class_id: torch.
     # code under graph capture gets the kernel without scratch, so that nothing is allocated there
     ws_bytes = lib.maestro_route_fitness_workspace(n, int(n_models), M, rtt_ms.shape[0], class_weights.shape[0], int(k),
                                                    plans is not None)
-    if ws_bytes:
+    if ws_bytes and _may_allocate(stream):
         ws = _scratch(ws_bytes, model_id.device, stream)
-        if ws is not None:
-            _check("maestro_route_fitness_pruned",
-                   lib.maestro_route_fitness_pruned(*args, _ptr(ws), ws_bytes, _stream(stream)))
-            return idx, fit
+        _check("maestro_route_fitness_pruned",
+               lib.maestro_route_fitness_pruned(*args, _ptr(ws), ws_bytes, _stream(stream)))
+        return idx, fit
     _check("maestro_route_fitness", lib.maestro_route_fitness(*args, _stream(stream)))
     return idx, fit
 
@@ -576,12 +584,10 @@ def quantiles_workspace_bytes(m: int) -> int:
     return int(load().maestro_quantiles_workspace(m))
 
 
-def _select_workspace(m: int, workspace: Optional[torch.Tensor], device) -> Tuple[Optional[int], int]:
+def _select_workspace(m: int, workspace: Optional[torch.Tensor], device, stream) -> Optional[torch.Tensor]:
     _workspace(workspace)
     need = quantiles_workspace_bytes(m)
-    if need and workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=device)
-    return (_ptr(workspace), workspace.numel()) if workspace is not None else (None, 0)
+    return _scratch(need, device, stream) if need and workspace is None else workspace
 
 
 def adaptive_rho(kv_actual: torch.Tensor, kv_pred: torch.Tensor, beta: float, q: float,
@@ -601,9 +607,9 @@ def adaptive_rho(kv_actual: torch.Tensor, kv_pred: torch.Tensor, beta: float, q:
     ew, rho = out
     _shape(_dev(ew, "ewma", torch.float32), "ewma", (m,))
     _shape(_dev(rho, "rho", torch.float32), "rho", (1,))
-    ws = _select_workspace(m, workspace, kv_actual.device)
+    ws = _select_workspace(m, workspace, kv_actual.device, stream)
     st = lib.maestro_adaptive_rho(_ptr(kv_actual), _ptr(kv_pred), m, float(beta), float(q), _ptr(ew), _ptr(rho),
-                                  ws[0], ws[1], _stream(stream))
+                                  _ptr(ws), ws.numel() if ws is not None else 0, _stream(stream))
     _check("maestro_adaptive_rho", st)
     return ew, rho
 
@@ -619,9 +625,9 @@ def quantiles(values: torch.Tensor, q_lo: float = 0.05, q_hi: float = 0.95,
     if out is None:
         out = torch.empty(2, dtype=torch.float32, device=values.device)
     _shape(_dev(out, "out", torch.float32), "out", (2,))
-    ws = _select_workspace(values.numel(), workspace, values.device)
-    st = lib.maestro_quantiles(_ptr(values), values.numel(), float(q_lo), float(q_hi), _ptr(out), ws[0], ws[1],
-                               _stream(stream))
+    ws = _select_workspace(values.numel(), workspace, values.device, stream)
+    st = lib.maestro_quantiles(_ptr(values), values.numel(), float(q_lo), float(q_hi), _ptr(out), _ptr(ws),
+                               ws.numel() if ws is not None else 0, _stream(stream))
     _check("maestro_quantiles", st)
     return out
 
@@ -745,7 +751,7 @@ def prioritize(chain_offset: torch.Tensor, stage_latency_s: torch.Tensor, deadli
     _workspace(workspace)
     ws_bytes = prioritize_workspace_bytes(W, S)
     if workspace is None:
-        workspace = torch.empty(max(ws_bytes, 256), dtype=torch.uint8, device=dev)
+        workspace = _scratch(max(ws_bytes, 256), dev, stream)
     st = lib.maestro_prioritize(W, S, _ptr(chain_offset), _ptr(stage_latency_s), _ptr(cursor),
                                 _ptr(deadline_us), int(now_us), _ptr(rem), _ptr(key), _ptr(order),
                                 _ptr(workspace), workspace.numel(), _stream(stream))
