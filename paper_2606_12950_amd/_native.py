@@ -186,10 +186,13 @@ def _scratch(n_bytes: int, device, stream) -> torch.Tensor:
 
 
 def _may_allocate(stream) -> bool:
-    """Whether a call that can do without scratch may allocate it: not under graph capture, and not
-    for a stream that is not torch's, of which that cannot be asked."""
+    """Whether a call that can do without scratch may allocate it: not while the launch stream or this
+    thread's current one is captured (memory from the driver would break the capture), and not for a
+    stream that is not torch's, of which that cannot be asked."""
+    if torch.cuda.is_current_stream_capturing():
+        return False
     if stream is None:
-        return not torch.cuda.is_current_stream_capturing()
+        return True
     if not isinstance(stream, torch.cuda.Stream):
         return False
     with torch.cuda.stream(stream):

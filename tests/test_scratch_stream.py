@@ -9,7 +9,7 @@ import pytest
 import torch
 
 import paper_2606_12950_amd as M
-from paper_2606_12950_amd import _native, pipeline  # noqa: F401
+from paper_2606_12950_amd import _native
 
 i32, f32, f64, i64 = torch.int32, torch.float32, torch.float64, torch.int64
 
@@ -81,6 +81,30 @@ def test_scratch_is_taken_under_the_launch_stream(monkeypatch, name, kind):
     call(handle)
     assert taken == [handle.cuda_stream]
     assert launched[0][-1] == handle.cuda_stream
+
+
+@pytest.mark.parametrize("capturing", ["neither", "current", "launch"])
+def test_no_scratch_while_a_stream_is_captured(monkeypatch, capturing):
+    # a call on another stream, itself not captured, still allocates in the capturing thread
+    class Stream:
+        pass
+
+    current = [None]
+
+    @contextlib.contextmanager
+    def on(s):
+        old, current[0] = current[0], s
+        yield
+        current[0] = old
+
+    launch = Stream()
+    monkeypatch.setattr(torch.cuda, "Stream", Stream)
+    monkeypatch.setattr(torch.cuda, "stream", on)
+    captured = {"neither": "no stream", "current": None, "launch": launch}[capturing]
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: current[0] is captured)
+    assert _native._may_allocate(launch) == (capturing == "neither")
+    assert _native._may_allocate(None) == (capturing != "current")
+    assert not _native._may_allocate(types.SimpleNamespace(cuda_stream=1))
 
 
 @pytest.mark.gpu
