@@ -71,10 +71,11 @@ Tables tables_of(int32_t n_models, int32_t n_nodes, int32_t n_src, int32_t n_cla
   return t;
 }
 
-// order-preserving map of float64 bits to unsigned (a total order, whatever the bits)
+// order-preserving map of float64 bits to unsigned; a headroom that is not a number admits no stage and
+// comes first, among the nodes that fall short
 __device__ __forceinline__ uint64_t double_key(double d) {
   const uint64_t u = __builtin_bit_cast(uint64_t, d);
-  return (u >> 63) ? ~u : (u | 0x8000000000000000ull);
+  return d != d ? 0ull : (u >> 63) ? ~u : (u | 0x8000000000000000ull);
 }
 
 // Position of every node in ascending (headroom, index) order by counting: wavefront w of a
@@ -311,8 +312,8 @@ __global__ __launch_bounds__(kThreads) void fitness_walk_kernel(
       int lo = 0, hi = n_nodes;
       while (lo < hi) {
         const int mid = (lo + hi) >> 1;
-        if (s_free[mid] < need) lo = mid + 1;
-        else hi = mid;
+        if (need <= s_free[mid]) hi = mid;
+        else lo = mid + 1;
       }
       start = lo;
     }
@@ -323,7 +324,7 @@ __global__ __launch_bounds__(kThreads) void fitness_walk_kernel(
 
     // ---- the nodes that fall short, by their plans
     if constexpr (kPlans) {
-      const int mine = ok ? start : 0;
+      const int mine = need == need ? start : 0;   // need is not a number: no score is
       for (int b = 0; __any(64 * b < mine); ++b) {
         const float ub = fmaf(fit_w, needf * s_r64[b], b64[b]);
         const bool want64 = 64 * b < mine && !(ub < floor_key());

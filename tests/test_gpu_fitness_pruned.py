@@ -108,6 +108,20 @@ def test_pruned_without_admitting_nodes_and_with_negative_demand(monkeypatch):
     _both(monkeypatch, **kw, k=4)
 
 
+@pytest.mark.parametrize("m,k,plans", [(600, 1, False), (600, 4, True), (2100, 4, False), (2100, 1, True)])
+def test_pruned_with_headrooms_that_are_not_numbers(monkeypatch, m, k, plans):
+    # such a node admits no stage (with plans it may free room), whatever the NaN's sign
+    kw = _inputs(m + k, 140_003, m, 16, 5, USUAL, 30.0, 2.0, plans, False)
+    kw["free_bytes"][3::29] = float("nan")
+    kw["free_bytes"][5::31] = -float("nan")
+    kw["kv_bytes"][::301] = float("nan")
+    print(f"nan m={m} k={k} plans={plans}", flush=True)
+    got = _both(monkeypatch, **kw, k=k)
+    if not plans:
+        nan = np.isnan(kw["free_bytes"].cpu().numpy())
+        assert not nan[got[0][got[0] >= 0]].any() and (got[0][::301] == -1).all()
+
+
 def test_pruned_on_a_stream_of_its_own(monkeypatch):
     kw = _inputs(6, 70_001, 3200, 16, 5, USUAL, 30.0, 2.0, False, False)
     want = _both(monkeypatch, **kw, k=4)
