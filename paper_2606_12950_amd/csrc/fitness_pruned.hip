@@ -374,6 +374,12 @@ __global__ __launch_bounds__(kThreads) void fitness_walk_kernel(
       }
     }
 
+    // A pair that fits and scores -inf (a penalty past the float32 range) takes no place in a list, nor
+    // one held by a short pair of that score: such places count as held by a node below every other.
+#pragma unroll
+    for (int i = 0; i < KT; ++i)
+      if (best.s[i] == INFINITY) best.n[i] ^= (int32_t)0x80000000;
+
     // ---- the nodes that admit the stage: those from `start` on
     const bool live = ok && start < n_nodes && need == need;
     const uint32_t room = (uint32_t)(n_nodes - start);
@@ -533,8 +539,9 @@ __global__ __launch_bounds__(kThreads) void fitness_walk_kernel(
 #pragma unroll
       for (int i = 0; i < KT; ++i) {
         if (i < k) {
-          const bool some = best.n[i] != kNoNode;
-          node_idx[stage * k + i] = some ? best.n[i] : -1;
+          const int32_t node = best.n[i] < 0 ? best.n[i] ^ (int32_t)0x80000000 : best.n[i];
+          const bool some = node != kNoNode;
+          node_idx[stage * k + i] = some ? node : -1;
           fitness[stage * k + i] = some ? -best.s[i] : -INFINITY;
         }
       }

@@ -122,6 +122,18 @@ def test_pruned_with_headrooms_that_are_not_numbers(monkeypatch, m, k, plans):
         assert not nan[got[0][got[0] >= 0]].any() and (got[0][::301] == -1).all()
 
 
+@pytest.mark.parametrize("m,k,plans", [(600, 1, False), (600, 4, True), (2100, 4, False), (2100, 1, True), (4096, 4, True)])
+def test_pruned_where_penalties_overflow(monkeypatch, m, k, plans):
+    # finite weights whose penalties pass the float32 range on some or all nodes: a pair that fits
+    # and scores -inf is not listed, one that falls short is
+    weights = [[0.25, 3e38, 3e38], [0.1, 2e38, 2.5e38], [0.25, 1.0, 1.0], [-0.3, 3.4e38, 3.4e38]]
+    kw = _inputs(m + k, 140_003, m, 16, 5, weights, 30.0, 10.0, plans, False, -3000.0)
+    kw["bounds"][2:4] = torch.tensor([-3000.0, 9000.0])
+    print(f"overflow m={m} k={k} plans={plans}", flush=True)
+    got = _both(monkeypatch, **kw, k=k)
+    assert (got[0] == -1).any()
+
+
 def test_pruned_on_a_stream_of_its_own(monkeypatch):
     kw = _inputs(6, 70_001, 3200, 16, 5, USUAL, 30.0, 2.0, False, False)
     want = _both(monkeypatch, **kw, k=4)
