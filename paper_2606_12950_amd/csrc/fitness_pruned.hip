@@ -43,6 +43,9 @@ namespace {
 constexpr int kThreads = 512;
 constexpr int kMaxNodes = 4096;          // one 64-bit mask of 64-node blocks; node records in LDS
 constexpr int kRecSteps = MAESTRO_PLAN_RECORD_STEPS;
+// Tied sub-blocks that a stage visits before it leaves the rest to tie_pass: one or two are common among
+// 512 nodes without any equal scores (leaving at the first: 58 against 48 us on 719,712 stages).
+constexpr int kTies = 2;
 
 struct __align__(16) SortedNode {
   double free, recip;                    // headroom and 1 / fl32(headroom) (0 without headroom)
@@ -51,8 +54,9 @@ struct __align__(16) SortedNode {
 // All sizes derive from the node count padded to whole 64-node blocks.
 struct Tables {
   // nodes, and floats of a bound row: blocks of 64 (padded to four), of 8, then the largest of the 64s from each on
-  int32_t padded, row;
-  size_t nodes, order, tr, prox, nd, gp, pen, bound, total;   // byte offsets
+  // ends: the same of the tables of block extremes, blocks of 64 (padded to four), then of 8
+  int32_t padded, row, ends;
+  size_t nodes, order, tr, prox, nd, gp, pen, bound, gp_top, pen_low, lowest, total;   // byte offsets
 };
 
 Tables tables_of(int32_t n_models, int32_t n_nodes, int32_t n_src, int32_t n_classes) {
@@ -67,7 +71,11 @@ Tables tables_of(int32_t n_models, int32_t n_nodes, int32_t n_src, int32_t n_cla
   t.gp = t.nd + (size_t)t.padded * sizeof(float);
   t.pen = t.gp + (size_t)n_classes * n_src * t.padded * sizeof(float);
   t.bound = t.pen + (size_t)n_classes * n_models * t.padded * sizeof(float);
-  t.total = t.bound + (size_t)n_classes * n_src * n_models * t.row * sizeof(float);
+  t.ends = (((t.padded >> 6) + 3) & ~3) + (t.padded >> 3);
+  t.gp_top = t.bound + (size_t)n_classes * n_src * n_models * t.row * sizeof(float);
+  t.pen_low = t.gp_top + (size_t)n_classes * n_src * t.ends * sizeof(float);
+  t.lowest = t.pen_low + (size_t)n_classes * n_models * t.ends * sizeof(float);
+  t.total = t.lowest + (size_t)t.ends * sizeof(uint16_t);
   return t;
 }
 
@@ -108,7 +116,7 @@ __global__ __launch_bounds__(kRankThreads) void fitness_rank_kernel(int32_t n_no
   if (i >= n_nodes) {                    // padding: admits nothing
     if (lane == 0) {
       nodes[i] = SortedNode{-INFINITY, 0.0};
-      order[i] = 0;
+      order[i] = 0xFFFFu;                // above every node: no tie is decided by it
       nd[i] = 0.0f;
     }
     if (lane < n_models) tr[(size_t)lane * padded + i] = 0.0f;
@@ -168,7 +176,8 @@ template <bool kPlans>
 __global__ __launch_bounds__(kMaxNodes / 8) void fitness_tables_kernel(
     int32_t n_models, int32_t n_nodes, int32_t n_src, int32_t padded, int32_t row, const float* __restrict__ tr,
     const float* __restrict__ prox, const float* __restrict__ nd, const float* __restrict__ class_weights,
-    float* __restrict__ gp, float* __restrict__ pen, float* __restrict__ bound) {
+    const uint16_t* __restrict__ order, float* __restrict__ gp, float* __restrict__ pen, float* __restrict__ bound,
+    int32_t ends, float* __restrict__ gp_top, float* __restrict__ pen_low, uint16_t* __restrict__ lowest) {
   __shared__ float s_top[64];
   const int m = blockIdx.x, c = blockIdx.y;
   const int p0 = threadIdx.x * 8;        // blockDim.x is padded / 8
@@ -183,8 +192,30 @@ __global__ __launch_bounds__(kMaxNodes / 8) void fitness_tables_kernel(
     pn[u] = kPlans ? lt : __fadd_rn(lt, __fmul_rn(mu, d[u]));
     low[u] = p0 + u >= n_nodes ? INFINITY : kPlans ? lt + deg_floor : pn[u];   // padding: bound -inf
   }
-  if (blockIdx.z == 0) store8(pen + (size_t)(c * n_models + m) * padded + p0, pn);
   const int blocks4 = ((padded >> 6) + 3) & ~3;
+  // the extreme `v` of these eight nodes and, over eight threads, of their block of 64
+  auto store_ends = [&](auto* __restrict__ to, auto v, auto&& of) {
+    to[blocks4 + (p0 >> 3)] = v;
+    v = of(v, __shfl_xor(v, 1));
+    v = of(v, __shfl_xor(v, 2));
+    v = of(v, __shfl_xor(v, 4));
+    if ((threadIdx.x & 7) == 0) to[p0 >> 6] = v;
+  };
+  if (blockIdx.z == 0) {
+    float least = INFINITY;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) least = p0 + u < n_nodes ? fminf(least, pn[u]) : least;
+    store8(pen + (size_t)(c * n_models + m) * padded + p0, pn);
+    store_ends(pen_low + (size_t)(c * n_models + m) * ends, least, [](float a, float b) { return fminf(a, b); });
+    if (m == 0 && c == 0) {
+      const uint4 o = *reinterpret_cast<const uint4*>(order + p0);
+      const uint32_t ow[4] = {o.x, o.y, o.z, o.w};
+      int least_node = 0xFFFF;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) least_node = min(least_node, (int)((ow[u >> 1] >> (16 * (u & 1))) & 0xFFFFu));
+      store_ends(lowest, least_node, [](int a, int b) { return min(a, b); });
+    }
+  }
   for (int s = blockIdx.z; s < n_src; s += gridDim.z) {    // workgroup-uniform
     float g[8], top = -INFINITY;
     load8(prox + (size_t)s * padded + p0, g);
@@ -193,7 +224,13 @@ __global__ __launch_bounds__(kMaxNodes / 8) void fitness_tables_kernel(
       g[u] = __fmul_rn(gamma, g[u]);
       top = fmaxf(top, g[u] - low[u]);
     }
-    if (m == 0) store8(gp + (size_t)(c * n_src + s) * padded + p0, g);
+    if (m == 0) {
+      float most = -INFINITY;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) most = p0 + u < n_nodes ? fmaxf(most, g[u]) : most;
+      store8(gp + (size_t)(c * n_src + s) * padded + p0, g);
+      store_ends(gp_top + (size_t)(c * n_src + s) * ends, most, [](float a, float b) { return fmaxf(a, b); });
+    }
     float* r = bound + (size_t)((c * n_src + s) * n_models + m) * row;
     r[blocks4 + (p0 >> 3)] = top;
     top = fmaxf(top, __shfl_xor(top, 1));
@@ -224,16 +261,104 @@ __global__ __launch_bounds__(kMaxNodes / 8) void fitness_tables_kernel(
 // than 2^-21 of it).
 constexpr float kSlack = 1.9073486328125e-06f;
 
-// Stages in turn, one per lane; the sorted node records, their original
-// indices and the largest reciprocal of every block are staged in LDS once per workgroup.
+// The rest of a stage whose k-th best score so far ties with the bounds of blocks it has not visited:
+// all its blocks again, in sorted order. A block is left out when its bound is below that score, or when
+// no node of it can enter the list: its scores are at most the one of the block's largest proximity
+// term, its least penalty and the fit on its first admitting node, evaluated as scores are (every
+// rounded operation is monotone, so no widening), and on that score only a lower node index enters. Where
+// one score fills the list, all blocks but those of lower indices go that way: 719,712 stages on 512
+// idle nodes of one kind (one result) take 74 us a call, 131,072 on 4,096 take 58, against 466 and 692
+// with every tie visited, and 146 and 367 scoring every pair. Apart from the loops that every stage
+// takes, whose registers decide how many wavefronts run (tests inside those loops: 51 against 48 us on
+// 719,712 stages without ties), so the stage's inputs are read again.
 template <int KT, bool kPlans>
-__global__ __launch_bounds__(kThreads) void fitness_walk_kernel(
+__device__ __forceinline__ void tie_pass(
+    TopK<KT>& best, int64_t stage, int start, const int32_t* __restrict__ model_id, const int32_t* __restrict__ src_id,
+    const int32_t* __restrict__ class_id, const double* __restrict__ kv_bytes, int32_t n_models, int32_t n_nodes,
+    int32_t n_src, int32_t padded, int32_t row, const double* s_recip, const float* s_r8, const float* s_r64,
+    const uint16_t* s_order, const float* __restrict__ gp, const float* __restrict__ pen, const float* __restrict__ bound,
+    int32_t ends, const float* __restrict__ gp_top, const float* __restrict__ pen_low,
+    const uint16_t* __restrict__ lowest, const float* __restrict__ class_weights, double rho, float nd_fits) {
+  asm volatile("" : "+v"(stage));          // not the values held since the stage's start
+  const int32_t m = model_id[stage], si = src_id[stage], ci = class_id[stage];
+  const double need = (rho == 0.0) ? kv_bytes[stage] : __dmul_rn(kv_bytes[stage], 1.0 + rho);
+  const double needd = (double)__double2float_rn(need);
+  const float gamma = class_weights[3 * ci], lambda = class_weights[3 * ci + 1], mu = class_weights[3 * ci + 2];
+  const float omg = __fsub_rn(1.0f, gamma), md = __fmul_rn(mu, nd_fits);
+  const float needf = fmaxf((float)needd, 0.0f), fit_w = fmaxf(omg, 0.0f) * (1.0f + kSlack);
+  const float widen = (needd < 0.0 && omg < 0.0f)
+                          ? INFINITY
+                          : kSlack * (fabsf(gamma) + fabsf(lambda) + fabsf(mu) + fabsf(omg));
+  const bool monotone = needd >= 0.0 && omg >= 0.0f;   // of the fit; otherwise no block is shut
+  const int cs = ci * n_src + si, cm = ci * n_models + m;
+  const int blocks = padded >> 6, blocks4 = (blocks + 3) & ~3;
+  const float* t64 = bound + ((size_t)cs * n_models + m) * row;
+  const float *g64 = gp_top + (size_t)cs * ends, *p64 = pen_low + (size_t)cm * ends;
+  auto shut = [&](float ub, float g, float p, int first, int low) {
+    const float fit = __double2float_rn(__dmul_rn(needd, s_recip[max(first, start)]));
+    const float key = -__fsub_rn(__fadd_rn(g, __fmul_rn(omg, fit)), kPlans ? __fadd_rn(p, md) : p);
+    const float kth = best.s[KT - 1];
+    return ub < -kth - widen || (monotone && (key > kth || (key == kth && low > best.n[KT - 1])));
+  };
+  // those of entries q .. q + 3 of a row (blocks of 64, or at + q sub-blocks) that are not shut
+  auto open4 = [&](int at, int q, int width, const float* s_r) {
+    const float4 t = *reinterpret_cast<const float4*>(t64 + at + q), r = *reinterpret_cast<const float4*>(s_r + q);
+    const float4 g = *reinterpret_cast<const float4*>(g64 + at + q), p = *reinterpret_cast<const float4*>(p64 + at + q);
+    const uint2 o = *reinterpret_cast<const uint2*>(lowest + at + q);
+    const float tv[4] = {t.x, t.y, t.z, t.w}, rv[4] = {r.x, r.y, r.z, r.w}, gv[4] = {g.x, g.y, g.z, g.w},
+                pv[4] = {p.x, p.y, p.z, p.w};
+    uint32_t mask = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const uint32_t low = ((u < 2 ? o.x : o.y) >> (16 * (u & 1))) & 0xFFFFu;
+      const bool in = (q + u + 1) * width > start && (q + u) * width < n_nodes;
+      if (in && !shut(fmaf(fit_w, fminf(needf * rv[u], 1.0f), tv[u]), gv[u], pv[u], (q + u) * width, low)) mask |= 1u << u;
+    }
+    return mask;
+  };
+#pragma unroll 1
+  for (int q = (start >> 6) & ~3; q < blocks; q += 4) {
+#pragma unroll 1
+    for (uint32_t m64 = open4(0, q, 64, s_r64); m64; m64 &= m64 - 1) {
+      const int blk = q + __ffs(m64) - 1;
+#pragma unroll 1
+      for (int h = 8 * blk; h < 8 * blk + 8; h += 4) {
+#pragma unroll 1
+        for (uint32_t m8 = open4(blocks4, h, 8, s_r8); m8; m8 &= m8 - 1) {
+          const int i0 = 8 * (h + __ffs(m8) - 1);
+          float g[8], l[8];
+          load8(gp + (size_t)cs * padded + i0, g);
+          load8(pen + (size_t)cm * padded + i0, l);
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            const int i = i0 + u;
+            const float fit = __double2float_rn(__dmul_rn(needd, s_recip[i]));
+            const float a = __fadd_rn(g[u], __fmul_rn(omg, fit));
+            const int32_t node = s_order[i];
+            bool take = i >= start && i < n_nodes;
+#pragma unroll
+            for (int t = 0; t < KT; ++t) take = take && best.n[t] != node;   // scored before
+            if (take) best.push_lex(-__fsub_rn(a, kPlans ? __fadd_rn(l[u], md) : l[u]), node);
+          }
+        }
+      }
+    }
+  }
+}
+
+// Stages in turn, one per lane; the sorted node records, their original
+// indices and the largest reciprocal of every block are staged in LDS once per workgroup. The best node
+// alone fits 96 registers, five wavefronts a SIMD (one register more: 49.6 against 46.9 us on 719,712 stages).
+template <int KT, bool kPlans>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KT == 1 && !kPlans ? 5 : 4)))
+void fitness_walk_kernel(
     int64_t n, const int32_t* __restrict__ model_id, const int32_t* __restrict__ src_id,
     const int32_t* __restrict__ class_id, const double* __restrict__ kv_bytes, int32_t n_models, int32_t n_nodes,
     int32_t n_src, int32_t n_classes, int32_t padded, int32_t row, const SortedNode* __restrict__ nodes,
     const uint16_t* __restrict__ order, const float* __restrict__ gp, const float* __restrict__ pen,
-    const float* __restrict__ bound, const maestro_deg_plan* __restrict__ plans,
-    const maestro_plan_step* __restrict__ plan_steps, const float* __restrict__ class_weights,
+    const float* __restrict__ bound, int32_t ends, const float* __restrict__ gp_top, const float* __restrict__ pen_low,
+    const uint16_t* __restrict__ lowest, const maestro_deg_plan* __restrict__ plans, const maestro_plan_step* __restrict__ plan_steps,
+    const float* __restrict__ class_weights,
     const float* __restrict__ bounds, double rho, int32_t k, int32_t* __restrict__ node_idx,
     float* __restrict__ fitness) {
   extern __shared__ __attribute__((aligned(16))) unsigned char s_raw[];
@@ -422,6 +547,11 @@ __global__ __launch_bounds__(kThreads) void fitness_walk_kernel(
       for (int u = 0; u < 8; ++u)
         ub[u] = 8 * blk + u < seen ? -INFINITY : fmaf(fit_w, fminf(needf * r[u], 1.0f), t[u]);
     };
+    // Nodes that tie (idle nodes of one kind, a few distinct round-trip times) put every block's bound
+    // within the widening of the k-th best score: a stage that meets several such bounds leaves the rest
+    // to tie_pass.
+    int ties = 0;
+    auto tied = [&](float ub) { return (ties += ub <= widen - best.s[KT - 1] ? 1 : 0) > kTies; };
     // One pass over the bounds of the 64-node blocks from the stage's first one on: the two blocks
     // of the best bounds, the third best bound, and a lower bound of the k-th best fitness -- past
     // the first block every node admits the stage, so the node that holds a block's table entry
@@ -481,6 +611,7 @@ __global__ __launch_bounds__(kThreads) void fitness_walk_kernel(
         bt = fmaxf(bt, v);
       }
       if (!(bt > -INFINITY) || bt < floor_key()) break;
+      if (tied(bt)) break;
       score8(8 * (bs < 8 ? arg : arg2) + (bs & 7));
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
@@ -488,7 +619,7 @@ __global__ __launch_bounds__(kThreads) void fitness_walk_kernel(
         ub2[u] = u + 8 == bs ? -INFINITY : ub2[u];
       }
     }
-    const bool more = third > -INFINITY && !(third < floor_key());
+    const bool more = ties <= kTies && third > -INFINITY && !(third < floor_key());
     if (__any(more)) {
       uint64_t rest = 0;
       auto bound64 = [&](int blk) { return fmaf(fit_w, fminf(needf * s_r64[blk], 1.0f), b64[blk]); };
@@ -521,6 +652,7 @@ __global__ __launch_bounds__(kThreads) void fitness_walk_kernel(
           bt = fmaxf(bt, ub[u]);
         }
         if (bt > -INFINITY && !(bt < floor_key())) {
+          if (tied(bt)) break;
           score8(8 * blk + bs);
 #pragma unroll
           for (int u = 0; u < 8; ++u) ub[u] = u == bs ? -INFINITY : ub[u];
@@ -534,6 +666,11 @@ __global__ __launch_bounds__(kThreads) void fitness_walk_kernel(
         }
       }
     }
+
+    if (ties > kTies)
+      tie_pass<KT, kPlans>(best, stage, start, model_id, src_id, class_id, kv_bytes, n_models, n_nodes, n_src, padded, row,
+                           s_recip, s_r8, s_r64, s_order, gp, pen, bound, ends, gp_top, pen_low, lowest, class_weights,
+                           rho, nd_fits);
 
     if (stage < n) {
 #pragma unroll
@@ -599,6 +736,9 @@ maestro_status launch_route_fitness_pruned(int64_t n, const int32_t* model_id, c
   float* tr = reinterpret_cast<float*>(ws + t.tr);
   float* prox = reinterpret_cast<float*>(ws + t.prox);
   float* nd = reinterpret_cast<float*>(ws + t.nd);
+  float* gp_top = reinterpret_cast<float*>(ws + t.gp_top);
+  float* pen_low = reinterpret_cast<float*>(ws + t.pen_low);
+  uint16_t* lowest = reinterpret_cast<uint16_t*>(ws + t.lowest);
   fitness_rank_kernel<<<dim3((unsigned)((t.padded + 15) / 16)), dim3(kRankThreads), 0, stream>>>(
       n_nodes, t.padded, n_models, n_src, free_bytes, queue_ms, act_ms, resident_mask, act_matrix,
       plans ? nullptr : deg_ms, rtt_ms, bounds, nodes, order, tr, prox, nd);
@@ -606,10 +746,12 @@ maestro_status launch_route_fitness_pruned(int64_t n, const int32_t* model_id, c
   const dim3 tblock((unsigned)(t.padded / 8));
   if (plans)
     fitness_tables_kernel<true><<<tgrid, tblock, 0, stream>>>(n_models, n_nodes, n_src, t.padded, t.row, tr,
-                                                                           prox, nd, class_weights, gp, pen, bound);
+                                                                           prox, nd, class_weights, order, gp, pen, bound, t.ends, gp_top, pen_low,
+                                                                lowest);
   else
     fitness_tables_kernel<false><<<tgrid, tblock, 0, stream>>>(n_models, n_nodes, n_src, t.padded, t.row, tr,
-                                                                            prox, nd, class_weights, gp, pen, bound);
+                                                                            prox, nd, class_weights, order, gp, pen, bound, t.ends, gp_top, pen_low,
+                                                                lowest);
   const size_t lds = walk_lds_bytes(t.padded);
   // One round of stages per workgroup while the LDS staging is small, up to four (equal ones)
   // at 4,096 nodes, where only two workgroups fit a CU and each stages 74 KB.
@@ -625,7 +767,8 @@ maestro_status launch_route_fitness_pruned(int64_t n, const int32_t* model_id, c
       return MAESTRO_ERR_LAUNCH;                                                                                      \
     fitness_walk_kernel<KT, PL><<<grid, dim3(threads), lds, stream>>>(                                               \
         n, model_id, src_id, class_id, kv_bytes, n_models, n_nodes, n_src, n_classes, t.padded, t.row, nodes, order,  \
-        gp, pen, bound, plans, plan_steps, class_weights, bounds, rho, k, node_idx, fitness);                         \
+        gp, pen, bound, t.ends, gp_top, pen_low, lowest, plans, plan_steps, class_weights, bounds, rho, k, node_idx,  \
+        fitness);                                                                                                    \
   } while (0)
 #define MAESTRO_FITW_KT(KT)               \
   do {                                    \
