@@ -14,7 +14,11 @@
 // With degradation plans (Alg. 2, Eq. 4) the nodes that fall short of the demand are the first
 // ones in headroom order. Their fit exceeds 1, so they come first: a wavefront goes through
 // them together (node data and plan records are then wavefront-uniform), block by block under
-// the same bounds, the C_deg term bounded by its smallest value.
+// the same bounds, the C_deg term bounded by its smallest value; a node of a block by the cheapest step of
+// its plan and by what all its steps free. Where those bounds do not help (all nodes short of room, one
+// headroom, plans that fail) every short pair is looked at, so the wavefronts of a small batch
+// share them: 8,192 stages on 4,096 nodes without headroom take 148 us, 792 before, 164 scoring every
+// pair; 500,000 stages 1,660 us, 2,010 before, against 1,480.
 //
 // Three launches: ranks of the headrooms and the sorted node records; the penalty, proximity and
 // bound tables; the stages.
@@ -32,15 +36,14 @@
 // per SIMD (51 against 43 us on 512 nodes), all tables in LDS with 1,024 lanes a CU (61 against 50
 // us a call), sub-block bounds as packed integer keys (no change).
 #include "fitness.h"
+#include "fitness_grid.h"
 #include "internal.h"
 #include "select.h"
 
 namespace maestro {
 namespace {
 
-// of the stage kernel: 512 where the LDS of 4,096 nodes admits two workgroups a CU, half that up to 1,024
-// nodes (registers admit four or five wavefronts a SIMD: 43 against 47 us on 512 nodes)
-constexpr int kThreads = 512;
+constexpr int kThreads = 512;            // of the stage kernel, at most (fitness_grid.h)
 constexpr int kMaxNodes = 4096;          // one 64-bit mask of 64-node blocks; node records in LDS
 constexpr int kRecSteps = MAESTRO_PLAN_RECORD_STEPS;
 // Tied sub-blocks that a stage visits before it leaves the rest to tie_pass: one or two are common among
@@ -50,13 +53,18 @@ constexpr int kTies = 2;
 struct __align__(16) SortedNode {
   double free, recip;                    // headroom and 1 / fl32(headroom) (0 without headroom)
 };
+struct __align__(16) SortedPlan {        // of a node that falls short
+  double reach;                          // a larger demand is past its headroom and all that its plan frees
+  float cost;                            // normalised cost of the plan's cheapest step
+  float recip;                           // SortedNode::recip, rounded up
+};
 
 // All sizes derive from the node count padded to whole 64-node blocks.
 struct Tables {
   // nodes, and floats of a bound row: blocks of 64 (padded to four), of 8, then the largest of the 64s from each on
   // ends: the same of the tables of block extremes, blocks of 64 (padded to four), then of 8
   int32_t padded, row, ends;
-  size_t nodes, order, tr, prox, nd, gp, pen, bound, gp_top, pen_low, lowest, total;   // byte offsets
+  size_t nodes, plans, order, tr, prox, nd, gp, pen, bound, gp_top, pen_low, lowest, total;   // byte offsets
 };
 
 Tables tables_of(int32_t n_models, int32_t n_nodes, int32_t n_src, int32_t n_classes) {
@@ -64,7 +72,8 @@ Tables tables_of(int32_t n_models, int32_t n_nodes, int32_t n_src, int32_t n_cla
   t.padded = (n_nodes + 63) & ~63;
   t.row = 2 * (((t.padded >> 6) + 3) & ~3) + (t.padded >> 3);
   t.nodes = 0;
-  t.order = t.nodes + (size_t)t.padded * sizeof(SortedNode);
+  t.plans = t.nodes + (size_t)t.padded * sizeof(SortedNode);
+  t.order = t.plans + (size_t)t.padded * sizeof(SortedPlan);
   t.tr = t.order + (size_t)t.padded * sizeof(uint16_t);
   t.prox = t.tr + (size_t)n_models * t.padded * sizeof(float);
   t.nd = t.prox + (size_t)n_src * t.padded * sizeof(float);
@@ -91,7 +100,7 @@ __device__ __forceinline__ uint64_t double_key(double d) {
 // on the scalar unit. 16 nodes per workgroup, so 4,096 nodes spread over 256 workgroups; the M^2
 // compares take 8 us there, a third of what a radix sort in one workgroup does. The wavefront then
 // writes the node's terms at its position: lane m norm(T_ready) of model m, lane s 1 - norm(RTT)
-// from source s, and norm(C_deg).
+// from source s, and norm(C_deg), or what its plan frees and costs at best.
 constexpr int kRankThreads = 1024;
 __global__ __launch_bounds__(kRankThreads) void fitness_rank_kernel(int32_t n_nodes, int32_t padded,
                                                                     int32_t n_models, int32_t n_src,
@@ -101,9 +110,12 @@ __global__ __launch_bounds__(kRankThreads) void fitness_rank_kernel(int32_t n_no
                                                                     const uint64_t* __restrict__ resident_mask,
                                                                     const float* __restrict__ act_matrix,
                                                                     const float* __restrict__ deg_ms,
+                                                                    const maestro_deg_plan* __restrict__ plans,
+                                                                    const maestro_plan_step* __restrict__ plan_steps,
                                                                     const float* __restrict__ rtt_ms,
                                                                     const float* __restrict__ bounds,
                                                                     SortedNode* __restrict__ nodes,
+                                                                    SortedPlan* __restrict__ sorted_plans,
                                                                     uint16_t* __restrict__ order,
                                                                     float* __restrict__ tr, float* __restrict__ prox,
                                                                     float* __restrict__ nd) {
@@ -142,6 +154,26 @@ __global__ __launch_bounds__(kRankThreads) void fitness_rank_kernel(int32_t n_no
     nodes[rank] = SortedNode{fr, frf > 0.0f ? __ddiv_rn(1.0, (double)frf) : 0.0};
     order[rank] = (uint16_t)i;
     nd[rank] = deg_ms ? norm01(deg_ms[i], bounds[4], bounds[5]) : 0.0f;
+  }
+  if (plans) {
+    const maestro_deg_plan& pl = plans[i];
+    const int ne = pl.n_engines;         // wavefront-uniform
+    float cost = lane < min(ne, kRecSteps) ? pl.cost[lane] : INFINITY;
+    double freed = ne > 0 ? pl.freed[min(ne, kRecSteps) - 1] : -INFINITY;
+    if (ne > kRecSteps) {
+      const maestro_plan_step* st = plan_steps + pl.first_step;
+      for (int e = kRecSteps + lane; e < ne; e += 64) cost = fminf(cost, st[e].cost);
+      freed = st[ne - 1].freed;
+    }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) cost = fminf(cost, __shfl_xor(cost, off));
+    if (lane == 0) {
+      // past every rounding of R_need - headroom, which a stage compares with the freed bytes
+      const double fr = free_bytes[i], slack = (fabs(fr) + fabs(freed)) * 0x1p-50;
+      const float frf = __double2float_rn(fr);
+      sorted_plans[rank] = SortedPlan{ne > 0 ? fr + freed + slack : -INFINITY, norm01(cost, bounds[4], bounds[5]),
+                                      frf > 0.0f ? __double2float_ru(__ddiv_rn(1.0, (double)frf)) : 0.0f};
+    }
   }
   if (lane < n_models) {
     const float q = queue_ms[i];
@@ -357,9 +389,10 @@ void fitness_walk_kernel(
     int32_t n_src, int32_t n_classes, int32_t padded, int32_t row, const SortedNode* __restrict__ nodes,
     const uint16_t* __restrict__ order, const float* __restrict__ gp, const float* __restrict__ pen,
     const float* __restrict__ bound, int32_t ends, const float* __restrict__ gp_top, const float* __restrict__ pen_low,
-    const uint16_t* __restrict__ lowest, const maestro_deg_plan* __restrict__ plans, const maestro_plan_step* __restrict__ plan_steps,
+    const uint16_t* __restrict__ lowest, const SortedPlan* __restrict__ sorted_plans,
+    const maestro_deg_plan* __restrict__ plans, const maestro_plan_step* __restrict__ plan_steps,
     const float* __restrict__ class_weights,
-    const float* __restrict__ bounds, double rho, int32_t k, int32_t* __restrict__ node_idx,
+    const float* __restrict__ bounds, double rho, int32_t k, int parts, int merge_at, int32_t* __restrict__ node_idx,
     float* __restrict__ fitness) {
   extern __shared__ __attribute__((aligned(16))) unsigned char s_raw[];
   double* s_free = reinterpret_cast<double*>(s_raw);
@@ -393,10 +426,14 @@ void fitness_walk_kernel(
   const float lo_d = bounds[4], hi_d = bounds[5];
   const float nd_fits = norm01(0.0f, lo_d, hi_d);   // normalised C_deg of a stage that fits
 
-  const int64_t step = (int64_t)gridDim.x * threads;
+  // with plans, `parts` wavefronts take the same 64 stages and a part each of their short pairs
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int part = kPlans ? wave & (parts - 1) : 0, group = kPlans ? wave / parts : wave;
+  const int per_block = kPlans ? threads / parts : threads;
+  const int64_t step = (int64_t)gridDim.x * per_block;
   const int64_t rounds = (n + step - 1) / step;      // workgroup-uniform: whole wavefronts vote below
   for (int64_t it = 0; it < rounds; ++it) {
-    const int64_t stage = it * step + (int64_t)blockIdx.x * threads + tid;
+    const int64_t stage = it * step + (int64_t)blockIdx.x * per_block + 64 * group + (tid & 63);
     TopK<KT> best;                                   // keys are -fitness: the smallest key is the best node
     best.init();
     bool ok = false;
@@ -450,30 +487,71 @@ void fitness_walk_kernel(
     // ---- the nodes that fall short, by their plans
     if constexpr (kPlans) {
       const int mine = need == need ? start : 0;   // need is not a number: no score is
+      // the parts tell each other their k-th best scores: that of the stage is not below any of them
+      uint32_t* floors = reinterpret_cast<uint32_t*>(s_raw + merge_at) + 64 * group + (tid & 63);
+      if (parts > 1) {
+        if (part == 0) *floors = 0u;
+        __syncthreads();
+      }
       for (int b = 0; __any(64 * b < mine); ++b) {
+        if (parts > 1) {
+          const uint32_t told = *static_cast<volatile uint32_t*>(floors);
+          known = fmaxf(known, told ? key_float(told) : -INFINITY);
+        }
         const float ub = fmaf(fit_w, needf * s_r64[b], b64[b]);
         const bool want64 = 64 * b < mine && !(ub < floor_key());
         if (!__any(want64)) continue;
-        for (int s = 8 * b; s < 8 * b + 8; ++s) {
+        // the eight sub-blocks' bounds in two reads (one read of its own for each that a part takes):
+        // these divergent reads are what a wavefront waits for
+        float u8[8], r8[8];
+        if (parts == 1) {
+          load8(b8 + 8 * b, u8);
+          load8(s_r8 + 8 * b, r8);
+#pragma unroll
+          for (int u = 0; u < 8; ++u) u8[u] = fmaf(fit_w, needf * r8[u], u8[u]);
+        }
+#pragma unroll 1
+        for (int s = 8 * b + part; s < 8 * b + 8; s += parts) {
           if (!__any(8 * s < mine)) break;
-          const float u8 = fmaf(fit_w, needf * s_r8[s], b8[s]);
-          const bool want = want64 && 8 * s < mine && !(u8 < floor_key());
+          float us;
+          if (parts == 1) {
+            us = u8[0];
+#pragma unroll
+            for (int u = 0; u < 7; ++u) u8[u] = u8[u + 1];
+          } else {
+            us = fmaf(fit_w, needf * s_r8[s], b8[s]);
+          }
+          const bool want = want64 && 8 * s < mine && !(us < floor_key());
           if (!__any(want)) continue;
           float g[8], l[8];
           load8(gp_row + 8 * s, g);
           load8(pen_row + 8 * s, l);
+          // the nodes whose plan may put them on the list, by the bound of a single node
+          const SortedPlan* sp = sorted_plans + 8 * s;
+          const float reach = floor_key() + fminf(mu, 0.0f);
+          uint32_t maybe = 0, nodes_any = 0;
 #pragma unroll
           for (int u = 0; u < 8; ++u) {
+            const bool may = want && 8 * s + u < mine && !(need > sp[u].reach) &&
+                             !(fmaf(fit_w, needf * sp[u].recip, g[u]) - fmaf(fmaxf(mu, 0.0f), sp[u].cost, l[u]) < reach);
+            maybe |= may ? 1u << u : 0u;
+            nodes_any |= __any(may) ? 1u << u : 0u;
+          }
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            if (!((nodes_any >> u) & 1u)) continue;
             const int i = 8 * s + u;
             const float fit = __double2float_rn(__dmul_rn(needd, s_recip[i]));
             const float a = __fadd_rn(g[u], __fmul_rn(omg, fit));
-            // with mu >= 0 the fitness is at most the score with C_deg normalised to 0
-            const bool go = want && i < mine && !(mu >= 0.0f && -__fsub_rn(a, l[u]) > best.s[KT - 1]);
-            if (!__any(go)) continue;
             const int j = __builtin_amdgcn_readfirstlane((int)s_order[i]);
+            // with mu >= 0 the fitness is at most the score with the plan's cheapest step
+            const float most = -__fsub_rn(a, __fadd_rn(l[u], __fmul_rn(mu, sp[u].cost)));
+            const bool go = ((maybe >> u) & 1u) &&
+                            !(mu >= 0.0f && (most > best.s[KT - 1] || (most == best.s[KT - 1] && j > best.n[KT - 1])));
+            if (!__any(go)) continue;
+            const double R = __dsub_rn(need, s_free[i]);
             const maestro_deg_plan* pl = plans + j;
             const int ne = pl->n_engines;
-            const double R = __dsub_rn(need, s_free[i]);
             int jp = 0;
 #pragma unroll
             for (int e = 0; e < kRecSteps; ++e) jp += pl->freed[e] < R ? 1 : 0;
@@ -495,7 +573,33 @@ void fitness_walk_kernel(
             if (go && found)
               best.push_lex(-__fsub_rn(a, __fadd_rn(l[u], __fmul_rn(mu, norm01(cost, lo_d, hi_d)))), j);
           }
+          if (parts > 1 && best.s[KT - 1] < INFINITY) atomicMax(floors, float_key(-best.s[KT - 1]));
         }
+      }
+    }
+
+    if constexpr (kPlans) {
+      if (parts > 1) {                   // the parts' lists meet in the first one's wavefront
+        constexpr int kSlots = 2;        // groups of parts at a time: little LDS beside the nodes
+        float* m_key = reinterpret_cast<float*>(s_raw + merge_at) + threads / parts;
+        int32_t* m_node = reinterpret_cast<int32_t*>(m_key + kSlots * KT * 64);
+        for (int g0 = 0; g0 * parts < (threads >> 6); g0 += kSlots)
+          for (int p = 1; p < parts; ++p) {
+            const bool mine = group >= g0 && group < g0 + kSlots;
+            const int at = (group - g0) * KT * 64 + (tid & 63);
+            if (mine && part == p)
+#pragma unroll
+              for (int i = 0; i < KT; ++i) {
+                m_key[at + 64 * i] = best.s[i];
+                m_node[at + 64 * i] = best.n[i];
+              }
+            __syncthreads();
+            if (mine && part == 0)
+#pragma unroll
+              for (int i = 0; i < KT; ++i) best.push_lex(m_key[at + 64 * i], m_node[at + 64 * i]);
+            __syncthreads();
+          }
+        ok = ok && part == 0;
       }
     }
 
@@ -672,7 +776,7 @@ void fitness_walk_kernel(
                            s_recip, s_r8, s_r64, s_order, gp, pen, bound, ends, gp_top, pen_low, lowest, class_weights,
                            rho, nd_fits);
 
-    if (stage < n) {
+    if (stage < n && part == 0) {
 #pragma unroll
       for (int i = 0; i < KT; ++i) {
         if (i < k) {
@@ -729,6 +833,7 @@ maestro_status launch_route_fitness_pruned(int64_t n, const int32_t* model_id, c
   const Tables t = tables_of(n_models, n_nodes, n_src, n_classes);
   unsigned char* ws = static_cast<unsigned char*>(workspace);
   SortedNode* nodes = reinterpret_cast<SortedNode*>(ws + t.nodes);
+  SortedPlan* sorted_plans = reinterpret_cast<SortedPlan*>(ws + t.plans);
   uint16_t* order = reinterpret_cast<uint16_t*>(ws + t.order);
   float* gp = reinterpret_cast<float*>(ws + t.gp);
   float* pen = reinterpret_cast<float*>(ws + t.pen);
@@ -741,7 +846,7 @@ maestro_status launch_route_fitness_pruned(int64_t n, const int32_t* model_id, c
   uint16_t* lowest = reinterpret_cast<uint16_t*>(ws + t.lowest);
   fitness_rank_kernel<<<dim3((unsigned)((t.padded + 15) / 16)), dim3(kRankThreads), 0, stream>>>(
       n_nodes, t.padded, n_models, n_src, free_bytes, queue_ms, act_ms, resident_mask, act_matrix,
-      plans ? nullptr : deg_ms, rtt_ms, bounds, nodes, order, tr, prox, nd);
+      plans ? nullptr : deg_ms, plans, plan_steps, rtt_ms, bounds, nodes, sorted_plans, order, tr, prox, nd);
   const dim3 tgrid((unsigned)n_models, (unsigned)n_classes, (unsigned)(t.padded > 512 ? n_src : 1));
   const dim3 tblock((unsigned)(t.padded / 8));
   if (plans)
@@ -752,23 +857,20 @@ maestro_status launch_route_fitness_pruned(int64_t n, const int32_t* model_id, c
     fitness_tables_kernel<false><<<tgrid, tblock, 0, stream>>>(n_models, n_nodes, n_src, t.padded, t.row, tr,
                                                                             prox, nd, class_weights, order, gp, pen, bound, t.ends, gp_top, pen_low,
                                                                 lowest);
-  const size_t lds = walk_lds_bytes(t.padded);
-  // One round of stages per workgroup while the LDS staging is small, up to four (equal ones)
-  // at 4,096 nodes, where only two workgroups fit a CU and each stages 74 KB.
-  const int threads = t.padded > 1024 ? kThreads : kThreads / 2;
-  const int64_t want = (n + threads - 1) / threads, slots = 2 * (int64_t)cus;
-  const int64_t most_rounds = t.padded > 1024 ? t.padded / 1024 : 1;
-  const int64_t fair = (want + slots - 1) / slots, rounds = fair < most_rounds ? fair : most_rounds;
-  const dim3 grid((unsigned)((want + rounds - 1) / rounds));
+  const FitnessGrid shape = fitness_grid(n, t.padded, plans != nullptr, cus);
+  const dim3 grid((unsigned)shape.blocks);
+  const int threads = shape.threads;
 #define MAESTRO_FITW(KT, PL)                                                                                          \
   do {                                                                                                                \
+    const size_t staged = (walk_lds_bytes(t.padded) + 15) & ~(size_t)15;                                              \
+    const size_t lds = staged + (shape.parts > 1 ? 2 * KT * 64 * 8 + threads / shape.parts * 4 : 0);                  \
     if (lds > 65536 && hipFuncSetAttribute(reinterpret_cast<const void*>(&fitness_walk_kernel<KT, PL>),               \
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)       \
       return MAESTRO_ERR_LAUNCH;                                                                                      \
     fitness_walk_kernel<KT, PL><<<grid, dim3(threads), lds, stream>>>(                                               \
         n, model_id, src_id, class_id, kv_bytes, n_models, n_nodes, n_src, n_classes, t.padded, t.row, nodes, order,  \
-        gp, pen, bound, t.ends, gp_top, pen_low, lowest, plans, plan_steps, class_weights, bounds, rho, k, node_idx,  \
-        fitness);                                                                                                    \
+        gp, pen, bound, t.ends, gp_top, pen_low, lowest, sorted_plans, plans, plan_steps, class_weights, bounds, rho, \
+        k, shape.parts, (int)staged, node_idx, fitness);                                                             \
   } while (0)
 #define MAESTRO_FITW_KT(KT)               \
   do {                                    \

@@ -1,7 +1,9 @@
-"""Fitness routing from bound tables where nodes tie: clusters of idle nodes of one kind, whose scores
+"""Fitness routing from bound tables where bounds prune little. Nodes that tie: clusters of idle nodes of one kind, whose scores
 differ by the source's round-trip time, by residency or by nothing, so that the block bounds of most nodes
-reach the best score. Node indices and fitness bits against scoring every pair, and the time: visiting
-every tie took three to ten times as long as scoring every pair."""
+reach the best score. And with plans, nodes that all fall short: without headroom, of one headroom, with
+plans that never free enough. Node indices and fitness bits against scoring every pair, and the time:
+visiting every tie, and every short pair by one wavefront, took three to ten times as long as scoring
+every pair."""
 import numpy as np
 import pytest
 import torch
@@ -49,6 +51,38 @@ def test_ties_match_every_pair(monkeypatch, m, k, kind, plans):
         _both(monkeypatch, **kw, k=k)
 
 
+def _saturated(kw, kind):
+    m = kw["free_bytes"].shape[0]
+    kw["free_bytes"].fill_(0.0 if kind != "same" else 1e6)
+    kw["kv_bytes"].clamp_(min=2e6)
+    off = torch.arange(m + 1, device="cuda", dtype=torch.int32) * 3
+    e = 3 * m
+    r = torch.Generator(device="cuda").manual_seed(m)
+    level = torch.randint(1, 6, (e,), generator=r, device="cuda", dtype=torch.int32)
+    freed = torch.rand(e, generator=r, device="cuda", dtype=torch.float64) * (0.1 if kind == "fail" else 20) * GB
+    cost = torch.rand(e, generator=r, device="cuda") * 900
+    if kind == "same":
+        kw = _idle(kw, "regions")
+        kw["free_bytes"].fill_(1e6)
+        level.fill_(1), freed.fill_(20 * GB), cost.fill_(300.0)
+    if kind == "none":
+        off.zero_()
+        level, freed, cost = level[:0], freed[:0], cost[:0]
+    kw["plans"] = M.degradation_plans(off, level, freed, cost, 500.0)
+    return kw
+
+
+@pytest.mark.parametrize("n,m,k", [(4_000, 1_100, 4), (8_192, 4_096, 1), (50_001, 2_049, 2), (100_003, 1_100, 1),
+                                   (70_000, 1_024, 4), (300_001, 600, 3)])
+@pytest.mark.parametrize("kind", ["empty", "same", "fail", "none"])
+def test_short_of_room_everywhere_matches_every_pair(monkeypatch, n, m, k, kind):
+    # 8, 4, 2 and 1 wavefronts that share the short pairs of 64 stages; ragged last groups
+    print(f"saturated m={m} n={n} k={k} {kind}", flush=True)
+    for weights in (USUAL, ODD):
+        got = _both(monkeypatch, **_saturated(_inputs(m + k, n, m, 16, 5, weights, 30.0, 10.0, True, False), kind), k=k)
+        assert (got[0][:, 0] == -1).all() == (kind == "none")
+
+
 def _us(f):
     f()
     best = 1e9
@@ -67,12 +101,21 @@ def _us(f):
                                         (4096, 4096, 1, "one")])
 def test_ties_take_no_longer_than_every_pair(monkeypatch, n, m, k, kind):
     # measured 0.4 .. 0.7 of that time; 3 to 10 times it with every tie visited
-    kw = _idle(_inputs(m, n, m, 16, 5, USUAL, 30.0, 2.0, False, False), kind)
+    _time(monkeypatch, _idle(_inputs(m, n, m, 16, 5, USUAL, 30.0, 2.0, False, False), kind), n, m, k, kind)
+
+
+@pytest.mark.parametrize("n,m,k,kind", [(8192, 4096, 1, "same"), (8192, 4096, 1, "empty"), (32_768, 4096, 4, "fail")])
+def test_short_of_room_takes_no_longer_than_every_pair(monkeypatch, n, m, k, kind):
+    # measured 0.2 .. 1.0 of that time; 3 to 9 times it with one wavefront for the short pairs of 64 stages
+    _time(monkeypatch, _saturated(_inputs(m, n, m, 16, 5, USUAL, 30.0, 10.0, True, False), kind), n, m, k, kind)
+
+
+def _time(monkeypatch, kw, n, m, k, kind):
     out = (torch.empty(n, k, dtype=torch.int32, device="cuda"), torch.empty(n, k, device="cuda"))
     lib = _native.load()
-    assert lib.maestro_route_fitness_workspace(n, 16, m, 5, 2, k, 0)
+    assert lib.maestro_route_fitness_workspace(n, 16, m, 5, 2, k, "plans" in kw)
     tables = _us(lambda: M.route_fitness(**kw, k=k, out=out))
     monkeypatch.setattr(lib, "maestro_route_fitness_workspace", lambda *a: 0)
     every = _us(lambda: M.route_fitness(**kw, k=k, out=out))
-    print(f"ties n={n} m={m} k={k} {kind}: tables {tables:.1f} us, every pair {every:.1f} us", flush=True)
+    print(f"bounds n={n} m={m} k={k} {kind}: tables {tables:.1f} us, every pair {every:.1f} us", flush=True)
     assert tables < 1.5 * every
