@@ -23,6 +23,8 @@ inline FitnessGrid fitness_grid(int64_t n, int32_t padded, bool plans, int64_t c
   const int64_t most_rounds = padded > 1024 ? padded / 1024 : 1;
   const int64_t fair = (want + slots - 1) / slots, rounds = fair < most_rounds ? fair : most_rounds;
   g.blocks = (want + rounds - 1) / rounds;
+  const int64_t most = ((int64_t)1 << 31) / g.threads;   // a launch takes fewer than 2^32 threads a dimension
+  if (g.blocks > most) g.blocks = most;
   return g;
 }
 
