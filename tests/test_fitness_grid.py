@@ -10,6 +10,7 @@ CSRC = os.path.join(os.path.dirname(M.LIBRARY_PATH), "csrc")
 
 PROGRAM = r"""
 #include <cstdio>
+#include <initializer_list>
 #include "fitness_grid.h"
 using namespace maestro;
 
