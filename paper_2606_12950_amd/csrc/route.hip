@@ -500,8 +500,19 @@ bool sorted_possible(int32_t n_nodes) { return n_nodes <= kSortMax; }
 // / 7.9 (64 nodes) and 12.8 / 7.5 (256). Lists of several nodes: merging the lanes' lists makes the scan
 // as slow as the sorts (9.8 against 8.5 us at 256 x 64, 16.8 against 9.1 at 4,096 x 256), so only
 // batches too small for the sorts take it.
-bool prefer_sorted(int64_t n, int32_t n_models, int32_t n_nodes, int32_t k) {
-  return sorted_possible(n_nodes) && n >= 4 * (int64_t)n_models && (k > 1 || n * n_nodes > (int64_t)1 << 23);
+//
+// With readiness tiers (act_matrix) every workgroup of the scan forms the ready times of all nodes and
+// models itself, so that it also grows with their product: about 3.4 us + 0.6 ns a (node, model) +
+// 0.4 ns per 1,000 pairs, against 7.3 us + 2.2 ns a node for the sorted route. Measured (us, scan /
+// sorted, best node alone): 64 nodes, 8 models: 4.2 / 7.6 at 2^16 pairs, 5.6 / 7.6 at 2^22, 7.5 / 7.8 at 2^23;
+// 64 nodes, 64 models: 7.1 / 8.1 at 2^20, 9.9 / 8.4 at 2^23; 512 nodes, 8 models: 7.4 / 8.4 at 2^19, 8.5 /
+// 8.4 at 2^21, 11.1 / 8.5 at 2^23; 512 nodes, 16 models: 9.9 / 8.3 at 2^17; 2,048 nodes: 19.5 / 11.8 with 8
+// models and 88 / 12.9 with 64 at 2^21; 8,192 nodes, 64 models: 344 / 31 at 2^23.
+bool prefer_sorted(int64_t n, int32_t n_models, int32_t n_nodes, int32_t k, bool tiers) {
+  if (!sorted_possible(n_nodes) || n < 4 * (int64_t)n_models) return false;
+  if (k > 1) return true;
+  if (tiers) return (int64_t)n_nodes * (n_models + 2) + n * n_nodes / 1400 > 6500;
+  return n * n_nodes > (int64_t)1 << 23;
 }
 
 }  // namespace
@@ -569,7 +580,7 @@ maestro_status launch_route(int64_t n, const int32_t* model_id, const float* pre
   bool sorted;
   if (algo == MAESTRO_ROUTE_SCAN) sorted = false;
   else if (algo == MAESTRO_ROUTE_SORTED) sorted = true;
-  else sorted = prefer_sorted(n, n_models, n_nodes, k);
+  else sorted = prefer_sorted(n, n_models, n_nodes, k, act_matrix != nullptr);
   if (sorted) {
     if (!sorted_possible(n_nodes)) return MAESTRO_ERR_UNSUPPORTED;
     if (!workspace || workspace_bytes < sorted_lists_bytes(n_models, n_nodes)) return MAESTRO_ERR_WORKSPACE;

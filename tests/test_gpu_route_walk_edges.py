@@ -10,7 +10,7 @@ import torch
 
 import oracle
 import paper_2606_12950_amd as M
-from paper_2606_12950_amd import pipeline
+from paper_2606_12950_amd import _native, pipeline
 
 pytestmark = pytest.mark.gpu
 
@@ -61,3 +61,23 @@ def test_walk_at_block_edges(nodes, k):
 def test_algorithm_choice_changes_no_result(n, nodes, models):
     s = _inputs(n, n, nodes, models)
     _check(s, 1, (M._native.ROUTE_AUTO,), sample=np.unique(np.r_[0:400, n // 2, n - 400:n]))
+
+
+@pytest.mark.parametrize("n,nodes,models,lists", [
+    (4096, 64, 8, False), (65_536, 64, 8, False), (4096, 64, 64, False), (1024, 512, 8, False),      # small products
+    (131_073, 64, 8, True), (131_072, 64, 64, True), (1024, 512, 16, True), (16_384, 512, 8, True),
+    (4096, 2048, 64, True), (1024, 8192, 64, True), (256, 8192, 8, True)])
+def test_best_node_with_tiers_sorts_unless_the_scan_is_small(n, nodes, models, lists):
+    # the scan leaves the workspace as it is, the sorted route writes its lists there
+    s = _inputs(n, n, nodes, models)
+    act = np.random.default_rng(n).uniform(0, 20, (nodes, models)).astype(np.float32)
+    ws = torch.full((_native.route_workspace_bytes(n, models, nodes, 1),), 0x5A, dtype=torch.uint8, device="cuda")
+    args = [_t(s[name]) for name in ("model", "pred", "kv", "dec", "free", "q")]
+    print(f"tiers n={n} nodes={nodes} models={models}", flush=True)
+    outs = []
+    for algo, w in ((_native.ROUTE_AUTO, ws), (_native.ROUTE_SCAN, None), (_native.ROUTE_SORTED, None)):
+        outs.append([a.cpu().numpy() for a in M.route(*args, None, None, k=1, rho=0.0, algo=algo, workspace=w,
+                                                      act_s=_t(act))])
+    assert bool((ws != 0x5A).any()) == lists
+    for idx, score in outs[1:]:
+        assert np.array_equal(outs[0][0], idx) and np.array_equal(outs[0][1].view(np.uint32), score.view(np.uint32))
