@@ -203,6 +203,41 @@ __device__ __forceinline__ uint32_t wave_rank(uint32_t d, uint32_t* count, uint6
   return before + (uint32_t)__popcll(same & lanes_below);
 }
 
+// Suffix sums of one chain by one thread, in place in LDS (stage_us, from stage s_lo on) or from the
+// latencies in memory; returns the sum at the chain's head (0 when nothing is left of it).
+template <bool kStaged>
+__device__ __forceinline__ int64_t chain_suffix(int64_t first, int64_t end, int64_t head, int64_t s_lo, int64_t* stage_us,
+                                                const float* __restrict__ stage_latency_s,
+                                                int64_t* __restrict__ remaining_us) {
+  int64_t suffix = 0, rem_head = 0;
+  if constexpr (kStaged) {
+    // not unrolled: chains are a few stages long, and the unrolled form's set-up (64-bit
+    // addresses of eight stages) costs more than the loop itself
+#pragma unroll 1
+    for (int64_t j = end - 1; j >= first; --j) {
+      suffix = sat_add(stage_us[j - s_lo], suffix);
+      stage_us[j - s_lo] = suffix;
+      if (j == head) rem_head = suffix;
+    }
+  } else {
+    for (int64_t top = end - 1; top >= first; top -= kChainBatch) {
+      float lat[kChainBatch];
+#pragma unroll
+      for (int u = 0; u < kChainBatch; ++u) lat[u] = (top - u >= first) ? stage_latency_s[top - u] : 0.0f;
+#pragma unroll
+      for (int u = 0; u < kChainBatch; ++u) {
+        const int64_t j = top - u;
+        if (j >= first) {
+          suffix = sat_add(latency_us(lat[u]), suffix);
+          if (remaining_us) remaining_us[j] = suffix;
+          if (j == head) rem_head = suffix;
+        }
+      }
+    }
+  }
+  return rem_head;
+}
+
 // One block per sort tile, one workflow per thread; also writes the tile's counts of the
 // first digit. When the block's workflows span at most kStageCap stages (the usual case), the
 // stage latencies pass through LDS: quantised by a coalesced sweep over the block's stage
@@ -238,34 +273,13 @@ __global__ __launch_bounds__(kTile) void chain_kernel(
     int64_t cur = cursor ? (int64_t)cursor[w] : 0;
     if (cur < 0) cur = 0;
     const int64_t head = first + cur;
-    int64_t suffix = 0, rem_head = 0;
+    int64_t rem_head = 0;
     if (end - first > kLongChain) {
       long_mark = 0x80000000u;   // left to long_chain_kernel, which replaces the placeholder key (rem_head 0)
       *long_flag = epoch;        // this call has a long chain (every writer stores the same value)
-    } else if (staged) {
-      // not unrolled: chains are a few stages long, and the unrolled form's set-up (64-bit
-      // addresses of eight stages) costs more than the loop itself
-#pragma unroll 1
-      for (int64_t j = end - 1; j >= first; --j) {
-        suffix = sat_add(stage_us[j - s_lo], suffix);
-        stage_us[j - s_lo] = suffix;
-        if (j == head) rem_head = suffix;
-      }
     } else {
-      for (int64_t top = end - 1; top >= first; top -= kChainBatch) {
-        float lat[kChainBatch];
-#pragma unroll
-        for (int u = 0; u < kChainBatch; ++u) lat[u] = (top - u >= first) ? stage_latency_s[top - u] : 0.0f;
-#pragma unroll
-        for (int u = 0; u < kChainBatch; ++u) {
-          const int64_t j = top - u;
-          if (j >= first) {
-            suffix = sat_add(latency_us(lat[u]), suffix);
-            if (remaining_us) remaining_us[j] = suffix;
-            if (j == head) rem_head = suffix;
-          }
-        }
-      }
+      rem_head = staged ? chain_suffix<true>(first, end, head, s_lo, stage_us, stage_latency_s, nullptr)
+                        : chain_suffix<false>(first, end, head, 0, nullptr, stage_latency_s, remaining_us);
     }
     const int32_t key = slack_of(rem_head, deadline_us[w], now_us);
     slack_key[w] = key;
@@ -605,6 +619,12 @@ __global__ __launch_bounds__(kTile) void radix_scatter_kernel(
 // for 2,048 and 36 for 4,096; one workgroup takes 9, 15 and 26 with the buckets, 12, 21 and 35.6
 // where twenty distinct slacks overflow them (their attempt included: 12, 19 and 33 without). From
 // 4,097 on, tiles of their own are faster.
+// One workgroup also walks all chains, one 1,024-workflow tile after the other, where the tiled
+// launches take up to four at once. Measured (us, one workgroup / tiled launches) for 4,096 workflows
+// of 8 stages 36 / 41, 9 stages 40 / 41, 12 stages 51 / 43, 100 stages 496 / 134, 1,500 stages (all
+// scanned by every thread) 15,800 / 4,050; for 2,048 of 16 stages 36 / 47, 32 stages 74 / 66; for 1,024
+// or fewer it is the faster form at any length (1,024 of 100 stages 109 / 133, of 1,500 stages 3,960
+// / 3,960). So more than 1,024 workflows take it up to four staging areas of stages.
 struct SlackAbove {
   __device__ __forceinline__ float operator()(uint32_t key, uint32_t low) const { return (float)(key - low); }
 };
@@ -641,14 +661,8 @@ __global__ __launch_bounds__(kTile) void small_batch_kernel(
       if (end - first > kLongChain) {
         s_long[atomicAdd(&s_n_long, 1)] = tid;
       } else {
-        int64_t suffix = 0;
-#pragma unroll 1
-        for (int64_t j = end - 1; j >= first; --j) {
-          suffix = sat_add(staged ? stage_us[j - s_lo] : latency_us(stage_latency_s[j]), suffix);
-          if (staged) stage_us[j - s_lo] = suffix;
-          else if (remaining_us) remaining_us[j] = suffix;
-          if (j == head) rem_head = suffix;
-        }
+        rem_head = staged ? chain_suffix<true>(first, end, head, s_lo, stage_us, stage_latency_s, nullptr)
+                          : chain_suffix<false>(first, end, head, 0, nullptr, stage_latency_s, remaining_us);
       }
     }
     __syncthreads();
@@ -734,7 +748,7 @@ size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
 // Few workflows (up to kFusedScanMaxTiles tiles of kTile keys): one key per thread, offsets
 // fused into the scatter. More: tiles of kTile * kBigItems keys and the group/top scans.
-constexpr int32_t kSmallWorkflows = 4 * kTile;   // up to here one workgroup does everything
+constexpr int32_t kSmallWorkflows = 4 * kTile;   // up to here one workgroup may do everything
 struct PrioLayout {
   bool fused, sums;
   int64_t tile_keys, n_tiles, group_tiles, n_groups, padded;
@@ -801,12 +815,11 @@ maestro_status launch_prioritize(int32_t n_workflows, int64_t n_stages,
                                  const int32_t* cursor, const int64_t* deadline_us,
                                  int64_t now_us, int64_t* remaining_us, int32_t* slack_key,
                                  int32_t* order, void* workspace, size_t, hipStream_t stream) {
-  (void)n_stages;
   if (n_workflows == 0) return MAESTRO_OK;
 #define MAESTRO_SMALL(ITEMS)                                                                                       \
   small_batch_kernel<ITEMS><<<dim3(1), dim3(kTile), 0, stream>>>(n_workflows, chain_offset, stage_latency_s, cursor, \
                                                                  deadline_us, now_us, remaining_us, slack_key, order)
-  if (n_workflows <= kSmallWorkflows) {
+  if (n_workflows <= kTile || (n_workflows <= kSmallWorkflows && n_stages <= 4 * (int64_t)kStageCap)) {
     if (n_workflows <= kTile) MAESTRO_SMALL(1);
     else if (n_workflows <= 2 * kTile) MAESTRO_SMALL(2);
     else MAESTRO_SMALL(4);

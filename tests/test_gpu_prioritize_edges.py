@@ -1,5 +1,5 @@
 """Slack ordering at the batch sizes where its launches change -- one workgroup up to 4,096 workflows
-(one, two or four keys a thread), 1,024-key tiles up to 131,072, group totals up to 1,024 tiles of
+(one, two or four keys a thread; beyond 1,024 up to 32,768 stages), 1,024-key tiles up to 131,072, group totals up to 1,024 tiles of
 4,096 keys, group scans beyond -- bit for bit against the oracle: coarse deadlines (many equal keys,
 so that stability shows), cursors anywhere, infinite latencies, and long chains among short ones."""
 import numpy as np
@@ -80,3 +80,24 @@ def test_one_workgroup_where_buckets_fill(W, kind):
     torch.cuda.synchronize()
     want = oracle.prioritize(off, lat, deadline, 1_000)
     assert np.array_equal(key.cpu().numpy(), want[1]) and np.array_equal(order.cpu().numpy(), want[2])
+
+
+@pytest.mark.parametrize("W,mean,one", [(1024, 8, True), (1024, 300, True), (1025, 31, True), (1025, 33, False), (2048, 15, True),
+                                        (2048, 17, False), (4096, 7, True), (4096, 9, False), (4096, 100, False),
+                                        (4096, 1100, False)])
+def test_form_by_stages(W, mean, one):
+    # one workgroup leaves the workspace as it is, the tiled launches keep keys and counts there
+    rng = np.random.default_rng(W + mean)
+    lens = rng.integers(mean - mean // 4, mean + mean // 4 + 1, W)
+    off = np.zeros(W + 1, np.int64)
+    np.cumsum(lens, out=off[1:])
+    lat = rng.choice([0.5, 1.25, 3.0], int(off[-1])).astype(np.float32)
+    deadline = rng.integers(0, 10**9, W).astype(np.int64)
+    cur = rng.integers(-1, mean, W).astype(np.int32)
+    ws = torch.full((M._native.prioritize_workspace_bytes(W, lat.size),), 0x5A, dtype=torch.uint8, device="cuda")
+    print(f"prioritize W={W} S={lat.size}", flush=True)
+    got = M.prioritize(t(off), t(lat), t(deadline), 7_000_000, cursor=t(cur), workspace=ws)
+    torch.cuda.synchronize()
+    assert bool((ws == 0x5A).all()) == one
+    for a, b in zip(got, oracle.prioritize(off, lat, deadline, 7_000_000, cursor=cur)):
+        assert np.array_equal(a.cpu().numpy(), b)
