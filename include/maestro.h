@@ -422,7 +422,8 @@ MAESTRO_API maestro_status maestro_adaptive_rho(const double* kv_actual, const d
  * 0 <= q_lo <= q_hi <= 1, 1 <= m < 2^32. Below 32,768 values one workgroup selects (no
  * workspace); from there on a workgroup per 4,096 values, up to 128, counts each 8-bit digit into
  * histograms of its own in the workspace (maestro_quantiles_workspace(m) bytes) and picks the
- * digit before from its predecessors', five launches in all. WORKSPACE for a workspace that is too small. */
+ * digit before from its predecessors', five launches in all; from 2^22 values on 256 workgroups
+ * count and one picks, eight launches. WORKSPACE for a workspace that is too small. */
 MAESTRO_API maestro_status maestro_quantiles(const float* values, int64_t m, double q_lo, double q_hi,
                              float* out, void* workspace, size_t workspace_bytes, void* stream);
 /* Workspace bytes of maestro_quantiles and maestro_adaptive_rho over m values (0 when none is

@@ -700,10 +700,15 @@ __global__ __launch_bounds__(kSelectThreads) void quantile_kernel(const float* _
 // atomics outside LDS, no waiting across workgroups and no launch between two passes that only one
 // workgroup works in. Histograms alternate between two buffers; workgroup 0 records the state.
 // The sums cost every workgroup 2 KB a histogram, the counts 1 / n of the window: n = 1 per 4,096
-// values up to 128 balances them. Measured (whole call, against 256 workgroups per pass with a launch of one
-// workgroup for the sums in between): 20.7 against 41 us at 65,536
-// values, 36 against 49 at 2^20, 43 against 58 at 2^21, 77 against 78 at 2^22.
+// values up to 128 balances them. From 2^22 values on the counts are what a pass takes, and 256
+// workgroups share them (a compute unit each), with a launch of one workgroup for the sums in between
+// (they would cost each of 256 workgroups 0.5 MB); their one set of histograms takes the room of the
+// other form's two. Measured (us, whole call, 128 workgroups and five launches / 256 and eight): 45 / 55
+// at 2^21 values, 80 / 73 at 2^22, 129 / 97 at 2^23, 426 / 251 at 2^25, 4,540 / 2,390 at 2^28. Shorter ones:
+// 21 against 41 us at 65,536 values, 39 against 49 at 2^20.
 constexpr int kSelMaxBlocks = 128;
+constexpr int64_t kWideSelectMin = (int64_t)1 << 22;
+constexpr int kWideBlocks = 2 * kSelMaxBlocks;
 constexpr int64_t kMultiSelectMin = 32768;   // inputs at least this long take the multi-workgroup passes
 
 size_t select_workspace_bytes(int64_t m) {
@@ -736,6 +741,8 @@ __device__ __forceinline__ void select_previous(SelectShared& sh, int pass, cons
   pick_digit(sh, 32 - 8 * pass);
 }
 
+// kWide: the digit before was picked by a launch of its own (prev is not read)
+template <bool kWide>
 __global__ __launch_bounds__(kSelectThreads) void select_pass_kernel(const float* __restrict__ v, int64_t m, int pass,
                                                                      int64_t r_lo, int64_t r_hi,
                                                                      const uint32_t* __restrict__ prev,
@@ -757,11 +764,11 @@ __global__ __launch_bounds__(kSelectThreads) void select_pass_kernel(const float
   };
   load(b0);                                // on its way while the previous digit is picked
   clear_counts(sh);
-  if (pass > 0) {
+  if (pass > 0 && !kWide) {
     select_previous(sh, pass, prev, gridDim.x, r_lo, r_hi, st);
     if (blockIdx.x == 0 && tid == 0) st[pass - 1] = sh.st;
   } else if (tid < 2) {
-    sh.st.prefix[tid] = 0;
+    sh.st.prefix[tid] = pass > 0 ? st[pass - 1].prefix[tid] : 0u;
   }
   __syncthreads();
   const uint32_t p0 = sh.st.prefix[0], p1 = sh.st.prefix[1], mask = select_mask(shift);
@@ -775,13 +782,15 @@ __global__ __launch_bounds__(kSelectThreads) void select_pass_kernel(const float
   if (tid < (p1 != p0 ? 512 : 256)) hist[(int64_t)blockIdx.x * 512 + tid] = counted(sh);
 }
 
-__global__ __launch_bounds__(kSelectThreads) void select_result_kernel(const uint32_t* __restrict__ hist, int n_blocks,
-                                                                       int64_t r_lo, int64_t r_hi,
-                                                                       const SelectState* __restrict__ st,
-                                                                       float* __restrict__ out, int n_out) {
+// Picks the digit that the last pass (`pass` - 1) counted: the result after four passes, else the state.
+__global__ __launch_bounds__(kSelectThreads) void select_pick_kernel(const uint32_t* __restrict__ hist, int n_blocks,
+                                                                     int pass, int64_t r_lo, int64_t r_hi,
+                                                                     SelectState* __restrict__ st,
+                                                                     float* __restrict__ out, int n_out) {
   __shared__ __attribute__((aligned(16))) SelectShared sh;
-  select_previous(sh, 4, hist, n_blocks, r_lo, r_hi, st);
-  if ((int)threadIdx.x < n_out) out[threadIdx.x] = key_float(sh.st.prefix[threadIdx.x]);
+  select_previous(sh, pass, hist, n_blocks, r_lo, r_hi, st);
+  if (pass < 4 && threadIdx.x == 0) st[pass - 1] = sh.st;
+  if (pass == 4 && (int)threadIdx.x < n_out) out[threadIdx.x] = key_float(sh.st.prefix[threadIdx.x]);
 }
 
 maestro_status launch_select(const float* v, int64_t m, int64_t r_lo, int64_t r_hi, float* out, int n_out,
@@ -798,12 +807,21 @@ maestro_status launch_select(const float* v, int64_t m, int64_t r_lo, int64_t r_
   }
   uint32_t* hist[2] = {static_cast<uint32_t*>(workspace), static_cast<uint32_t*>(workspace) + kSelMaxBlocks * 512};
   SelectState* st = reinterpret_cast<SelectState*>(hist[1] + kSelMaxBlocks * 512);
+  if (m >= kWideSelectMin) {
+    for (int pass = 0; pass < 4; ++pass) {
+      select_pass_kernel<true><<<dim3(kWideBlocks), dim3(kSelectThreads), 0, stream>>>(v, m, pass, r_lo, r_hi, nullptr,
+                                                                                     hist[0], st);
+      select_pick_kernel<<<dim3(1), dim3(kSelectThreads), 0, stream>>>(hist[0], kWideBlocks, pass + 1, r_lo, r_hi, st, out,
+                                                                       n_out);
+    }
+    return launch_status();
+  }
   const int64_t want = (m + 4095) / 4096;
   const int blocks = (int)(want < kSelMaxBlocks ? want : kSelMaxBlocks);
   for (int pass = 0; pass < 4; ++pass)
-    select_pass_kernel<<<dim3(blocks), dim3(kSelectThreads), 0, stream>>>(v, m, pass, r_lo, r_hi, hist[(pass + 1) & 1],
+    select_pass_kernel<false><<<dim3(blocks), dim3(kSelectThreads), 0, stream>>>(v, m, pass, r_lo, r_hi, hist[(pass + 1) & 1],
                                                                           hist[pass & 1], st);
-  select_result_kernel<<<dim3(1), dim3(kSelectThreads), 0, stream>>>(hist[1], blocks, r_lo, r_hi, st, out, n_out);
+  select_pick_kernel<<<dim3(1), dim3(kSelectThreads), 0, stream>>>(hist[1], blocks, 4, r_lo, r_hi, st, out, n_out);
   return launch_status();
 }
 
