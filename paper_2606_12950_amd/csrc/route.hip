@@ -197,9 +197,10 @@ __host__ __device__ constexpr int64_t skip_per_model(int32_t n_nodes) {
 // barriers per pass.
 // Both wait mostly for LDS and barriers, one workgroup a model. Measured (us, 64 models, buckets /
 // radix): 64 nodes 5.0 / 7.0, 512 nodes 6.0 / 7.8, 1,024 nodes 7.5 / 9.9, 4,096 nodes 14.2 / 21.3,
-// 8,192 nodes 24.9 / 37.8. Where a bucket overflows, the buckets' part of the time is lost: eight
-// distinct ready times on 512 nodes 9.4 against 7.7 with the radix passes alone, on 4,096 nodes
-// 24.1 against 20.2.
+// 8,192 nodes 24.9 / 37.8. Coarse ready times fill buckets (two or three dozen distinct ones on 512 nodes 7.5
+// / 7.9, 128 nodes in five readiness tiers without queues 5.8 / 7.2) or crowd them, and the buckets' part
+// of the time is lost, most of it after the sample: 11.7 against 9.9 with the radix passes alone on
+// 1,024 nodes, 22.9 against 20.3 on 4,096.
 // LDS: `padded` (key, index) pairs (dynamic), 16 KB of counts.
 constexpr int kSortWaves = kBucketWaves;
 constexpr int kSortBuckets = 256;

@@ -61,3 +61,58 @@ def test_order_where_buckets_fill(nodes, kind):
         assert np.array_equal(got[m]["node"], order.astype(np.int32))
         assert np.array_equal(got[m]["ready"].view(np.uint32), ready[order].view(np.uint32))
         assert np.array_equal(got[m]["free"], free[order])
+
+
+def _check_order(nodes, q):
+    free, mask = np.random.default_rng(nodes).uniform(0, 80e9, nodes), np.ones(nodes, np.uint64)
+    got = _lists(M.route_sort_nodes(_t(free), _t(q), _t(np.zeros(nodes, np.float32)), _t(mask), 1), 1, nodes)
+    assert np.array_equal(got[0]["node"], np.lexsort((np.arange(nodes), q)).astype(np.int32))
+
+
+@pytest.mark.parametrize("nodes,most", [(255, 256), (256, 256), (512, 256), (600, 64), (1024, 64), (2048, 32), (4096, 32), (8192, 32)])
+@pytest.mark.parametrize("over", [0, 1])
+@pytest.mark.parametrize("spread", [False, True])
+def test_order_at_the_bucket_limits(nodes, most, over, spread):
+    # one bucket with as many equal ready times as it takes, or one more, among distinct ones; next to each
+    # other (where the sample sees them) or spread over the nodes
+    rng = np.random.default_rng(nodes + over)
+    size = min(most + over, nodes - 2)
+    q = rng.permutation(np.linspace(0, 9, nodes)).astype(np.float32)
+    at = np.arange(nodes) if not spread else rng.permutation(nodes)
+    q[at[:size]] = 4.5
+    print(f"bucket limit nodes={nodes} size={size} spread={spread}", flush=True)
+    _check_order(nodes, q)
+
+
+def test_coarse_ready_times_are_not_sorted_twice():
+    # 512 nodes, 8 queue lengths, residents or not: 1.3 times the time of distinct ready times, 1.6 where the
+    # buckets gave up at 33 equal ones and radix passes followed
+    rng = np.random.default_rng(5)
+    nodes, models = 512, 8
+    free, mask = _t(rng.uniform(0, 288e9, nodes)), _t(rng.integers(0, 2**63, nodes, dtype=np.int64) & rng.integers(
+        0, 2**63, nodes, dtype=np.int64))
+    lists = torch.empty(M._native.route_lists_bytes(models, nodes), dtype=torch.uint8, device="cuda")
+
+    def us(q, cold):
+        q, cold = _t(q.astype(np.float32)), _t(cold.astype(np.float32))
+        run = lambda: M.route_sort_nodes(free, q, cold, mask, models, lists=lists)
+        run()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(20):
+                run()
+        best = 1e9
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            graph.replay()
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 50)
+        return best
+
+    fine = us(rng.uniform(0, 5, nodes), rng.uniform(2, 20, nodes))
+    coarse = us(np.round(rng.uniform(0, 8, nodes)) * 0.5, np.full(nodes, 8.0))
+    print(f"sort: distinct {fine:.2f} us, coarse {coarse:.2f} us", flush=True)
+    assert coarse < 1.45 * fine
