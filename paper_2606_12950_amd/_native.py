@@ -447,7 +447,7 @@ def route_fitness(model_id: torch.Tensor, src_id: torch.Tensor, class_id: torch.
                   n_models: int, k: int = 1, rho: float = 0.0, plans: Optional[DegradationPlans] = None,
                   act_matrix: Optional[torch.Tensor] = None,
                   out: Optional[Tuple[torch.Tensor, torch.Tensor]] = None,
-                  stream=None) -> Tuple[torch.Tensor, torch.Tensor]:
+                  stream=None, workspace: Optional[torch.Tensor] = None) -> Tuple[torch.Tensor, torch.Tensor]:
     """maestro_route_fitness: returns (node_idx int32 [N][k], fitness float32 [N][k]).
 
     ``rtt_ms`` is [n_src][n_nodes], ``class_weights`` [n_classes][3] = (gamma, lambda, mu),
@@ -455,7 +455,12 @@ def route_fitness(model_id: torch.Tensor, src_id: torch.Tensor, class_id: torch.
     side (same bits as the C-ABI's uint64). With ``plans`` (from :func:`degradation_plans`)
     C_deg comes from the node's degradation plan and ``deg_ms`` may be None. With ``act_matrix``
     [n_nodes][n_models] (from :func:`activation_latency`) T_act comes from it and ``act_ms`` /
-    ``resident_mask`` may be None."""
+    ``resident_mask`` may be None.
+
+    Batches that the bound tables serve (route_fitness_workspace_bytes > 0) take them in ``workspace`` (uint8),
+    so that with ``out`` too the call allocates nothing. Without one it takes scratch of its own, or, where
+    it may not or cannot (graph capture, a stream that is not torch's, memory exhausted), scores every
+    pair: the same results."""
     lib = load()
     _dev(model_id, "model_id", torch.int32)
     n = model_id.shape[0]
@@ -510,16 +515,25 @@ def route_fitness(model_id: torch.Tensor, src_id: torch.Tensor, class_id: torch.
             _ptr(act_matrix), _ptr(deg_ms), _ptr(plans.records) if plans is not None else None,
             _ptr(plans.steps) if plans is not None else None, _ptr(rtt_ms), _ptr(class_weights), _ptr(bounds),
             float(rho), int(k), _ptr(idx), _ptr(fit))
-    # code under graph capture gets the kernel without scratch, so that nothing is allocated there
-    ws_bytes = lib.maestro_route_fitness_workspace(n, int(n_models), M, rtt_ms.shape[0], class_weights.shape[0], int(k),
-                                                   plans is not None)
-    if ws_bytes and _may_allocate(stream):
-        ws = _scratch(ws_bytes, model_id.device, stream)
+    _workspace(workspace)
+    ws_bytes = route_fitness_workspace_bytes(n, n_models, M, rtt_ms.shape[0], class_weights.shape[0], k, plans is not None)
+    if ws_bytes and workspace is None and _may_allocate(stream):
+        try:
+            workspace = _scratch(ws_bytes, model_id.device, stream)
+        except torch.OutOfMemoryError:
+            pass
+    if ws_bytes and workspace is not None:
         _check("maestro_route_fitness_pruned",
-               lib.maestro_route_fitness_pruned(*args, _ptr(ws), ws_bytes, _stream(stream)))
+               lib.maestro_route_fitness_pruned(*args, _ptr(workspace), workspace.numel(), _stream(stream)))
         return idx, fit
     _check("maestro_route_fitness", lib.maestro_route_fitness(*args, _stream(stream)))
     return idx, fit
+
+
+def route_fitness_workspace_bytes(n: int, n_models: int, n_nodes: int, n_src: int, n_classes: int, k: int = 1,
+                                  plans: bool = False) -> int:
+    """maestro_route_fitness_workspace: bytes of the bound tables, 0 where every pair is scored instead."""
+    return int(load().maestro_route_fitness_workspace(n, int(n_models), n_nodes, n_src, n_classes, int(k), bool(plans)))
 
 
 def degradation_plans(engine_offset: torch.Tensor, engine_level: torch.Tensor, engine_freed_bytes: torch.Tensor,

@@ -175,6 +175,60 @@ def test_streams_that_are_not_torchs_and_capture_take_no_scratch(monkeypatch):
             a.zero_()
 
 
+@pytest.mark.parametrize("plans", [False, True])
+def test_workspace_of_the_caller(monkeypatch, plans):
+    # nothing is allocated, and captured code and streams that are not torch's take the tables too
+    n = 70_001
+    kw = _inputs(8, n, 3200, 16, 5, USUAL, 30.0, 2.0, plans, False)
+    want = _both(monkeypatch, **kw, k=4)
+    out = (torch.empty(n, 4, dtype=torch.int32, device="cuda"), torch.empty(n, 4, device="cuda"))
+    need = M.route_fitness_workspace_bytes(n, 16, 3200, 5, 2, 4, plans)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    lib, used = _native.load(), []
+    real = lib.maestro_route_fitness_pruned
+    monkeypatch.setattr(lib, "maestro_route_fitness_pruned", lambda *a: (used.append(a[-3]), real(*a))[1])
+
+    def check(calls):
+        torch.cuda.synchronize()
+        assert used == [ws.data_ptr()] * calls
+        for a, b in zip(out, want):
+            assert np.array_equal(a.cpu().numpy().view(np.uint32), b.view(np.uint32))
+            a.zero_()
+
+    before = torch.cuda.memory_stats()["allocation.all.allocated"]
+    M.route_fitness(**kw, k=4, out=out, workspace=ws)
+    assert torch.cuda.memory_stats()["allocation.all.allocated"] == before
+    check(1)
+
+    class Handle:
+        cuda_stream = torch.cuda.current_stream().cuda_stream
+
+    M.route_fitness(**kw, k=4, out=out, workspace=ws, stream=Handle())
+    check(2)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        M.route_fitness(**kw, k=4, out=out, workspace=ws)
+    for _ in range(3):
+        ws.random_(0, 255)                     # the program's own work between the replays
+        graph.replay()
+        check(3)
+    with pytest.raises(_native.MaestroError, match="workspace"):
+        M.route_fitness(**kw, k=4, out=out, workspace=ws[:need - 16])
+
+
+def test_exhausted_memory_scores_every_pair(monkeypatch):
+    kw = _inputs(9, 70_001, 3200, 16, 5, USUAL, 30.0, 2.0, False, False)
+    want = _both(monkeypatch, **kw, k=1)
+
+    def no_memory(*a):
+        raise torch.OutOfMemoryError("no memory")
+
+    monkeypatch.setattr(_native, "_scratch", no_memory)
+    monkeypatch.setattr(_native.load(), "maestro_route_fitness_pruned", None)      # not to be called
+    for a, b in zip(M.route_fitness(**kw, k=1), want):
+        assert np.array_equal(a.cpu().numpy().view(np.uint32), b.view(np.uint32))
+
+
 def test_pruned_argument_checks():
     lib = _native.load()
     assert lib.maestro_route_fitness_workspace(1000, 16, 512, 5, 2, 1, 0) == 0          # small batch
