@@ -17,14 +17,15 @@ extern "C" {
 #endif
 
 /* Workspace bytes of maestro_route_fitness_pruned, or 0 where scoring every pair is the faster
- * way (small batches, few nodes) or the tables are not built (more than 4,096 nodes, k > 4):
- * call maestro_route_fitness then. with_plans: nonzero when the call passes plans. */
+ * way by far (small batches, few nodes) or the tables are not built (more than 4,096 nodes,
+ * k > 4): call maestro_route_fitness then. with_plans: nonzero when the call passes plans. */
 MAESTRO_API size_t maestro_route_fitness_workspace(int64_t n, int32_t n_models, int32_t n_nodes,
                              int32_t n_src, int32_t n_classes, int32_t k, int32_t with_plans);
 
 /* maestro_route_fitness with a workspace of at least maestro_route_fitness_workspace() bytes, 16-byte
  * aligned (MAESTRO_ERR_WORKSPACE when it is smaller; MAESTRO_ERR_UNSUPPORTED where that size is
- * 0; MAESTRO_ERR_INVALID_ARG when NULL or misaligned). Other arguments, outputs and errors as
+ * 0; MAESTRO_ERR_INVALID_ARG when NULL or misaligned). Where scoring every pair is still the faster
+ * way the workspace is left as it is. Other arguments, outputs and errors as
  * maestro_route_fitness; all arrays stay alive until the stream reaches the call's end. */
 MAESTRO_API maestro_status maestro_route_fitness_pruned(int64_t n, const int32_t* model_id, const int32_t* src_id,
                              const int32_t* class_id, const double* kv_bytes, int32_t n_models,

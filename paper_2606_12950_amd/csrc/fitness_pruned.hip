@@ -797,16 +797,40 @@ size_t walk_lds_bytes(int32_t padded) {
 
 }  // namespace
 
-// Where the tables pay. Scoring every pair takes a latency that grows with the nodes a lane walks
-// (86 us at 4,096 nodes, 24 at 1,024, for a batch of any size up to 4,096 stages) plus the pairs at
-// about 2 per ps; the tables and the walk take 28 us up to 1,024 nodes and 35 at 4,096 for one
-// result per stage or with plans, 55 .. 90 us for lists of up to four (more blocks reach the
-// fourth best score, each a chain of two dependent reads). Measured on both sides of the lines
-// (us, tables / every pair): k = 1, 512 nodes: 28.7 / 17.3 at 2^23 pairs, 28.0 / 32.6 at 2^25,
-// 31.3 / 67.0 at 2^27; 4,096 nodes: 34 / 86 at 2^22. k = 4: 512 nodes 67.7 / 47.1 at 2^25, 80.2 /
-// 86.7 at 2^27; 4,096 nodes 81 / 117 at 2^22. Plans, k = 1: 256 nodes 30.8 / 27.2 at 2^24, 29.4 /
-// 55.7 at 2^26; 1,024 nodes 29.8 / 35.4 at 2^20. Many (class, source, model) combinations make the
-// tables themselves the cost: 640 of them take 5 us at 4,096 nodes.
+// Where the tables pay: from so many nodes on, from 2^pairs (stage, node) pairs on. Scoring every pair
+// takes a latency that grows with the nodes a lane walks (17 us at 512 nodes, 45 at 2,000) plus about 1 us
+// per 2^21 pairs; the tables and the walk take 22 to 60 us plus a time per stage that hardly grows with
+// the nodes, but with the list: more blocks reach the fourth best score. So the lines lie higher for
+// longer lists, and few nodes never pay. Where they lie was measured over three headroom
+// distributions (0 .. 30 GB, 0 .. 288 GB, two modes) at 64 .. 4,096 nodes and 2^18 .. 2^28 pairs. Time of the
+// tables over that of every pair, best .. worst distribution, below and at a line:
+//   no plans  k = 1  128 nodes 1.09-1.21 at 2^25, 0.99-1.01 at 2^26; 256 1.11-1.21 at 2^24, 0.79-0.82 at 2^25;
+//                    1,000 0.8-1.0 at 2^18 .. 2^23; 2,000 0.5-0.7 from 2^18 on; 96 nodes 1.06-1.09 at most
+//             k = 2  128 nodes 0.99-1.19 at 2^28; 192 1.03-1.13 at 2^26, 0.94-0.99 at 2^27; 4,096 0.3-0.5
+//             k = 4  384 nodes 0.81-1.14 at 2^28; 512 0.84-0.91 at 2^27; 4,096 0.5-0.7
+//   plans     k = 1  128 nodes 0.78-1.13 at 2^25, 0.78-0.94 at 2^26; 192 1.06-1.16 at 2^24, 0.68-0.94 at 2^25;
+//                    512 0.97-1.18 at 2^23, 0.84-0.99 at 2^24; 1,100 0.6-0.9; 96 nodes 0.99-1.06 at most
+//             k = 2  128 nodes 0.79-1.05 at 2^28; 192 0.74-1.08 at 2^25, 0.71-0.92 at 2^26; 384 0.88-1.11 at 2^24,
+//                    0.71-0.86 at 2^25; 700 0.9-1.0 at 2^24; 1,100 0.6-1.04
+//             k = 4  256 nodes 0.70-1.17 at 2^28; 384 0.87-1.16 at 2^25, 0.64-1.02 at 2^26; 700 0.7-1.2 at 2^24,
+//                    0.59-0.97 at 2^25; 1,100 0.7-1.4 up to 2^23, 0.56-0.95 at 2^25; 2,000 0.4-0.9
+static bool tables_pay(int64_t n, int32_t n_nodes, int32_t k, bool plans) {
+  struct Line {
+    int32_t nodes;
+    int pairs_log2;                      // 0: any batch
+  };
+  static constexpr Line kLines[2][3][4] = {
+      {{{2048, 0}, {256, 25}, {128, 26}}, {{3072, 0}, {192, 27}}, {{3072, 0}, {512, 27}}},
+      {{{1024, 0}, {512, 24}, {192, 25}, {128, 26}}, {{1024, 0}, {640, 24}, {384, 25}, {192, 26}},
+       {{2000, 0}, {640, 25}, {384, 26}}}};
+  for (const Line& line : kLines[plans][min(k, 3) - 1])
+    if (line.nodes > 0 && n_nodes >= line.nodes && n * n_nodes >= (int64_t)1 << line.pairs_log2) return true;
+  return false;
+}
+
+// The batches that the entry point takes. Its lines lie below those of tables_pay, between the two it
+// scores every pair: a caller with a workspace need not know which of the two is faster. Many (class, source, model) combinations make the tables themselves the cost: 640
+// of them take 5 us at 4,096 nodes.
 size_t fitness_workspace_bytes(int64_t n, int32_t n_models, int32_t n_nodes, int32_t n_src, int32_t n_classes,
                                int32_t k, bool plans) {
   if (k > 4 || n_nodes > kMaxNodes || n_nodes < 64) return 0;
@@ -826,6 +850,10 @@ maestro_status launch_route_fitness_pruned(int64_t n, const int32_t* model_id, c
                                            const float* class_weights, const float* bounds, double rho, int32_t k,
                                            int32_t* node_idx, float* fitness, void* workspace, hipStream_t stream) {
   if (n == 0) return MAESTRO_OK;
+  if (!tables_pay(n, n_nodes, k, plans != nullptr))
+    return launch_route_fitness(n, model_id, src_id, class_id, kv_bytes, n_models, n_nodes, n_src, n_classes, free_bytes,
+                                queue_ms, act_ms, resident_mask, act_matrix, deg_ms, plans, plan_steps, rtt_ms,
+                                class_weights, bounds, rho, k, node_idx, fitness, stream);
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)

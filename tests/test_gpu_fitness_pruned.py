@@ -97,6 +97,44 @@ def test_pruned_matches_every_pair(monkeypatch, m, models, k, n_src, free_gb, kv
         _both(monkeypatch, **kw, k=k, rho=rho)
 
 
+def _takes_tables(kw, k):
+    n, m = kw["kv_bytes"].shape[0], kw["free_bytes"].shape[0]
+    need = M.route_fitness_workspace_bytes(n, kw["n_models"], m, kw["rtt_ms"].shape[0], kw["class_weights"].shape[0], k,
+                                           "plans" in kw)
+    ws = torch.full((max(need, 16),), 0xA5, dtype=torch.uint8, device="cuda")
+    M.route_fitness(**kw, k=k, workspace=ws)
+    return bool((ws != 0xA5).any())
+
+
+# where the tables begin: from so many nodes on, from 2^pairs (stage, node) pairs on (0: any batch)
+@pytest.mark.parametrize("k,plans,m,pairs", [
+    (1, False, 2048, 0), (1, False, 256, 25), (1, False, 128, 26), (2, False, 3072, 0), (2, False, 192, 27),
+    (3, False, 3072, 0), (3, False, 512, 27), (4, False, 512, 27), (1, True, 1024, 0), (1, True, 512, 24),
+    (1, True, 192, 25), (1, True, 128, 26), (2, True, 1024, 0), (2, True, 640, 24), (2, True, 384, 25),
+    (2, True, 192, 26), (3, True, 2000, 0), (4, True, 2000, 0), (3, True, 640, 25), (4, True, 384, 26)])
+def test_where_the_tables_begin(monkeypatch, k, plans, m, pairs):
+    n = -(-2 ** pairs // m) if pairs else 1025
+    print(f"line k={k} plans={plans} m={m} n={n}", flush=True)
+    below = _inputs(m, n, m - 1, 16, 5, ODD, 30.0, 10.0, plans, False)
+    assert not _takes_tables(below, k)
+    _both_routes(monkeypatch, **below, k=k)
+    kw = _inputs(m + k, n, m, 16, 5, ODD, 30.0, 10.0, plans, m % 256 != 0, -50.0)
+    assert _takes_tables(kw, k)
+    _both_routes(monkeypatch, **kw, k=k)
+    if pairs:
+        kw = _inputs(m, n - 1, m, 16, 5, USUAL, 288.0, 60.0, plans, False)
+        assert not _takes_tables(kw, k)
+        _both_routes(monkeypatch, **kw, k=k)
+
+
+def _both_routes(monkeypatch, **kw):
+    got = [a.cpu().numpy().view(np.uint32) for a in M.route_fitness(**kw)]
+    with monkeypatch.context() as mp:
+        mp.setattr(_native.load(), "maestro_route_fitness_workspace", lambda *a: 0)
+        want = [a.cpu().numpy().view(np.uint32) for a in M.route_fitness(**kw)]
+    assert all(np.array_equal(a, b) for a, b in zip(got, want))
+
+
 def test_pruned_without_admitting_nodes_and_with_negative_demand(monkeypatch):
     kw = _inputs(3, 70_001, 1100, 16, 5, ODD, 5.0, 1000.0, True, False)
     _both(monkeypatch, **kw, k=4)                 # nearly every pair short

@@ -10,7 +10,7 @@ import torch
 
 import paper_2606_12950_amd as M
 from paper_2606_12950_amd import _native
-from test_gpu_fitness_pruned import ODD, USUAL, _both, _inputs
+from test_gpu_fitness_pruned import ODD, USUAL, _both, _inputs, _takes_tables
 
 pytestmark = pytest.mark.gpu
 
@@ -35,19 +35,15 @@ def _idle(kw, kind):
     return kw
 
 
-@pytest.mark.parametrize("m,k", [(65, 1), (512, 1), (512, 4), (1000, 3), (1100, 2), (2049, 4), (4096, 1), (4096, 4)])
+@pytest.mark.parametrize("n,m,k", [(2**19, 128, 1), (2**16, 512, 1), (2**18, 512, 4), (134_300, 1000, 3),
+                                   (122_100, 1100, 2), (2**16, 2049, 4), (1024, 4096, 1), (1024, 4096, 4)])
 @pytest.mark.parametrize("kind", ["one", "regions", "steps"])
 @pytest.mark.parametrize("plans", [False, True])
-def test_ties_match_every_pair(monkeypatch, m, k, kind, plans):
-    lib = _native.load()
-    n = 1024
-    while n < 1 << 22 and not lib.maestro_route_fitness_workspace(n, 16, m, 5, len(ODD), k, plans):
-        n *= 2
-    if not lib.maestro_route_fitness_workspace(n, 16, m, 5, len(ODD), k, plans):
-        pytest.skip("the tables do not take this form")
+def test_ties_match_every_pair(monkeypatch, n, m, k, kind, plans):
     print(f"ties m={m} n={n} k={k} {kind} plans={plans}", flush=True)
     for weights, tiers in ((USUAL, False), (ODD, m == 512)):
         kw = _idle(_inputs(m + k, n + 77, m, 16, 5, weights, 30.0, 10.0, plans, tiers), kind)
+        assert _takes_tables(kw, k)
         _both(monkeypatch, **kw, k=k)
 
 
@@ -72,14 +68,16 @@ def _saturated(kw, kind):
     return kw
 
 
-@pytest.mark.parametrize("n,m,k", [(4_000, 1_100, 4), (8_192, 4_096, 1), (50_001, 2_049, 2), (100_003, 1_100, 1),
+@pytest.mark.parametrize("n,m,k", [(4_000, 2_049, 4), (8_192, 4_096, 1), (50_001, 2_049, 2), (100_003, 1_100, 1),
                                    (70_000, 1_024, 4), (300_001, 600, 3)])
 @pytest.mark.parametrize("kind", ["empty", "same", "fail", "none"])
 def test_short_of_room_everywhere_matches_every_pair(monkeypatch, n, m, k, kind):
     # 8, 4, 2 and 1 wavefronts that share the short pairs of 64 stages; ragged last groups
     print(f"saturated m={m} n={n} k={k} {kind}", flush=True)
     for weights in (USUAL, ODD):
-        got = _both(monkeypatch, **_saturated(_inputs(m + k, n, m, 16, 5, weights, 30.0, 10.0, True, False), kind), k=k)
+        kw = _saturated(_inputs(m + k, n, m, 16, 5, weights, 30.0, 10.0, True, False), kind)
+        assert _takes_tables(kw, k)
+        got = _both(monkeypatch, **kw, k=k)
         assert (got[0][:, 0] == -1).all() == (kind == "none")
 
 
@@ -113,7 +111,7 @@ def test_short_of_room_takes_no_longer_than_every_pair(monkeypatch, n, m, k, kin
 def _time(monkeypatch, kw, n, m, k, kind):
     out = (torch.empty(n, k, dtype=torch.int32, device="cuda"), torch.empty(n, k, device="cuda"))
     lib = _native.load()
-    assert lib.maestro_route_fitness_workspace(n, 16, m, 5, 2, k, "plans" in kw)
+    assert _takes_tables(kw, k)
     tables = _us(lambda: M.route_fitness(**kw, k=k, out=out))
     monkeypatch.setattr(lib, "maestro_route_fitness_workspace", lambda *a: 0)
     every = _us(lambda: M.route_fitness(**kw, k=k, out=out))
