@@ -145,8 +145,9 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 def _stream(stream) -> int:
     if stream is not None:
         return stream.cuda_stream
-    # the handle torch.cuda.current_stream() wraps, without the Stream object
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    # the handle torch.cuda.current_stream() wraps, without the Stream object where this torch gives it away
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    return raw(device()) if raw and device else torch.cuda.current_stream().cuda_stream
 
 
 def _dev(t: torch.Tensor, name: str, dtype: torch.dtype) -> torch.Tensor:

@@ -129,3 +129,20 @@ def test_current_stream_is_not_given_the_block(monkeypatch, name):
         address, size = used[-1]
         assert address not in {torch.empty(size, dtype=torch.uint8, device="cuda").data_ptr() for _ in range(4)}
     assert used[0] == used[1]                 # one stream, by either name: one pool
+
+
+@pytest.mark.parametrize("missing", [(), ("_cuda_getDevice",), ("_cuda_getCurrentRawStream",)])
+def test_current_stream_without_torchs_private_calls(monkeypatch, missing):
+    class Torch:                              # torch with some of its private calls gone
+        class cuda:
+            current_stream = staticmethod(lambda: types.SimpleNamespace(cuda_stream=4096))
+
+        class _C:
+            _cuda_getDevice = staticmethod(lambda: 3)
+            _cuda_getCurrentRawStream = staticmethod(lambda device: 4096 if device == 3 else 0)
+
+    for name in missing:
+        delattr(Torch._C, name)
+    monkeypatch.setattr(_native, "torch", Torch)
+    assert _native._stream(None) == 4096
+    assert _native._stream(types.SimpleNamespace(cuda_stream=64)) == 64
