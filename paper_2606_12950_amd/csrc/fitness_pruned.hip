@@ -14,11 +14,13 @@
 // With degradation plans (Alg. 2, Eq. 4) the nodes that fall short of the demand are the first
 // ones in headroom order. Their fit exceeds 1, so they come first: a wavefront goes through
 // them together (node data and plan records are then wavefront-uniform), block by block under
-// the same bounds, the C_deg term bounded by its smallest value; a node of a block by the cheapest step of
-// its plan and by what all its steps free. Where those bounds do not help (all nodes short of room, one
-// headroom, plans that fail) every short pair is looked at, so the wavefronts of a small batch
-// share them: 8,192 stages on 4,096 nodes without headroom take 148 us, 792 before, 164 scoring every
-// pair; 500,000 stages 1,660 us, 2,010 before, against 1,480.
+// the same bounds, the C_deg term bounded by its smallest value. Where those bounds do not help (all
+// nodes short of room, one headroom, plans that fail) every short pair would be looked at, so after a few
+// sub-blocks short_pass goes on, with a bound for each node (the cheapest step of its plan, what all its
+// steps free) and, in small batches, up to eight wavefronts for the same stages: 8,192 stages on 4,096
+// nodes without headroom take 153 us, 796 without short_pass, 166 scoring every pair; 500,000 stages
+// 1,540, 2,010 and 1,490; with plans that free little 680, 1,940 and 3,090. (short_pass for all short pairs:
+// 47 against 42 us on 512 nodes whose bounds prune well.)
 //
 // Three launches: ranks of the headrooms and the sorted node records; the penalty, proximity and
 // bound tables; the stages.
@@ -49,6 +51,12 @@ constexpr int kRecSteps = MAESTRO_PLAN_RECORD_STEPS;
 // Tied sub-blocks that a stage visits before it leaves the rest to tie_pass: one or two are common among
 // 512 nodes without any equal scores (leaving at the first: 58 against 48 us on 719,712 stages).
 constexpr int kTies = 2;
+// Sub-blocks of nodes that fall short that 64 stages visit before they leave the rest to short_pass, alone
+// and where other wavefronts share it. Stages whose bounds prune well visit fewer; nodes without headroom, plans
+// that free little (500,000 stages on 512 nodes: 100, 120, 160, 210 us at 8, 16, 32, never) visit up to all.
+constexpr int kShortAlone = 16, kShortShared = 4;
+constexpr int kMaxGroups = kThreads / 128;   // groups of 64 stages of a workgroup whose wavefronts share
+constexpr int kSlots = 2;                // of them, those whose lists meet at a time: little LDS beside the nodes
 
 struct __align__(16) SortedNode {
   double free, recip;                    // headroom and 1 / fl32(headroom) (0 without headroom)
@@ -121,9 +129,20 @@ __global__ __launch_bounds__(kRankThreads) void fitness_rank_kernel(int32_t n_no
                                                                     float* __restrict__ nd) {
   __shared__ uint64_t s_key[kMaxNodes];
   const int tid = threadIdx.x, lane = tid & 63;
+  const int i = blockIdx.x * (kRankThreads / 64) + __builtin_amdgcn_readfirstlane(tid >> 6);
+  // the node's plan, read ahead of the keys
+  int32_t ne = 0, first = 0;
+  float cost = INFINITY;
+  double freed = 0.0;
+  if (plans && i < n_nodes) {
+    const maestro_deg_plan& pl = plans[i];
+    ne = pl.n_engines;
+    first = pl.first_step;
+    cost = pl.cost[lane & (kRecSteps - 1)];
+    freed = pl.freed[min(max(ne, 1), kRecSteps) - 1];
+  }
   for (int j = tid; j < padded; j += kRankThreads) s_key[j] = j < n_nodes ? double_key(free_bytes[j]) : ~0ull;
   __syncthreads();
-  const int i = blockIdx.x * (kRankThreads / 64) + (tid >> 6);
   if (i >= padded) return;
   if (i >= n_nodes) {                    // padding: admits nothing
     if (lane == 0) {
@@ -134,6 +153,13 @@ __global__ __launch_bounds__(kRankThreads) void fitness_rank_kernel(int32_t n_no
     if (lane < n_models) tr[(size_t)lane * padded + i] = 0.0f;
     if (lane < n_src) prox[(size_t)lane * padded + i] = 0.0f;
     return;
+  }
+  // the steps past the record, read ahead of the count
+  const maestro_plan_step* st = plan_steps + first;
+  float more = INFINITY;
+  if (ne > kRecSteps) {
+    if (kRecSteps + lane < ne) more = st[kRecSteps + lane].cost;
+    freed = st[ne - 1].freed;
   }
   const uint64_t key = s_key[i];
   // 64-node groups before the node's own count equal keys too, those after it do not (padding
@@ -156,15 +182,8 @@ __global__ __launch_bounds__(kRankThreads) void fitness_rank_kernel(int32_t n_no
     nd[rank] = deg_ms ? norm01(deg_ms[i], bounds[4], bounds[5]) : 0.0f;
   }
   if (plans) {
-    const maestro_deg_plan& pl = plans[i];
-    const int ne = pl.n_engines;         // wavefront-uniform
-    float cost = lane < min(ne, kRecSteps) ? pl.cost[lane] : INFINITY;
-    double freed = ne > 0 ? pl.freed[min(ne, kRecSteps) - 1] : -INFINITY;
-    if (ne > kRecSteps) {
-      const maestro_plan_step* st = plan_steps + pl.first_step;
-      for (int e = kRecSteps + lane; e < ne; e += 64) cost = fminf(cost, st[e].cost);
-      freed = st[ne - 1].freed;
-    }
+    cost = fminf(lane < min(ne, kRecSteps) ? cost : INFINITY, more);
+    for (int e = kRecSteps + 64 + lane; e < ne; e += 64) cost = fminf(cost, st[e].cost);
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) cost = fminf(cost, __shfl_xor(cost, off));
     if (lane == 0) {
@@ -378,11 +397,139 @@ __device__ __forceinline__ void tie_pass(
   }
 }
 
+// C_deg of the shortfall R by one node's plan (wavefront-uniform): the cost of the first step that has
+// freed R; false where none has. go: the lanes that need it.
+__device__ __forceinline__ bool plan_cost(const maestro_deg_plan* __restrict__ pl,
+                                          const maestro_plan_step* __restrict__ plan_steps, double R, bool go,
+                                          float& cost) {
+  const int ne = pl->n_engines;
+  int jp = 0;
+#pragma unroll
+  for (int e = 0; e < kRecSteps; ++e) jp += pl->freed[e] < R ? 1 : 0;
+  cost = pl->cost[0];
+#pragma unroll
+  for (int e = 1; e < kRecSteps; ++e) cost = jp == e ? pl->cost[e] : cost;
+  bool found = jp < ne && jp < kRecSteps;
+  if (go && !found && ne > kRecSteps) {    // the steps past the record
+    const maestro_plan_step* st = plan_steps + pl->first_step;
+    int lo = kRecSteps, hi = ne;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (st[mid].freed < R) lo = mid + 1;
+      else hi = mid;
+    }
+    found = lo < ne;
+    if (found) cost = st[lo].cost;
+  }
+  return found;
+}
+
+// The short pairs of 64 stages from sub-block `rest` on, for stages whose bounds prune little: part
+// `part` of `parts` wavefronts, which tell each other their k-th best scores (that of the stage is not below
+// any of them). A node is looked up only if the cheapest step of its plan can enter the list and all its
+// steps free enough. `mine`: the stage's short nodes, 0 without a stage. Reads the stage again, as tie_pass.
+template <int KT>
+__device__ __forceinline__ void short_pass(
+    TopK<KT>& best, int64_t stage, int mine, int rest, int part, int parts, uint32_t* floors,
+    const int32_t* __restrict__ model_id, const int32_t* __restrict__ src_id, const int32_t* __restrict__ class_id,
+    const double* __restrict__ kv_bytes, int32_t n_models, int32_t n_src, int32_t padded, int32_t row,
+    const double* s_free, const double* s_recip, const float* s_r8, const float* s_r64, const uint16_t* s_order,
+    const float* __restrict__ gp, const float* __restrict__ pen, const float* __restrict__ bound,
+    const SortedPlan* __restrict__ sorted_plans, const maestro_deg_plan* __restrict__ plans,
+    const maestro_plan_step* __restrict__ plan_steps, const float* __restrict__ class_weights, double rho, float lo_d,
+    float hi_d) {
+  asm volatile("" : "+v"(stage));
+  int32_t m = 0, si = 0, ci = 0;
+  double need = 0.0;
+  if (mine > 0) {
+    m = model_id[stage], si = src_id[stage], ci = class_id[stage];
+    need = (rho == 0.0) ? kv_bytes[stage] : __dmul_rn(kv_bytes[stage], 1.0 + rho);
+  }
+  const double needd = (double)__double2float_rn(need);
+  const float gamma = class_weights[3 * ci], lambda = class_weights[3 * ci + 1], mu = class_weights[3 * ci + 2];
+  const float omg = __fsub_rn(1.0f, gamma);
+  const float needf = fmaxf((float)needd, 0.0f), fit_w = fmaxf(omg, 0.0f) * (1.0f + kSlack);
+  const float widen = (needd < 0.0 && omg < 0.0f)
+                          ? INFINITY
+                          : kSlack * (fabsf(gamma) + fabsf(lambda) + fabsf(mu) + fabsf(omg));
+  const int cs = ci * n_src + si, blocks4 = ((padded >> 6) + 3) & ~3;
+  const float* gp_row = gp + (size_t)cs * padded;
+  const float* pen_row = pen + (size_t)(ci * n_models + m) * padded;
+  const float* b64 = bound + ((size_t)cs * n_models + m) * row;
+  const float* b8 = b64 + blocks4;
+  float known = -INFINITY;
+  auto floor_key = [&]() { return fmaxf(-best.s[KT - 1], known) - widen; };
+  for (int b = rest >> 3; __any(64 * b < mine); ++b) {
+    if (parts > 1) {
+      const uint32_t told = *static_cast<volatile uint32_t*>(floors);
+      known = fmaxf(known, told ? key_float(told) : -INFINITY);
+    }
+    const float ub = fmaf(fit_w, needf * s_r64[b], b64[b]);
+    const bool want64 = 64 * b < mine && !(ub < floor_key());
+    if (!__any(want64)) continue;
+    // the eight sub-blocks' bounds in two reads (one read of its own for each that a part takes):
+    // these divergent reads are what a wavefront waits for
+    float u8[8], r8[8];
+    if (parts == 1) {
+      load8(b8 + 8 * b, u8);
+      load8(s_r8 + 8 * b, r8);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) u8[u] = fmaf(fit_w, needf * r8[u], u8[u]);
+    }
+#pragma unroll 1
+    for (int s = 8 * b + part; s < 8 * b + 8; s += parts) {
+      if (!__any(8 * s < mine)) break;
+      float us;
+      if (parts == 1) {
+        us = u8[0];
+#pragma unroll
+        for (int u = 0; u < 7; ++u) u8[u] = u8[u + 1];
+      } else {
+        us = fmaf(fit_w, needf * s_r8[s], b8[s]);
+      }
+      const bool want = s >= rest && want64 && 8 * s < mine && !(us < floor_key());
+      if (!__any(want)) continue;
+      float g[8], l[8];
+      load8(gp_row + 8 * s, g);
+      load8(pen_row + 8 * s, l);
+      // the nodes whose plan may put them on the list, by the bound of a single node
+      const SortedPlan* sp = sorted_plans + 8 * s;
+      const float reach = floor_key() + fminf(mu, 0.0f);
+      uint32_t maybe = 0, nodes_any = 0;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const bool may = want && 8 * s + u < mine && !(need > sp[u].reach) &&
+                         !(fmaf(fit_w, needf * sp[u].recip, g[u]) - fmaf(fmaxf(mu, 0.0f), sp[u].cost, l[u]) < reach);
+        maybe |= may ? 1u << u : 0u;
+        nodes_any |= __any(may) ? 1u << u : 0u;
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        if (!((nodes_any >> u) & 1u)) continue;
+        const int i = 8 * s + u;
+        const float fit = __double2float_rn(__dmul_rn(needd, s_recip[i]));
+        const float a = __fadd_rn(g[u], __fmul_rn(omg, fit));
+        const int j = __builtin_amdgcn_readfirstlane((int)s_order[i]);
+        // with mu >= 0 the fitness is at most the score with the plan's cheapest step
+        const float most = -__fsub_rn(a, __fadd_rn(l[u], __fmul_rn(mu, sp[u].cost)));
+        const bool go = ((maybe >> u) & 1u) &&
+                        !(mu >= 0.0f && (most > best.s[KT - 1] || (most == best.s[KT - 1] && j > best.n[KT - 1])));
+        if (!__any(go)) continue;
+        float cost;
+        if (plan_cost(plans + j, plan_steps, __dsub_rn(need, s_free[i]), go, cost) && go)
+          best.push_lex(-__fsub_rn(a, __fadd_rn(l[u], __fmul_rn(mu, norm01(cost, lo_d, hi_d)))), j);
+      }
+      if (parts > 1 && best.s[KT - 1] < INFINITY) atomicMax(floors, float_key(-best.s[KT - 1]));
+    }
+  }
+}
+
 // Stages in turn, one per lane; the sorted node records, their original
 // indices and the largest reciprocal of every block are staged in LDS once per workgroup. The best node
 // alone fits 96 registers, five wavefronts a SIMD (one register more: 49.6 against 46.9 us on 719,712 stages).
-template <int KT, bool kPlans>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KT == 1 && !kPlans ? 5 : 4)))
+enum : int { kNoPlans, kAlone, kShared };  // the last two with plans, kShared where several wavefronts take 64 stages
+template <int KT, int kForm>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KT == 1 && kForm == kNoPlans ? 5 : 4)))
 void fitness_walk_kernel(
     int64_t n, const int32_t* __restrict__ model_id, const int32_t* __restrict__ src_id,
     const int32_t* __restrict__ class_id, const double* __restrict__ kv_bytes, int32_t n_models, int32_t n_nodes,
@@ -394,6 +541,7 @@ void fitness_walk_kernel(
     const float* __restrict__ class_weights,
     const float* __restrict__ bounds, double rho, int32_t k, int parts, int merge_at, int32_t* __restrict__ node_idx,
     float* __restrict__ fitness) {
+  constexpr bool kPlans = kForm != kNoPlans;
   extern __shared__ __attribute__((aligned(16))) unsigned char s_raw[];
   double* s_free = reinterpret_cast<double*>(s_raw);
   double* s_recip = s_free + padded;
@@ -426,10 +574,10 @@ void fitness_walk_kernel(
   const float lo_d = bounds[4], hi_d = bounds[5];
   const float nd_fits = norm01(0.0f, lo_d, hi_d);   // normalised C_deg of a stage that fits
 
-  // with plans, `parts` wavefronts take the same 64 stages and a part each of their short pairs
+  // kShared: the first of `parts` wavefronts takes 64 stages, the others a part of the short pairs that it leaves
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int part = kPlans ? wave & (parts - 1) : 0, group = kPlans ? wave / parts : wave;
-  const int per_block = kPlans ? threads / parts : threads;
+  const int part = kForm == kShared ? wave & (parts - 1) : 0, group = kForm == kShared ? wave / parts : wave;
+  const int per_block = kForm == kShared ? threads / parts : threads;
   const int64_t step = (int64_t)gridDim.x * per_block;
   const int64_t rounds = (n + step - 1) / step;      // workgroup-uniform: whole wavefronts vote below
   for (int64_t it = 0; it < rounds; ++it) {
@@ -440,7 +588,7 @@ void fitness_walk_kernel(
     double need = NAN, needd = 0.0;
     float gamma = 0.0f, omg = 0.0f, lambda = 0.0f, mu = 0.0f;
     int cs = 0, cm = 0, m = 0;
-    if (stage < n) {
+    if (stage < n && part == 0) {
       const int32_t mi = model_id[stage], si = src_id[stage], ci = class_id[stage];
       ok = (uint32_t)mi < (uint32_t)n_models && (uint32_t)si < (uint32_t)n_src && (uint32_t)ci < (uint32_t)n_classes;
       if (ok) {
@@ -486,120 +634,84 @@ void fitness_walk_kernel(
 
     // ---- the nodes that fall short, by their plans
     if constexpr (kPlans) {
-      const int mine = need == need ? start : 0;   // need is not a number: no score is
-      // the parts tell each other their k-th best scores: that of the stage is not below any of them
-      uint32_t* floors = reinterpret_cast<uint32_t*>(s_raw + merge_at) + 64 * group + (tid & 63);
-      if (parts > 1) {
-        if (part == 0) *floors = 0u;
-        __syncthreads();
-      }
-      for (int b = 0; __any(64 * b < mine); ++b) {
-        if (parts > 1) {
-          const uint32_t told = *static_cast<volatile uint32_t*>(floors);
-          known = fmaxf(known, told ? key_float(told) : -INFINITY);
-        }
-        const float ub = fmaf(fit_w, needf * s_r64[b], b64[b]);
-        const bool want64 = 64 * b < mine && !(ub < floor_key());
-        if (!__any(want64)) continue;
-        // the eight sub-blocks' bounds in two reads (one read of its own for each that a part takes):
-        // these divergent reads are what a wavefront waits for
-        float u8[8], r8[8];
-        if (parts == 1) {
-          load8(b8 + 8 * b, u8);
-          load8(s_r8 + 8 * b, r8);
-#pragma unroll
-          for (int u = 0; u < 8; ++u) u8[u] = fmaf(fit_w, needf * r8[u], u8[u]);
-        }
-#pragma unroll 1
-        for (int s = 8 * b + part; s < 8 * b + 8; s += parts) {
-          if (!__any(8 * s < mine)) break;
-          float us;
-          if (parts == 1) {
-            us = u8[0];
-#pragma unroll
-            for (int u = 0; u < 7; ++u) u8[u] = u8[u + 1];
-          } else {
-            us = fmaf(fit_w, needf * s_r8[s], b8[s]);
-          }
-          const bool want = want64 && 8 * s < mine && !(us < floor_key());
-          if (!__any(want)) continue;
-          float g[8], l[8];
-          load8(gp_row + 8 * s, g);
-          load8(pen_row + 8 * s, l);
-          // the nodes whose plan may put them on the list, by the bound of a single node
-          const SortedPlan* sp = sorted_plans + 8 * s;
-          const float reach = floor_key() + fminf(mu, 0.0f);
-          uint32_t maybe = 0, nodes_any = 0;
-#pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            const bool may = want && 8 * s + u < mine && !(need > sp[u].reach) &&
-                             !(fmaf(fit_w, needf * sp[u].recip, g[u]) - fmaf(fmaxf(mu, 0.0f), sp[u].cost, l[u]) < reach);
-            maybe |= may ? 1u << u : 0u;
-            nodes_any |= __any(may) ? 1u << u : 0u;
-          }
-#pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            if (!((nodes_any >> u) & 1u)) continue;
-            const int i = 8 * s + u;
-            const float fit = __double2float_rn(__dmul_rn(needd, s_recip[i]));
-            const float a = __fadd_rn(g[u], __fmul_rn(omg, fit));
-            const int j = __builtin_amdgcn_readfirstlane((int)s_order[i]);
-            // with mu >= 0 the fitness is at most the score with the plan's cheapest step
-            const float most = -__fsub_rn(a, __fadd_rn(l[u], __fmul_rn(mu, sp[u].cost)));
-            const bool go = ((maybe >> u) & 1u) &&
-                            !(mu >= 0.0f && (most > best.s[KT - 1] || (most == best.s[KT - 1] && j > best.n[KT - 1])));
-            if (!__any(go)) continue;
-            const double R = __dsub_rn(need, s_free[i]);
-            const maestro_deg_plan* pl = plans + j;
-            const int ne = pl->n_engines;
-            int jp = 0;
-#pragma unroll
-            for (int e = 0; e < kRecSteps; ++e) jp += pl->freed[e] < R ? 1 : 0;
-            float cost = pl->cost[0];
-#pragma unroll
-            for (int e = 1; e < kRecSteps; ++e) cost = jp == e ? pl->cost[e] : cost;
-            bool found = jp < ne && jp < kRecSteps;
-            if (go && !found && ne > kRecSteps) {    // the steps past the record: the first freed >= R
-              const maestro_plan_step* st = plan_steps + pl->first_step;
-              int lo = kRecSteps, hi = ne;
-              while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (st[mid].freed < R) lo = mid + 1;
-                else hi = mid;
-              }
-              found = lo < ne;
-              if (found) cost = st[lo].cost;
+      int mine = need == need ? start : 0;   // need is not a number: no score is
+      int left = kForm == kShared ? kShortShared : kShortAlone, rest = -1;
+      if (part == 0)
+        for (int b = 0; rest < 0 && __any(64 * b < mine); ++b) {
+          const float ub = fmaf(fit_w, needf * s_r64[b], b64[b]);
+          const bool want64 = 64 * b < mine && !(ub < floor_key());
+          if (!__any(want64)) continue;
+          for (int s = 8 * b; s < 8 * b + 8; ++s) {
+            if (!__any(8 * s < mine)) break;
+            const float u8 = fmaf(fit_w, needf * s_r8[s], b8[s]);
+            const bool want = want64 && 8 * s < mine && !(u8 < floor_key());
+            if (!__any(want)) continue;
+            if (left-- == 0) {
+              rest = s;
+              break;
             }
-            if (go && found)
-              best.push_lex(-__fsub_rn(a, __fadd_rn(l[u], __fmul_rn(mu, norm01(cost, lo_d, hi_d)))), j);
+            float g[8], l[8];
+            load8(gp_row + 8 * s, g);
+            load8(pen_row + 8 * s, l);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+              const int i = 8 * s + u;
+              const float fit = __double2float_rn(__dmul_rn(needd, s_recip[i]));
+              const float a = __fadd_rn(g[u], __fmul_rn(omg, fit));
+              // with mu >= 0 the fitness is at most the score with C_deg normalised to 0
+              const bool go = want && i < mine && !(mu >= 0.0f && -__fsub_rn(a, l[u]) > best.s[KT - 1]);
+              if (!__any(go)) continue;
+              const int j = __builtin_amdgcn_readfirstlane((int)s_order[i]);
+              float cost;
+              if (plan_cost(plans + j, plan_steps, __dsub_rn(need, s_free[i]), go, cost) && go)
+                best.push_lex(-__fsub_rn(a, __fadd_rn(l[u], __fmul_rn(mu, norm01(cost, lo_d, hi_d)))), j);
+            }
           }
-          if (parts > 1 && best.s[KT - 1] < INFINITY) atomicMax(floors, float_key(-best.s[KT - 1]));
         }
-      }
-    }
-
-    if constexpr (kPlans) {
-      if (parts > 1) {                   // the parts' lists meet in the first one's wavefront
-        constexpr int kSlots = 2;        // groups of parts at a time: little LDS beside the nodes
-        float* m_key = reinterpret_cast<float*>(s_raw + merge_at) + threads / parts;
+      if constexpr (kForm == kShared) {
+        uint32_t* floors = reinterpret_cast<uint32_t*>(s_raw + merge_at) + 64 * group + (tid & 63);
+        // two sets in turn: a set is written again only behind the next stages' barrier
+        int32_t* rests = reinterpret_cast<int32_t*>(s_raw + merge_at) + per_block + (it & 1) * kMaxGroups;
+        float* m_key = reinterpret_cast<float*>(s_raw + merge_at) + per_block + 2 * kMaxGroups;
         int32_t* m_node = reinterpret_cast<int32_t*>(m_key + kSlots * KT * 64);
-        for (int g0 = 0; g0 * parts < (threads >> 6); g0 += kSlots)
-          for (int p = 1; p < parts; ++p) {
-            const bool mine = group >= g0 && group < g0 + kSlots;
-            const int at = (group - g0) * KT * 64 + (tid & 63);
-            if (mine && part == p)
+        uint16_t* mines = reinterpret_cast<uint16_t*>(m_node + kSlots * KT * 64) + 64 * group + (tid & 63);
+        if (part == 0) {
+          *floors = best.s[KT - 1] < INFINITY ? float_key(-best.s[KT - 1]) : 0u;
+          *mines = (uint16_t)mine;
+          rests[group] = rest;
+        }
+        __syncthreads();
+        bool any = false;                // workgroup-uniform
+        for (int g = 0; g * parts < (threads >> 6); ++g) any |= rests[g] >= 0;
+        if (any) {
+          rest = rests[group];
+          mine = *mines;
+          if (rest >= 0)
+            short_pass<KT>(best, stage, mine, rest, part, parts, floors, model_id, src_id, class_id, kv_bytes, n_models,
+                           n_src, padded, row, s_free, s_recip, s_r8, s_r64, s_order, gp, pen, bound, sorted_plans, plans,
+                           plan_steps, class_weights, rho, lo_d, hi_d);
+          // the parts' lists meet in the first one's wavefront
+          for (int g0 = 0; g0 * parts < (threads >> 6); g0 += kSlots)
+            for (int p = 1; p < parts; ++p) {
+              const bool slot = group >= g0 && group < g0 + kSlots;
+              const int at = (group - g0) * KT * 64 + (tid & 63);
+              if (slot && part == p)
 #pragma unroll
-              for (int i = 0; i < KT; ++i) {
-                m_key[at + 64 * i] = best.s[i];
-                m_node[at + 64 * i] = best.n[i];
-              }
-            __syncthreads();
-            if (mine && part == 0)
+                for (int i = 0; i < KT; ++i) {
+                  m_key[at + 64 * i] = best.s[i];
+                  m_node[at + 64 * i] = best.n[i];
+                }
+              __syncthreads();
+              if (slot && part == 0)
 #pragma unroll
-              for (int i = 0; i < KT; ++i) best.push_lex(m_key[at + 64 * i], m_node[at + 64 * i]);
-            __syncthreads();
-          }
-        ok = ok && part == 0;
+                for (int i = 0; i < KT; ++i) best.push_lex(m_key[at + 64 * i], m_node[at + 64 * i]);
+              __syncthreads();
+            }
+        }
+      } else if (rest >= 0) {
+        short_pass<KT>(best, stage, mine, rest, 0, 1, nullptr, model_id, src_id, class_id, kv_bytes, n_models, n_src,
+                       padded, row, s_free, s_recip, s_r8, s_r64, s_order, gp, pen, bound, sorted_plans, plans, plan_steps,
+                       class_weights, rho, lo_d, hi_d);
       }
     }
 
@@ -790,10 +902,17 @@ void fitness_walk_kernel(
   }
 }
 
-size_t walk_lds_bytes(int32_t padded) {
+constexpr size_t walk_lds_bytes(int32_t padded) {
   return (size_t)padded * (2 * sizeof(double) + sizeof(uint16_t)) + (size_t)(padded / 8) * sizeof(float) +
          (size_t)(((padded >> 6) + 3) & ~3) * sizeof(float);
 }
+// beside it where wavefronts share: floors and counts of short nodes, the resume points, the lists that meet
+constexpr size_t share_lds_bytes(int kt, int threads, int parts) {
+  return threads / parts * (sizeof(uint32_t) + sizeof(uint16_t)) + 2 * kMaxGroups * sizeof(int32_t) +
+         kSlots * kt * 64 * (sizeof(float) + sizeof(int32_t));
+}
+// two workgroups a CU (one: 53 against 38 us for 131,072 stages)
+static_assert(((walk_lds_bytes(kMaxNodes) + 15) & ~(size_t)15) + share_lds_bytes(4, kThreads, 2) <= 160 * 1024 / 2, "LDS");
 
 }  // namespace
 
@@ -888,22 +1007,23 @@ maestro_status launch_route_fitness_pruned(int64_t n, const int32_t* model_id, c
   const FitnessGrid shape = fitness_grid(n, t.padded, plans != nullptr, cus);
   const dim3 grid((unsigned)shape.blocks);
   const int threads = shape.threads;
-#define MAESTRO_FITW(KT, PL)                                                                                          \
+#define MAESTRO_FITW(KT, FORM)                                                                                          \
   do {                                                                                                                \
     const size_t staged = (walk_lds_bytes(t.padded) + 15) & ~(size_t)15;                                              \
-    const size_t lds = staged + (shape.parts > 1 ? 2 * KT * 64 * 8 + threads / shape.parts * 4 : 0);                  \
-    if (lds > 65536 && hipFuncSetAttribute(reinterpret_cast<const void*>(&fitness_walk_kernel<KT, PL>),               \
+    const size_t lds = staged + (shape.parts > 1 ? share_lds_bytes(KT, threads, shape.parts) : 0);                    \
+    if (lds > 65536 && hipFuncSetAttribute(reinterpret_cast<const void*>(&fitness_walk_kernel<KT, FORM>),               \
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)       \
       return MAESTRO_ERR_LAUNCH;                                                                                      \
-    fitness_walk_kernel<KT, PL><<<grid, dim3(threads), lds, stream>>>(                                               \
+    fitness_walk_kernel<KT, FORM><<<grid, dim3(threads), lds, stream>>>(                                               \
         n, model_id, src_id, class_id, kv_bytes, n_models, n_nodes, n_src, n_classes, t.padded, t.row, nodes, order,  \
         gp, pen, bound, t.ends, gp_top, pen_low, lowest, sorted_plans, plans, plan_steps, class_weights, bounds, rho, \
         k, shape.parts, (int)staged, node_idx, fitness);                                                             \
   } while (0)
-#define MAESTRO_FITW_KT(KT)               \
-  do {                                    \
-    if (plans) MAESTRO_FITW(KT, true);    \
-    else MAESTRO_FITW(KT, false);         \
+#define MAESTRO_FITW_KT(KT)                                \
+  do {                                                     \
+    if (!plans) MAESTRO_FITW(KT, kNoPlans);                \
+    else if (shape.parts == 1) MAESTRO_FITW(KT, kAlone);   \
+    else MAESTRO_FITW(KT, kShared);                        \
   } while (0)
   if (k == 1) MAESTRO_FITW_KT(1);
   else if (k == 2) MAESTRO_FITW_KT(2);

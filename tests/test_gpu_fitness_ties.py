@@ -57,6 +57,10 @@ def _saturated(kw, kind):
     level = torch.randint(1, 6, (e,), generator=r, device="cuda", dtype=torch.int32)
     freed = torch.rand(e, generator=r, device="cuda", dtype=torch.float64) * (0.1 if kind == "fail" else 20) * GB
     cost = torch.rand(e, generator=r, device="cuda") * 900
+    if kind == "mixed":
+        kw["kv_bytes"][torch.arange(kw["kv_bytes"].shape[0], device="cuda") // 64 % 3 == 0] = 0.0
+        kw["free_bytes"][::5] = 1e6 * torch.rand(m, generator=torch.Generator(device="cuda").manual_seed(m),
+                                                 device="cuda", dtype=torch.float64)[::5]
     if kind == "same":
         kw = _idle(kw, "regions")
         kw["free_bytes"].fill_(1e6)
@@ -68,11 +72,12 @@ def _saturated(kw, kind):
     return kw
 
 
-@pytest.mark.parametrize("n,m,k", [(4_000, 2_049, 4), (8_192, 4_096, 1), (50_001, 2_049, 2), (100_003, 1_100, 1),
+@pytest.mark.parametrize("n,m,k", [(4_000, 2_049, 4), (8_192, 4_096, 1), (30_001, 2_049, 3), (50_001, 2_049, 2), (100_003, 1_100, 1),
                                    (70_000, 1_024, 4), (300_001, 600, 3)])
-@pytest.mark.parametrize("kind", ["empty", "same", "fail", "none"])
+@pytest.mark.parametrize("kind", ["empty", "same", "fail", "none", "mixed"])
 def test_short_of_room_everywhere_matches_every_pair(monkeypatch, n, m, k, kind):
-    # 8, 4, 2 and 1 wavefronts that share the short pairs of 64 stages; ragged last groups
+    # 8, 4, 2 and 1 wavefronts that share the short pairs of 64 stages; ragged last groups; "mixed": two groups
+    # of 64 stages in three short of room on every node, with headrooms that differ
     print(f"saturated m={m} n={n} k={k} {kind}", flush=True)
     for weights in (USUAL, ODD):
         kw = _saturated(_inputs(m + k, n, m, 16, 5, weights, 30.0, 10.0, True, False), kind)
