@@ -238,8 +238,8 @@ __device__ __forceinline__ int64_t chain_suffix(int64_t first, int64_t end, int6
   return rem_head;
 }
 
-// One block per sort tile, one workflow per thread; also writes the tile's counts of the
-// first digit. When the block's workflows span at most kStageCap stages (the usual case), the
+// One block per 1,024 workflows, one workflow per thread; with tiles of that size also writes the tile's
+// counts of the first digit (null counts: larger tiles, counted by radix_count_kernel). When the block's workflows span at most kStageCap stages (the usual case), the
 // stage latencies pass through LDS: quantised by a coalesced sweep over the block's stage
 // range, summed per chain from LDS, and the remaining times written back by a second coalesced
 // sweep. Longer ranges walk the chains in global memory directly.
@@ -287,7 +287,7 @@ __global__ __launch_bounds__(kTile) void chain_kernel(
   }
   keys[w] = ukey;
   vals[w] = (uint32_t)w | long_mark;
-  atomicAdd(&hist[ukey & (kBuckets - 1)], 1u);
+  if (counts) atomicAdd(&hist[ukey & (kBuckets - 1)], 1u);
   __syncthreads();
   if (counts && tid < kBuckets) counts[(int64_t)tile * kBuckets + tid] = hist[tid];
   if (staged && remaining_us) {
