@@ -23,7 +23,7 @@
 // 47 against 42 us on 512 nodes whose bounds prune well.)
 //
 // Three launches: ranks of the headrooms and the sorted node records; the penalty, proximity and
-// bound tables; the stages.
+// bound tables and the sorted plans; the stages.
 // What bounds it: scoring every pair costs 14 vector instructions a pair; here a lane reads up to
 // M / 256 float4 of bounds, visits one to five sub-blocks of 8 nodes, and a wavefront waits for
 // the lane that visits most, each visit two dependent rounds of divergent 16-byte reads. On 512
@@ -108,7 +108,7 @@ __device__ __forceinline__ uint64_t double_key(double d) {
 // on the scalar unit. 16 nodes per workgroup, so 4,096 nodes spread over 256 workgroups; the M^2
 // compares take 8 us there, a third of what a radix sort in one workgroup does. The wavefront then
 // writes the node's terms at its position: lane m norm(T_ready) of model m, lane s 1 - norm(RTT)
-// from source s, and norm(C_deg), or what its plan frees and costs at best.
+// from source s, and norm(C_deg).
 constexpr int kRankThreads = 1024;
 __global__ __launch_bounds__(kRankThreads) void fitness_rank_kernel(int32_t n_nodes, int32_t padded,
                                                                     int32_t n_models, int32_t n_src,
@@ -118,31 +118,17 @@ __global__ __launch_bounds__(kRankThreads) void fitness_rank_kernel(int32_t n_no
                                                                     const uint64_t* __restrict__ resident_mask,
                                                                     const float* __restrict__ act_matrix,
                                                                     const float* __restrict__ deg_ms,
-                                                                    const maestro_deg_plan* __restrict__ plans,
-                                                                    const maestro_plan_step* __restrict__ plan_steps,
                                                                     const float* __restrict__ rtt_ms,
                                                                     const float* __restrict__ bounds,
                                                                     SortedNode* __restrict__ nodes,
-                                                                    SortedPlan* __restrict__ sorted_plans,
                                                                     uint16_t* __restrict__ order,
                                                                     float* __restrict__ tr, float* __restrict__ prox,
                                                                     float* __restrict__ nd) {
   __shared__ uint64_t s_key[kMaxNodes];
   const int tid = threadIdx.x, lane = tid & 63;
-  const int i = blockIdx.x * (kRankThreads / 64) + __builtin_amdgcn_readfirstlane(tid >> 6);
-  // the node's plan, read ahead of the keys
-  int32_t ne = 0, first = 0;
-  float cost = INFINITY;
-  double freed = 0.0;
-  if (plans && i < n_nodes) {
-    const maestro_deg_plan& pl = plans[i];
-    ne = pl.n_engines;
-    first = pl.first_step;
-    cost = pl.cost[lane & (kRecSteps - 1)];
-    freed = pl.freed[min(max(ne, 1), kRecSteps) - 1];
-  }
   for (int j = tid; j < padded; j += kRankThreads) s_key[j] = j < n_nodes ? double_key(free_bytes[j]) : ~0ull;
   __syncthreads();
+  const int i = blockIdx.x * (kRankThreads / 64) + (tid >> 6);
   if (i >= padded) return;
   if (i >= n_nodes) {                    // padding: admits nothing
     if (lane == 0) {
@@ -153,13 +139,6 @@ __global__ __launch_bounds__(kRankThreads) void fitness_rank_kernel(int32_t n_no
     if (lane < n_models) tr[(size_t)lane * padded + i] = 0.0f;
     if (lane < n_src) prox[(size_t)lane * padded + i] = 0.0f;
     return;
-  }
-  // the steps past the record, read ahead of the count
-  const maestro_plan_step* st = plan_steps + first;
-  float more = INFINITY;
-  if (ne > kRecSteps) {
-    if (kRecSteps + lane < ne) more = st[kRecSteps + lane].cost;
-    freed = st[ne - 1].freed;
   }
   const uint64_t key = s_key[i];
   // 64-node groups before the node's own count equal keys too, those after it do not (padding
@@ -180,19 +159,6 @@ __global__ __launch_bounds__(kRankThreads) void fitness_rank_kernel(int32_t n_no
     nodes[rank] = SortedNode{fr, frf > 0.0f ? __ddiv_rn(1.0, (double)frf) : 0.0};
     order[rank] = (uint16_t)i;
     nd[rank] = deg_ms ? norm01(deg_ms[i], bounds[4], bounds[5]) : 0.0f;
-  }
-  if (plans) {
-    cost = fminf(lane < min(ne, kRecSteps) ? cost : INFINITY, more);
-    for (int e = kRecSteps + 64 + lane; e < ne; e += 64) cost = fminf(cost, st[e].cost);
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) cost = fminf(cost, __shfl_xor(cost, off));
-    if (lane == 0) {
-      // past every rounding of R_need - headroom, which a stage compares with the freed bytes
-      const double fr = free_bytes[i], slack = (fabs(fr) + fabs(freed)) * 0x1p-50;
-      const float frf = __double2float_rn(fr);
-      sorted_plans[rank] = SortedPlan{ne > 0 ? fr + freed + slack : -INFINITY, norm01(cost, bounds[4], bounds[5]),
-                                      frf > 0.0f ? __double2float_ru(__ddiv_rn(1.0, (double)frf)) : 0.0f};
-    }
   }
   if (lane < n_models) {
     const float q = queue_ms[i];
@@ -223,12 +189,58 @@ __device__ __forceinline__ void store8(float* __restrict__ p, const float (&v)[8
 // sub-blocks ahead of the pass, more than the pass itself over up to 16 blocks when one node is wanted.
 __host__ __device__ constexpr bool early_end(int32_t padded) { return padded > 1024; }
 
+// What the plans of nodes in sorted order free and cost at best, eight lanes a node: lane e takes step e of the
+// record and every eighth step past it. Workgroup w of n_w.
+__device__ __forceinline__ void sort_plans(int w, int n_w, int32_t n_nodes, const SortedNode* __restrict__ nodes,
+                                           const uint16_t* __restrict__ order,
+                                           const maestro_deg_plan* __restrict__ plans,
+                                           const maestro_plan_step* __restrict__ plan_steps, float lo_d, float hi_d,
+                                           SortedPlan* __restrict__ sorted_plans) {
+  static_assert(kRecSteps == 8, "a step a lane");
+  const int per_w = blockDim.x >> 3, e = threadIdx.x & 7;
+  for (int p = w * per_w + (int)(threadIdx.x >> 3); p < n_nodes; p += n_w * per_w) {   // the same for the eight lanes
+    const maestro_deg_plan& pl = plans[order[p]];
+    const SortedNode nd = nodes[p];
+    const int ne = pl.n_engines;
+    double freed = __shfl(pl.freed[e], min(max(ne, 1), kRecSteps) - 1, 8);
+    float cost = pl.cost[e];
+    if (e >= ne) cost = INFINITY;
+    if (ne > kRecSteps) {
+      const maestro_plan_step* st = plan_steps + pl.first_step;
+      freed = st[ne - 1].freed;
+#pragma unroll 4
+      for (int q = kRecSteps + e; q < ne; q += 8) cost = fminf(cost, st[q].cost);
+    }
+#pragma unroll
+    for (int off = 1; off < 8; off <<= 1) cost = fminf(cost, __shfl_xor(cost, off));
+    // past every rounding of R_need - headroom, which a stage compares with the freed bytes
+    const double slack = (fabs(nd.free) + fabs(freed)) * 0x1p-50;
+    if (e == 0)
+      sorted_plans[p] = SortedPlan{ne > 0 ? nd.free + freed + slack : -INFINITY, norm01(cost, lo_d, hi_d),
+                                   __double2float_ru(nd.recip)};
+  }
+}
+
+// Rows of workgroups beside those of the classes that take the plans: the reads of a plan, one after another,
+// take as long as a table's. (By the rank kernel, which leaves nothing idle: 0.3 us more on 512 nodes, 1.0 on 4,096.)
+constexpr int kPlanRows = 8;
 template <bool kPlans>
 __global__ __launch_bounds__(kMaxNodes / 8) void fitness_tables_kernel(
     int32_t n_models, int32_t n_nodes, int32_t n_src, int32_t padded, int32_t row, const float* __restrict__ tr,
     const float* __restrict__ prox, const float* __restrict__ nd, const float* __restrict__ class_weights,
     const uint16_t* __restrict__ order, float* __restrict__ gp, float* __restrict__ pen, float* __restrict__ bound,
-    int32_t ends, float* __restrict__ gp_top, float* __restrict__ pen_low, uint16_t* __restrict__ lowest) {
+    int32_t ends, float* __restrict__ gp_top, float* __restrict__ pen_low, uint16_t* __restrict__ lowest,
+    const SortedNode* __restrict__ nodes, const maestro_deg_plan* __restrict__ plans,
+    const maestro_plan_step* __restrict__ plan_steps, const float* __restrict__ bounds,
+    SortedPlan* __restrict__ sorted_plans) {
+  if constexpr (kPlans) {                // whole workgroups
+    const int r = (int)blockIdx.y - ((int)gridDim.y - kPlanRows);
+    if (r >= 0) {
+      sort_plans((r * gridDim.z + blockIdx.z) * gridDim.x + blockIdx.x, kPlanRows * gridDim.z * gridDim.x, n_nodes, nodes,
+                 order, plans, plan_steps, bounds[4], bounds[5], sorted_plans);
+      return;
+    }
+  }
   __shared__ float s_top[64];
   const int m = blockIdx.x, c = blockIdx.y;
   const int p0 = threadIdx.x * 8;        // blockDim.x is padded / 8
@@ -312,6 +324,78 @@ __global__ __launch_bounds__(kMaxNodes / 8) void fitness_tables_kernel(
 // than 2^-21 of it).
 constexpr float kSlack = 1.9073486328125e-06f;
 
+// Plans of a wavefront-uniform node, read by scalar loads. By vector loads, which the compiler takes where it
+// does not see that nothing writes there: 46.2 against 44.8 us on 582 nodes, 8,192 stages that are short of room on
+// all of 4,096 nodes 340 against 257.
+typedef const __attribute__((address_space(4))) maestro_deg_plan* ScalarPlans;
+typedef const __attribute__((address_space(4))) SortedPlan* ScalarSortedPlans;
+
+struct WalkArgs {
+  int64_t n;
+  const int32_t *model_id, *src_id, *class_id;
+  const double* kv_bytes;
+  int32_t n_models, n_nodes, n_src, n_classes, padded, row;
+  const SortedNode* nodes;
+  const uint16_t* order;
+  const float *gp, *pen, *bound;
+  int32_t ends;
+  const float *gp_top, *pen_low;
+  const uint16_t* lowest;
+  const SortedPlan* sorted_plans;
+  const maestro_deg_plan* plans;
+  const maestro_plan_step* plan_steps;
+  const float *class_weights, *bounds;
+  double rho;
+  int32_t k, parts, merge_at;
+  int32_t* node_idx;
+  float* fitness;
+};
+
+// The kernel's argument, read again where it is used: held from the kernel's start, the pointers of the passes
+// that few stages take (and with plans those of a round) fill the scalar registers, and the loops that every stage
+// takes spill to vector lanes. On 512 nodes 7% more vector instructions: 56.3 against 54.3 us with plans, 50.3
+// against 49.4 without.
+typedef const __attribute__((address_space(4))) WalkArgs* ColdArgs;
+__device__ __forceinline__ ColdArgs cold_args() {
+  ColdArgs p = (ColdArgs)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
+// What a round of stages reads. With plans it is read again for each round and for the round's end; without
+// them it fits the scalar registers (49.1 against 49.9 us on 512 nodes).
+struct RoundArgs {
+  int64_t n;
+  const int32_t *model_id, *src_id, *class_id;
+  const double* kv_bytes;
+  const float *class_weights, *gp, *pen, *bound;
+  int32_t n_models, n_src, n_classes, k;
+  double rho;
+  int32_t* node_idx;
+  float* fitness;
+};
+template <class Args>
+__device__ __forceinline__ RoundArgs round_args(Args a) {
+  return RoundArgs{a->n, a->model_id, a->src_id, a->class_id, a->kv_bytes, a->class_weights, a->gp, a->pen, a->bound,
+                   a->n_models, a->n_src, a->n_classes, a->k, a->rho, a->node_idx, a->fitness};
+}
+
+// Node records of a workgroup in LDS.
+struct WalkLds {
+  double *free, *recip;                  // [padded]
+  float *r8, *r64;                       // [padded / 8], [padded / 64, to a multiple of four]
+  uint16_t* order;                       // [padded]
+};
+__device__ __forceinline__ WalkLds walk_lds(unsigned char* raw, int32_t padded) {
+  WalkLds l;
+  l.free = reinterpret_cast<double*>(raw);
+  l.recip = l.free + padded;
+  l.r8 = reinterpret_cast<float*>(l.recip + padded);
+  l.r64 = l.r8 + (padded >> 3);
+  l.order = reinterpret_cast<uint16_t*>(l.r64 + (((padded >> 6) + 3) & ~3));
+  return l;
+}
+
 // The rest of a stage whose k-th best score so far ties with the bounds of blocks it has not visited:
 // all its blocks again, in sorted order. A block is left out when its bound is below that score, or when
 // no node of it can enter the list: its scores are at most the one of the block's largest proximity
@@ -323,13 +407,20 @@ constexpr float kSlack = 1.9073486328125e-06f;
 // takes, whose registers decide how many wavefronts run (tests inside those loops: 51 against 48 us on
 // 719,712 stages without ties), so the stage's inputs are read again.
 template <int KT, bool kPlans>
-__device__ __forceinline__ void tie_pass(
-    TopK<KT>& best, int64_t stage, int start, const int32_t* __restrict__ model_id, const int32_t* __restrict__ src_id,
-    const int32_t* __restrict__ class_id, const double* __restrict__ kv_bytes, int32_t n_models, int32_t n_nodes,
-    int32_t n_src, int32_t padded, int32_t row, const double* s_recip, const float* s_r8, const float* s_r64,
-    const uint16_t* s_order, const float* __restrict__ gp, const float* __restrict__ pen, const float* __restrict__ bound,
-    int32_t ends, const float* __restrict__ gp_top, const float* __restrict__ pen_low,
-    const uint16_t* __restrict__ lowest, const float* __restrict__ class_weights, double rho, float nd_fits) {
+__device__ __forceinline__ void tie_pass(TopK<KT>& best, int64_t stage, int start, unsigned char* raw) {
+  const ColdArgs args = cold_args();
+  const int32_t n_models = args->n_models, n_nodes = args->n_nodes, n_src = args->n_src, padded = args->padded,
+                row = args->row, ends = args->ends;
+  const int32_t *model_id = args->model_id, *src_id = args->src_id, *class_id = args->class_id;
+  const double *kv_bytes = args->kv_bytes, rho = args->rho;
+  const float *gp = args->gp, *pen = args->pen, *bound = args->bound, *gp_top = args->gp_top,
+              *pen_low = args->pen_low, *class_weights = args->class_weights, *bounds = args->bounds;
+  const uint16_t* lowest = args->lowest;
+  const float nd_fits = norm01(0.0f, bounds[4], bounds[5]);
+  const WalkLds lds = walk_lds(raw, padded);
+  const double* s_recip = lds.recip;
+  const float *s_r8 = lds.r8, *s_r64 = lds.r64;
+  const uint16_t* s_order = lds.order;
   asm volatile("" : "+v"(stage));          // not the values held since the stage's start
   const int32_t m = model_id[stage], si = src_id[stage], ci = class_id[stage];
   const double need = (rho == 0.0) ? kv_bytes[stage] : __dmul_rn(kv_bytes[stage], 1.0 + rho);
@@ -399,9 +490,8 @@ __device__ __forceinline__ void tie_pass(
 
 // C_deg of the shortfall R by one node's plan (wavefront-uniform): the cost of the first step that has
 // freed R; false where none has. go: the lanes that need it.
-__device__ __forceinline__ bool plan_cost(const maestro_deg_plan* __restrict__ pl,
-                                          const maestro_plan_step* __restrict__ plan_steps, double R, bool go,
-                                          float& cost) {
+__device__ __forceinline__ bool plan_cost(ScalarPlans pl, const maestro_plan_step* __restrict__ plan_steps, double R,
+                                          bool go, float& cost) {
   const int ne = pl->n_engines;
   int jp = 0;
 #pragma unroll
@@ -429,15 +519,21 @@ __device__ __forceinline__ bool plan_cost(const maestro_deg_plan* __restrict__ p
 // any of them). A node is looked up only if the cheapest step of its plan can enter the list and all its
 // steps free enough. `mine`: the stage's short nodes, 0 without a stage. Reads the stage again, as tie_pass.
 template <int KT>
-__device__ __forceinline__ void short_pass(
-    TopK<KT>& best, int64_t stage, int mine, int rest, int part, int parts, uint32_t* floors,
-    const int32_t* __restrict__ model_id, const int32_t* __restrict__ src_id, const int32_t* __restrict__ class_id,
-    const double* __restrict__ kv_bytes, int32_t n_models, int32_t n_src, int32_t padded, int32_t row,
-    const double* s_free, const double* s_recip, const float* s_r8, const float* s_r64, const uint16_t* s_order,
-    const float* __restrict__ gp, const float* __restrict__ pen, const float* __restrict__ bound,
-    const SortedPlan* __restrict__ sorted_plans, const maestro_deg_plan* __restrict__ plans,
-    const maestro_plan_step* __restrict__ plan_steps, const float* __restrict__ class_weights, double rho, float lo_d,
-    float hi_d) {
+__device__ __forceinline__ void short_pass(TopK<KT>& best, int64_t stage, int mine, int rest, int part, int parts,
+                                           uint32_t* floors, unsigned char* raw) {
+  const ColdArgs args = cold_args();
+  const int32_t n_models = args->n_models, n_src = args->n_src, padded = args->padded, row = args->row;
+  const int32_t *model_id = args->model_id, *src_id = args->src_id, *class_id = args->class_id;
+  const double *kv_bytes = args->kv_bytes, rho = args->rho;
+  const float *gp = args->gp, *pen = args->pen, *bound = args->bound, *class_weights = args->class_weights;
+  const ScalarPlans plans = (ScalarPlans)args->plans;
+  const ScalarSortedPlans sorted_plans = (ScalarSortedPlans)args->sorted_plans;
+  const maestro_plan_step* plan_steps = args->plan_steps;
+  const float lo_d = args->bounds[4], hi_d = args->bounds[5];
+  const WalkLds lds = walk_lds(raw, padded);
+  const double *s_free = lds.free, *s_recip = lds.recip;
+  const float *s_r8 = lds.r8, *s_r64 = lds.r64;
+  const uint16_t* s_order = lds.order;
   asm volatile("" : "+v"(stage));
   int32_t m = 0, si = 0, ci = 0;
   double need = 0.0;
@@ -493,7 +589,7 @@ __device__ __forceinline__ void short_pass(
       load8(gp_row + 8 * s, g);
       load8(pen_row + 8 * s, l);
       // the nodes whose plan may put them on the list, by the bound of a single node
-      const SortedPlan* sp = sorted_plans + 8 * s;
+      const ScalarSortedPlans sp = sorted_plans + 8 * s;
       const float reach = floor_key() + fminf(mu, 0.0f);
       uint32_t maybe = 0, nodes_any = 0;
 #pragma unroll
@@ -530,25 +626,19 @@ __device__ __forceinline__ void short_pass(
 enum : int { kNoPlans, kAlone, kShared };  // the last two with plans, kShared where several wavefronts take 64 stages
 template <int KT, int kForm>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KT == 1 && kForm == kNoPlans ? 5 : 4)))
-void fitness_walk_kernel(
-    int64_t n, const int32_t* __restrict__ model_id, const int32_t* __restrict__ src_id,
-    const int32_t* __restrict__ class_id, const double* __restrict__ kv_bytes, int32_t n_models, int32_t n_nodes,
-    int32_t n_src, int32_t n_classes, int32_t padded, int32_t row, const SortedNode* __restrict__ nodes,
-    const uint16_t* __restrict__ order, const float* __restrict__ gp, const float* __restrict__ pen,
-    const float* __restrict__ bound, int32_t ends, const float* __restrict__ gp_top, const float* __restrict__ pen_low,
-    const uint16_t* __restrict__ lowest, const SortedPlan* __restrict__ sorted_plans,
-    const maestro_deg_plan* __restrict__ plans, const maestro_plan_step* __restrict__ plan_steps,
-    const float* __restrict__ class_weights,
-    const float* __restrict__ bounds, double rho, int32_t k, int parts, int merge_at, int32_t* __restrict__ node_idx,
-    float* __restrict__ fitness) {
+void fitness_walk_kernel(const WalkArgs args) {
   constexpr bool kPlans = kForm != kNoPlans;
+  const int32_t n_nodes = args.n_nodes, padded = args.padded, row = args.row, parts = args.parts;
+  const SortedNode* __restrict__ nodes = args.nodes;
+  const uint16_t* __restrict__ order = args.order;
+  const float* __restrict__ bounds = args.bounds;
+  RoundArgs in = round_args(&args);
   extern __shared__ __attribute__((aligned(16))) unsigned char s_raw[];
-  double* s_free = reinterpret_cast<double*>(s_raw);
-  double* s_recip = s_free + padded;
-  float* s_r8 = reinterpret_cast<float*>(s_recip + padded);       // [padded / 8]
-  float* s_r64 = s_r8 + (padded >> 3);                            // [padded / 64, to a multiple of four]
+  const WalkLds lds = walk_lds(s_raw, padded);
+  double *s_free = lds.free, *s_recip = lds.recip;
+  float *s_r8 = lds.r8, *s_r64 = lds.r64;
+  uint16_t* s_order = lds.order;
   const int blocks = padded >> 6, blocks4 = (blocks + 3) & ~3;
-  uint16_t* s_order = reinterpret_cast<uint16_t*>(s_r64 + blocks4);
   const int tid = threadIdx.x, threads = blockDim.x;
   for (int i = tid; i < padded; i += threads) {
     const SortedNode nd = nodes[i];
@@ -579,20 +669,32 @@ void fitness_walk_kernel(
   const int part = kForm == kShared ? wave & (parts - 1) : 0, group = kForm == kShared ? wave / parts : wave;
   const int per_block = kForm == kShared ? threads / parts : threads;
   const int64_t step = (int64_t)gridDim.x * per_block;
-  const int64_t rounds = (n + step - 1) / step;      // workgroup-uniform: whole wavefronts vote below
+  const int64_t rounds = (args.n + step - 1) / step;   // workgroup-uniform: whole wavefronts vote below
   for (int64_t it = 0; it < rounds; ++it) {
     const int64_t stage = it * step + (int64_t)blockIdx.x * per_block + 64 * group + (tid & 63);
+    ScalarPlans plans = nullptr;
+    const maestro_plan_step* plan_steps = nullptr;
+    if constexpr (kPlans) {
+      const ColdArgs again = cold_args();
+      in = round_args(again);
+      plans = (ScalarPlans)again->plans;
+      plan_steps = again->plan_steps;
+    }
+    const int32_t n_models = in.n_models, n_src = in.n_src;
+    const float* class_weights = in.class_weights;
     TopK<KT> best;                                   // keys are -fitness: the smallest key is the best node
     best.init();
     bool ok = false;
     double need = NAN, needd = 0.0;
     float gamma = 0.0f, omg = 0.0f, lambda = 0.0f, mu = 0.0f;
     int cs = 0, cm = 0, m = 0;
-    if (stage < n && part == 0) {
-      const int32_t mi = model_id[stage], si = src_id[stage], ci = class_id[stage];
-      ok = (uint32_t)mi < (uint32_t)n_models && (uint32_t)si < (uint32_t)n_src && (uint32_t)ci < (uint32_t)n_classes;
+    if (stage < in.n && part == 0) {
+      const int32_t mi = in.model_id[stage], si = in.src_id[stage], ci = in.class_id[stage];
+      ok = (uint32_t)mi < (uint32_t)n_models && (uint32_t)si < (uint32_t)n_src &&
+           (uint32_t)ci < (uint32_t)in.n_classes;
       if (ok) {
-        need = (rho == 0.0) ? kv_bytes[stage] : __dmul_rn(kv_bytes[stage], 1.0 + rho);
+        const double kv = in.kv_bytes[stage], rho = in.rho;
+        need = (rho == 0.0) ? kv : __dmul_rn(kv, 1.0 + rho);
         needd = (double)__double2float_rn(need);
         gamma = class_weights[3 * ci];
         lambda = class_weights[3 * ci + 1];
@@ -603,9 +705,9 @@ void fitness_walk_kernel(
         m = mi;
       }
     }
-    const float* gp_row = gp + (size_t)cs * padded;
-    const float* pen_row = pen + (size_t)cm * padded;
-    const float* b64 = bound + ((size_t)cs * n_models + m) * row;
+    const float* gp_row = in.gp + (size_t)cs * padded;
+    const float* pen_row = in.pen + (size_t)cm * padded;
+    const float* b64 = in.bound + ((size_t)cs * n_models + m) * row;
     const float* b8 = b64 + blocks4;
     const float* after = b8 + (padded >> 3);
     // bound of a block: fit_w * min(1, needf * largest reciprocal) + its table entry; a
@@ -669,10 +771,10 @@ void fitness_walk_kernel(
           }
         }
       if constexpr (kForm == kShared) {
-        uint32_t* floors = reinterpret_cast<uint32_t*>(s_raw + merge_at) + 64 * group + (tid & 63);
+        uint32_t* floors = reinterpret_cast<uint32_t*>(s_raw + args.merge_at) + 64 * group + (tid & 63);
         // two sets in turn: a set is written again only behind the next stages' barrier
-        int32_t* rests = reinterpret_cast<int32_t*>(s_raw + merge_at) + per_block + (it & 1) * kMaxGroups;
-        float* m_key = reinterpret_cast<float*>(s_raw + merge_at) + per_block + 2 * kMaxGroups;
+        int32_t* rests = reinterpret_cast<int32_t*>(s_raw + args.merge_at) + per_block + (it & 1) * kMaxGroups;
+        float* m_key = reinterpret_cast<float*>(s_raw + args.merge_at) + per_block + 2 * kMaxGroups;
         int32_t* m_node = reinterpret_cast<int32_t*>(m_key + kSlots * KT * 64);
         uint16_t* mines = reinterpret_cast<uint16_t*>(m_node + kSlots * KT * 64) + 64 * group + (tid & 63);
         if (part == 0) {
@@ -687,9 +789,7 @@ void fitness_walk_kernel(
           rest = rests[group];
           mine = *mines;
           if (rest >= 0)
-            short_pass<KT>(best, stage, mine, rest, part, parts, floors, model_id, src_id, class_id, kv_bytes, n_models,
-                           n_src, padded, row, s_free, s_recip, s_r8, s_r64, s_order, gp, pen, bound, sorted_plans, plans,
-                           plan_steps, class_weights, rho, lo_d, hi_d);
+            short_pass<KT>(best, stage, mine, rest, part, parts, floors, s_raw);
           // the parts' lists meet in the first one's wavefront
           for (int g0 = 0; g0 * parts < (threads >> 6); g0 += kSlots)
             for (int p = 1; p < parts; ++p) {
@@ -709,9 +809,7 @@ void fitness_walk_kernel(
             }
         }
       } else if (rest >= 0) {
-        short_pass<KT>(best, stage, mine, rest, 0, 1, nullptr, model_id, src_id, class_id, kv_bytes, n_models, n_src,
-                       padded, row, s_free, s_recip, s_r8, s_r64, s_order, gp, pen, bound, sorted_plans, plans, plan_steps,
-                       class_weights, rho, lo_d, hi_d);
+        short_pass<KT>(best, stage, mine, rest, 0, 1, nullptr, s_raw);
       }
     }
 
@@ -883,19 +981,17 @@ void fitness_walk_kernel(
       }
     }
 
-    if (ties > kTies)
-      tie_pass<KT, kPlans>(best, stage, start, model_id, src_id, class_id, kv_bytes, n_models, n_nodes, n_src, padded, row,
-                           s_recip, s_r8, s_r64, s_order, gp, pen, bound, ends, gp_top, pen_low, lowest, class_weights,
-                           rho, nd_fits);
+    if (ties > kTies) tie_pass<KT, kPlans>(best, stage, start, s_raw);
 
-    if (stage < n && part == 0) {
+    if constexpr (kPlans) in = round_args(cold_args());
+    if (stage < in.n && part == 0) {
 #pragma unroll
       for (int i = 0; i < KT; ++i) {
-        if (i < k) {
+        if (i < in.k) {
           const int32_t node = best.n[i] < 0 ? best.n[i] ^ (int32_t)0x80000000 : best.n[i];
           const bool some = node != kNoNode;
-          node_idx[stage * k + i] = some ? node : -1;
-          fitness[stage * k + i] = some ? -best.s[i] : -INFINITY;
+          in.node_idx[stage * in.k + i] = some ? node : -1;
+          in.fitness[stage * in.k + i] = some ? -best.s[i] : -INFINITY;
         }
       }
     }
@@ -993,17 +1089,14 @@ maestro_status launch_route_fitness_pruned(int64_t n, const int32_t* model_id, c
   uint16_t* lowest = reinterpret_cast<uint16_t*>(ws + t.lowest);
   fitness_rank_kernel<<<dim3((unsigned)((t.padded + 15) / 16)), dim3(kRankThreads), 0, stream>>>(
       n_nodes, t.padded, n_models, n_src, free_bytes, queue_ms, act_ms, resident_mask, act_matrix,
-      plans ? nullptr : deg_ms, plans, plan_steps, rtt_ms, bounds, nodes, sorted_plans, order, tr, prox, nd);
-  const dim3 tgrid((unsigned)n_models, (unsigned)n_classes, (unsigned)(t.padded > 512 ? n_src : 1));
+      plans ? nullptr : deg_ms, rtt_ms, bounds, nodes, order, tr, prox, nd);
+  const dim3 tgrid((unsigned)n_models, (unsigned)(n_classes + (plans ? kPlanRows : 0)),
+                   (unsigned)(t.padded > 512 ? n_src : 1));
   const dim3 tblock((unsigned)(t.padded / 8));
-  if (plans)
-    fitness_tables_kernel<true><<<tgrid, tblock, 0, stream>>>(n_models, n_nodes, n_src, t.padded, t.row, tr,
-                                                                           prox, nd, class_weights, order, gp, pen, bound, t.ends, gp_top, pen_low,
-                                                                lowest);
-  else
-    fitness_tables_kernel<false><<<tgrid, tblock, 0, stream>>>(n_models, n_nodes, n_src, t.padded, t.row, tr,
-                                                                            prox, nd, class_weights, order, gp, pen, bound, t.ends, gp_top, pen_low,
-                                                                lowest);
+  auto tables = plans ? fitness_tables_kernel<true> : fitness_tables_kernel<false>;
+  tables<<<tgrid, tblock, 0, stream>>>(n_models, n_nodes, n_src, t.padded, t.row, tr, prox, nd, class_weights, order, gp,
+                                       pen, bound, t.ends, gp_top, pen_low, lowest, nodes, plans, plan_steps, bounds,
+                                       sorted_plans);
   const FitnessGrid shape = fitness_grid(n, t.padded, plans != nullptr, cus);
   const dim3 grid((unsigned)shape.blocks);
   const int threads = shape.threads;
@@ -1015,9 +1108,9 @@ maestro_status launch_route_fitness_pruned(int64_t n, const int32_t* model_id, c
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)       \
       return MAESTRO_ERR_LAUNCH;                                                                                      \
     fitness_walk_kernel<KT, FORM><<<grid, dim3(threads), lds, stream>>>(                                               \
-        n, model_id, src_id, class_id, kv_bytes, n_models, n_nodes, n_src, n_classes, t.padded, t.row, nodes, order,  \
-        gp, pen, bound, t.ends, gp_top, pen_low, lowest, sorted_plans, plans, plan_steps, class_weights, bounds, rho, \
-        k, shape.parts, (int)staged, node_idx, fitness);                                                             \
+        WalkArgs{n, model_id, src_id, class_id, kv_bytes, n_models, n_nodes, n_src, n_classes, t.padded, t.row, nodes, \
+                 order, gp, pen, bound, t.ends, gp_top, pen_low, lowest, sorted_plans, plans, plan_steps,             \
+                 class_weights, bounds, rho, k, shape.parts, (int)staged, node_idx, fitness});                       \
   } while (0)
 #define MAESTRO_FITW_KT(KT)                                \
   do {                                                     \
