@@ -1,6 +1,6 @@
 """Slack ordering at the batch sizes where its launches change -- one workgroup up to 4,096 workflows
-(one, two or four keys a thread; beyond 1,024 up to 32,768 stages), 1,024-key tiles up to 131,072, group totals up to 1,024 tiles of
-4,096 keys, group scans beyond -- bit for bit against the oracle: coarse deadlines (many equal keys,
+(one, two or four keys a thread; beyond 1,024 up to 32,768 stages), 1,024-key tiles up to 131,072, group
+totals up to 1,024 tiles of 4,096 keys, group scans beyond -- bit for bit against the oracle: coarse deadlines (many equal keys,
 so that stability shows), cursors anywhere, infinite latencies, and long chains among short ones."""
 import numpy as np
 import pytest
@@ -44,7 +44,8 @@ def test_orders_at_the_edges(W):
 @pytest.mark.parametrize("W", [1, 1000, 1025, 4096])
 @pytest.mark.parametrize("long_len", [1024, 1025, 2500, 9000])
 def test_long_chains_in_one_workgroup(W, long_len):
-    # ranges of a tile's stages within the staging capacity (short chains of none or one stage) and beyond
+    # ranges of a tile's stages within the staging capacity (short chains of none or one stage) and beyond; all of
+    # one workgroup but 4,096 workflows of up to 11 stages and 9,000, whose 49,000 stages are tiled
     rng = np.random.default_rng(W + long_len)
     for hi in (2, 12):
         lens = rng.integers(0, hi, W)
@@ -67,7 +68,7 @@ def test_one_workgroup_where_buckets_fill(W, kind):
     elif kind == "two":
         deadline = np.where(rng.random(W) < 0.5, 5, 9).astype(np.int64)
     elif kind in ("most", "crowded"):
-        size = 32 if kind == "most" else 33
+        size = (64 if W <= 1024 else 32) + (kind == "crowded")    # bucket_most of one or several keys a thread
         deadline = rng.permutation(np.arange(W) // size * 1_000_000).astype(np.int64)
     elif kind == "saturated":
         deadline[rng.random(W) < 0.4] = 2**62
