@@ -18,8 +18,8 @@
 // nodes short of room, one headroom, plans that fail) every short pair would be looked at, so after a few
 // sub-blocks short_pass goes on, with a bound for each node (the cheapest step of its plan, what all its
 // steps free) and, in small batches, up to eight wavefronts for the same stages: 8,192 stages on 4,096
-// nodes without headroom take 153 us, 796 without short_pass, 166 scoring every pair; 500,000 stages
-// 1,540, 2,010 and 1,490; with plans that free little 680, 1,940 and 3,090. (short_pass for all short pairs:
+// nodes without headroom take 165 us, 796 without short_pass, 168 scoring every pair; 500,000 stages
+// 1,650, 2,010 and 1,620; with plans that free little 680, 1,940 and 3,090. (short_pass for all short pairs:
 // 47 against 42 us on 512 nodes whose bounds prune well.)
 //
 // Three launches: ranks of the headrooms and the sorted node records; the penalty, proximity and
@@ -402,8 +402,8 @@ __device__ __forceinline__ WalkLds walk_lds(unsigned char* raw, int32_t padded) 
 // term, its least penalty and the fit on its first admitting node, evaluated as scores are (every
 // rounded operation is monotone, so no widening), and on that score only a lower node index enters. Where
 // one score fills the list, all blocks but those of lower indices go that way: 719,712 stages on 512
-// idle nodes of one kind (one result) take 74 us a call, 131,072 on 4,096 take 58, against 466 and 692
-// with every tie visited, and 146 and 367 scoring every pair. Apart from the loops that every stage
+// idle nodes of one kind (one result) take 78 us a call, 131,072 on 4,096 take 68, against 466 and 692
+// with every tie visited, and 150 and 400 scoring every pair. Apart from the loops that every stage
 // takes, whose registers decide how many wavefronts run (tests inside those loops: 51 against 48 us on
 // 719,712 stages without ties), so the stage's inputs are read again.
 template <int KT, bool kPlans>
