@@ -3,7 +3,8 @@
 // never falls as the key rises, whatever the rounding), counted with LDS atomics; a scan gives each
 // bucket its place, and within its bucket a pair's place is the number of smaller pairs there: six
 // barriers in all, where four radix passes take twenty. A bucket of more than bucket_most pairs
-// gives up, before the first count if a sample of the keys shows it. Keys equal to the smallest or the largest one (idle nodes' zeros, saturated slacks) and
+// gives up, before the first count if a sample of the keys shows it (up to 0.3 us; of all eight keys a thread 0.6
+// of 24 at 8,192 pairs). Keys equal to the smallest or the largest one (idle nodes' zeros, saturated slacks) and
 // outliers above the others would crowd buckets, so they get their own treatment (1.4 us of 14.2 at
 // 4,096 pairs). Not kept: twice the buckets (no change at 4,096 pairs), and a thread's pairs compared
 // round by round together (13.5 against 12.4 us).
@@ -47,14 +48,15 @@ __device__ __forceinline__ bool bucket_sort(const uint32_t (&key)[IPT], const ui
     low = min(low, __shfl_xor(low, off));
     high = max(high, __shfl_xor(high, off));
   }
-  // one key a wavefront, neither its smallest nor its largest, and how many others equal it there: over
-  // the wavefronts about as many as share a bucket
+  // one key a wavefront, neither its smallest nor its largest (so below the padding's), and how many others
+  // equal it there, among four of eight keys a thread: over the wavefronts about as many as share a bucket
+  constexpr int kSample = IPT > 4 ? 4 : IPT;
   uint32_t same = 0u;
   const uint64_t between = __ballot((int)idx[0] < n && key[0] != low && key[0] != high);
   if (between) {
     const uint32_t one = __builtin_amdgcn_readlane(key[0], __ffsll((unsigned long long)between) - 1);
 #pragma unroll
-    for (int j = 0; j < IPT; ++j) same += (uint32_t)__popcll(__ballot((int)idx[j] < n && key[j] == one));
+    for (int j = 0; j < kSample; ++j) same += (uint32_t)__popcll(__ballot(key[j] == one));
     same -= 1u;
   }
   if (lane == 0) {
@@ -83,7 +85,8 @@ __device__ __forceinline__ bool bucket_sort(const uint32_t (&key)[IPT], const ui
   const int last = 4 * (int)blockDim.x - 1;
   const float scale = (float)last / span;
   const uint32_t most = bucket_most(n_waves, IPT);
-  if (!(above(high, low) < INFINITY) || (low != high && !(scale < INFINITY)) || 5u * same > 4u * most) return false;
+  const bool crowded = 5u * (IPT / kSample) * same > 4u * most;
+  if (!(above(high, low) < INFINITY) || (low != high && !(scale < INFINITY)) || crowded) return false;
   // The smallest and the largest key are not counted: their pairs' places are the first and the last
   // ones, in index order.
   const uint64_t lanes_below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
