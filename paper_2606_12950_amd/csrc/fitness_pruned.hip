@@ -1044,8 +1044,8 @@ static bool tables_pay(int64_t n, int32_t n_nodes, int32_t k, bool plans) {
 }
 
 // The batches that the entry point takes. Its lines lie below those of tables_pay, between the two it
-// scores every pair: a caller with a workspace need not know which of the two is faster. Many (class, source, model) combinations make the tables themselves the cost: 640
-// of them take 5 us at 4,096 nodes.
+// scores every pair: a caller with a workspace need not know which of the two is faster. Many (class,
+// source, model) combinations make the tables themselves the cost: 640 of them take 5 us at 4,096 nodes.
 size_t fitness_workspace_bytes(int64_t n, int32_t n_models, int32_t n_nodes, int32_t n_src, int32_t n_classes,
                                int32_t k, bool plans) {
   if (k > 4 || n_nodes > kMaxNodes || n_nodes < 64) return 0;
